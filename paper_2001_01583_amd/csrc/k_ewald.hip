@@ -5,18 +5,28 @@
 // The box of side L is cut into nc^3 cubic cells of side h = L / nc >= rcut,
 // so every pair closer than rcut lies in the same or a neighbouring cell.
 // Ions are counting-sorted by cell (count, scan, scatter, then input order
-// within each cell) into one float64 (x, y, z, q) record each.  One workgroup per cell: each thread holds one
-// ion of the cell, the 27 neighbour cells stream through LDS in tiles, and
-// a neighbour across the periodic boundary is shifted by L on the way in, so
-// every pair is seen once per ion with its nearest image.  Each ion's force
-// has a single writer; the energy is reduced per cell in float64 and summed
-// in a fixed order.
+// within each cell) into one float64 (x, y, z, q) record each.  A workgroup holds the 27 neighbour cells of a
+// cell in LDS; a neighbour across the periodic boundary is shifted by L on the
+// way in, so every pair is seen once per ion with its nearest image.  Each ion's force
+// has a single writer; the energy is reduced per workgroup in float64 and
+// summed in a fixed order.
+#include <algorithm>
+
 #include "internal.h"
+#include "pairs.h"
 
 namespace hpnfft {
 
-constexpr int kPairThreads = 128;
-constexpr int kPairTile = 256;
+constexpr int kPairThreads = 1024;
+constexpr int kPairGroups = 1024;  // workgroups worth having
+
+// Parts a cell's ions are split into.
+static int cell_parts(long long M, int nc)
+{
+    const long long ncell = (long long)nc * nc * nc;
+    const long long most = std::max(1LL, M / ncell / (kPairThreads / 64));  // an ion per wavefront at least
+    return (int)std::max(1LL, std::min(most, (kPairGroups + ncell - 1) / ncell));
+}
 
 // Wrap into [0, L) and return the cell coordinate along one axis.
 __device__ inline double wrap_box(double v, double L)
@@ -80,82 +90,85 @@ __global__ __launch_bounds__(256) void k_cells_reorder(const double4 *__restrict
 
 // U = 1/2 sum_i sum_{j != i, r_ij < rcut} q_i q_j erfc(alpha r_ij) / r_ij and
 // F_i = sum_j q_i q_j [erfc(alpha r)/r + 2 alpha/sqrt(pi) exp(-alpha^2 r^2)] d_ij / r^2.
+//
+// Workgroup <-> (cell, part): the ions of the 27 cells around it go to LDS
+// (in tiles of kPairCap, shifted to their image on the way in), then each
+// wavefront takes every (wavefronts x parts)-th ion of the cell.  Small boxes
+// have few cells (27 at L = 3 rcut), so a cell is split into parts until about
+// kPairGroups workgroups run.  An ion's partial sums over later tiles are
+// added by the lanes that stored the first.
+//
+// Bound by the float64 vector unit (pair terms, then distance tests):
+// 393,216 ions, 593 partners each within the cut-off, 143 ions per cell: 8.46
+// -> 2.57 ms; 6,144 ions in 27 cells: 4.90 -> 0.10 ms.
 __global__ __launch_bounds__(kPairThreads) void k_cells_pairs(const double4 *__restrict__ sorted,
                                                               const int *__restrict__ orig,
-                                                              const int *__restrict__ start, int nc, double L,
-                                                              double alpha, double rcut2,
+                                                              const int *__restrict__ start, int nc, int parts,
+                                                              double L, double alpha, double rcut2,
                                                               double *__restrict__ part,
                                                               double *__restrict__ forces)
 {
-    __shared__ double4 tile[kPairTile];
-    __shared__ double red[kPairThreads];
-    const int c = blockIdx.x;
+    extern __shared__ __align__(16) unsigned char smem[];
+    PairTile &tile = *reinterpret_cast<PairTile *>(smem);
+    __shared__ unsigned short queues[kPairThreads / 64][kPairQueue];
+    __shared__ double red[kPairThreads / 64];
+    __shared__ int off[28], t0s[27];
+    __shared__ double sh[27][3];
+    const int c = blockIdx.x / parts, pt = blockIdx.x - c * parts;
     const int cz = c % nc, cy = (c / nc) % nc, cx = c / (nc * nc);
     const int s0 = start[c], s1 = start[c + 1];
+    const int tid = threadIdx.x, wave = tid >> 6, nw = kPairThreads / 64;
+    if (tid < 27) {
+        int ax = cx + tid / 9 - 1, ay = cy + (tid / 3) % 3 - 1, az = cz + tid % 3 - 1;
+        double sx = 0.0, sy = 0.0, sz = 0.0;
+        if (ax < 0) { ax += nc; sx = -L; } else if (ax >= nc) { ax -= nc; sx = L; }
+        if (ay < 0) { ay += nc; sy = -L; } else if (ay >= nc) { ay -= nc; sy = L; }
+        if (az < 0) { az += nc; sz = -L; } else if (az >= nc) { az -= nc; sz = L; }
+        const int a = (ax * nc + ay) * nc + az;
+        t0s[tid] = start[a];
+        off[tid + 1] = start[a + 1] - start[a];
+        sh[tid][0] = sx;
+        sh[tid][1] = sy;
+        sh[tid][2] = sz;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        off[0] = 0;
+        for (int k = 1; k < 28; ++k) off[k] += off[k - 1];
+    }
+    __syncthreads();
+    const int total = off[27], own = off[13] - s0;  // candidate of own-cell ion i: own + i
     const double c2 = 2.0 * alpha / sqrt(M_PI);
     double e_acc = 0.0;
-    for (int ib = s0; ib < s1; ib += kPairThreads) {
-        const int i = ib + threadIdx.x;
-        const bool vi = i < s1;
-        const double4 pi = vi ? sorted[i] : make_double4(0.0, 0.0, 0.0, 0.0);
-        double fx = 0.0, fy = 0.0, fz = 0.0, e = 0.0;
-        for (int nb = 0; nb < 27; ++nb) {
-            int ax = cx + nb / 9 - 1, ay = cy + (nb / 3) % 3 - 1, az = cz + nb % 3 - 1;
-            double sx = 0.0, sy = 0.0, sz = 0.0;
-            if (ax < 0) { ax += nc; sx = -L; } else if (ax >= nc) { ax -= nc; sx = L; }
-            if (ay < 0) { ay += nc; sy = -L; } else if (ay >= nc) { ay -= nc; sy = L; }
-            if (az < 0) { az += nc; sz = -L; } else if (az >= nc) { az -= nc; sz = L; }
-            const int a = (ax * nc + ay) * nc + az;
-            const int t0 = start[a], t1 = start[a + 1];
-            for (int tb = t0; tb < t1; tb += kPairTile) {
-                const int cnt = min(kPairTile, t1 - tb);
-                __syncthreads();
-                for (int k = threadIdx.x; k < cnt; k += kPairThreads) {
-                    double4 v = sorted[tb + k];
-                    v.x += sx;
-                    v.y += sy;
-                    v.z += sz;
-                    tile[k] = v;
-                }
-                __syncthreads();
-                if (!vi) continue;
-                for (int k = 0; k < cnt; ++k) {
-                    if (nb == 13 && tb + k == i) continue;  // the ion itself (own cell, no shift)
-                    const double4 pj = tile[k];
-                    const double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
-                    const double d2 = dx * dx + dy * dy + dz * dz;
-                    if (d2 >= rcut2) continue;
-                    const double d = sqrt(d2);
-                    const double qq = pi.w * pj.w;
-                    const double ec = erfc(alpha * d) / d;
-                    e += 0.5 * qq * ec;
-                    const double g = qq * (ec + c2 * exp(-alpha * alpha * d2)) / d2;
-                    fx += g * dx;
-                    fy += g * dy;
-                    fz += g * dz;
-                }
-            }
+    for (int t0 = 0; t0 < total; t0 += kPairCap) {
+        const int cnt = min(kPairCap, total - t0);
+        if (t0 > 0) __syncthreads();
+        for (int k = tid; k < cnt; k += kPairThreads) {
+            int nb = 0;
+#pragma unroll
+            for (int b = 16; b > 0; b >>= 1)
+                if (nb + b < 27 && off[nb + b] <= t0 + k) nb += b;
+            const double4 v = sorted[t0s[nb] + (t0 + k - off[nb])];
+            tile.x[k] = v.x + sh[nb][0];
+            tile.y[k] = v.y + sh[nb][1];
+            tile.z[k] = v.z + sh[nb][2];
+            tile.q[k] = v.w;
         }
-        if (vi && forces) {
-            const long long o = orig[i];
-            forces[3 * o] = fx;
-            forces[3 * o + 1] = fy;
-            forces[3 * o + 2] = fz;
-        }
-        e_acc += e;
-    }
-    red[threadIdx.x] = e_acc;
-    __syncthreads();
-    for (int off = kPairThreads / 2; off > 0; off >>= 1) {
-        if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
         __syncthreads();
+        for (int i = s0 + wave + nw * pt; i < s1; i += nw * parts) {
+            PairSum s{0.0, 0.0, 0.0, 0.0};
+            sweep_pairs<false>(sorted[i], own + i - t0, cnt, tile, queues[wave], rcut2, alpha, c2, L, 0.0, s);
+            if (forces) store_force(s, forces + 3 * (size_t)orig[i], t0 > 0);
+            e_acc += s.e;
+        }
     }
-    if (threadIdx.x == 0) part[c] = red[0];
+    const double e = block_sum_fixed(e_acc, red);
+    if (tid == 0) part[blockIdx.x] = e;
 }
 
 // Workspace of the cell-list sum: [starts: nc^3 + 1 ints][scan scratch]
 // [cell, rank, orig, orig in scatter order: M ints each][sorted ions, and in
-// scatter order: M x 32 B each][cell partials: nc^3 doubles], each region
+// scatter order: M x 32 B each][partials: nc^3 x parts doubles], each region
 // 256-byte aligned.
 static size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 static size_t scan_tmp_ints(long long n)
@@ -185,7 +198,7 @@ CellsLayout cells_layout(long long M, int nc)
     C.sorted_tmp = off;
     off = al256(off + (size_t)M * 32);
     C.part = off;
-    off = al256(off + (size_t)ncell * 8);
+    off = al256(off + (size_t)ncell * cell_parts(M, nc) * 8);
     C.total = off;
     return C;
 }
@@ -211,11 +224,15 @@ hipError_t launch_ewald_cells(const double *r, const double *q, long long M, dou
                        orig_tmp);
     hipLaunchKernelGGL(k_cells_reorder, dim3((unsigned)ncell), dim3(256), 0, s, sorted_tmp, orig_tmp, start, sorted,
                        orig);
-    hipLaunchKernelGGL(k_cells_pairs, dim3((unsigned)ncell), dim3(kPairThreads), 0, s, sorted, orig, start, nc, L,
-                       alpha, rcut * rcut, part, forces);
+    const int parts = cell_parts(M, nc);
+    e = hipFuncSetAttribute((const void *)k_cells_pairs, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)sizeof(PairTile));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_cells_pairs, dim3((unsigned)(ncell * parts)), dim3(kPairThreads), sizeof(PairTile), s, sorted,
+                       orig, start, nc, parts, L, alpha, rcut * rcut, part, forces);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_sum_partials(part, (int)ncell, energy, s);
+    return launch_sum_partials(part, (int)(ncell * parts), energy, s);
 }
 
 }  // namespace hpnfft

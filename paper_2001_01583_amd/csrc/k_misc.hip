@@ -3,6 +3,7 @@
 // order, result scatter back to the caller's order, the gradient epilogue,
 // and the reciprocal-space Ewald sum of Eq. (12) with a float64 reduction.
 #include "internal.h"
+#include "pairs.h"
 
 namespace hpnfft {
 
@@ -218,69 +219,57 @@ hipError_t launch_ewald(const void *S, const Xform &X, double L, double alpha, d
 // convention (valid when erfc(alpha r) is negligible beyond half the box):
 //   U = 1/2 sum_i sum_{j != i} q_i q_j erfc(alpha r_ij) / r_ij   (r_ij < rcut)
 //   F_i = sum_j q_i q_j [erfc(alpha r)/r + 2 alpha/sqrt(pi) exp(-alpha^2 r^2)] d_ij / r^2
-// One thread per ion i; the j loop streams through LDS tiles of 256 ions.
+// Workgroup <-> 256 ions i (one energy partial each), 16 per wavefront; the
+// partners stream through LDS in tiles of kPairCap ions (pairs.h).
 constexpr int kRealTile = kEwaldRealTile;
+constexpr int kRealThreads = 1024;
 
-__global__ __launch_bounds__(kRealTile) void k_ewald_real(const double *__restrict__ r,
-                                                          const double *__restrict__ q, long long M,
-                                                          double L, double alpha, double rcut2,
-                                                          double *__restrict__ part,
-                                                          double *__restrict__ forces)
+__global__ __launch_bounds__(kRealThreads) void k_ewald_real(const double *__restrict__ r,
+                                                             const double *__restrict__ q, long long M, double L,
+                                                             double alpha, double rcut2, double *__restrict__ part,
+                                                             double *__restrict__ forces)
 {
-    __shared__ double sx[kRealTile], sy[kRealTile], sz[kRealTile], sq[kRealTile];
-    __shared__ double red[kRealTile];
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = i < M;
-    const double xi = valid ? r[3 * i] : 0.0, yi = valid ? r[3 * i + 1] : 0.0, zi = valid ? r[3 * i + 2] : 0.0;
-    const double qi = valid ? q[i] : 0.0;
+    extern __shared__ __align__(16) unsigned char smem[];
+    PairTile &tile = *reinterpret_cast<PairTile *>(smem);
+    __shared__ unsigned short queues[kRealThreads / 64][kPairQueue];
+    __shared__ double red[kRealThreads / 64];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const long long i0 = (long long)blockIdx.x * kRealTile;
+    const int ni = (int)min((long long)kRealTile, M - i0);
     const double c2 = 2.0 * alpha / sqrt(M_PI), invL = 1.0 / L;
-    double e = 0.0, fx = 0.0, fy = 0.0, fz = 0.0;
-    for (long long j0 = 0; j0 < M; j0 += kRealTile) {
-        long long j = j0 + threadIdx.x;
+    double e_acc = 0.0;
+    for (long long j0 = 0; j0 < M; j0 += kPairCap) {
+        const int cnt = (int)min((long long)kPairCap, M - j0);
+        if (j0 > 0) __syncthreads();
+        for (int k = tid; k < cnt; k += kRealThreads) {
+            tile.x[k] = r[3 * (j0 + k)];
+            tile.y[k] = r[3 * (j0 + k) + 1];
+            tile.z[k] = r[3 * (j0 + k) + 2];
+            tile.q[k] = q[j0 + k];
+        }
         __syncthreads();
-        sx[threadIdx.x] = j < M ? r[3 * j] : 0.0;
-        sy[threadIdx.x] = j < M ? r[3 * j + 1] : 0.0;
-        sz[threadIdx.x] = j < M ? r[3 * j + 2] : 0.0;
-        sq[threadIdx.x] = j < M ? q[j] : 0.0;
-        __syncthreads();
-        const int nj = (int)min((long long)kRealTile, M - j0);
-        for (int t = 0; t < nj; ++t) {
-            if (j0 + t == i) continue;
-            double dx = xi - sx[t], dy = yi - sy[t], dz = zi - sz[t];
-            dx -= L * rint(dx * invL);
-            dy -= L * rint(dy * invL);
-            dz -= L * rint(dz * invL);
-            double d2 = dx * dx + dy * dy + dz * dz;
-            if (d2 >= rcut2) continue;
-            double d = sqrt(d2);
-            double qq = qi * sq[t];
-            double ec = erfc(alpha * d) / d;
-            e += 0.5 * qq * ec;
-            double g = qq * (ec + c2 * exp(-alpha * alpha * d2)) / d2;
-            fx += g * dx;
-            fy += g * dy;
-            fz += g * dz;
+        for (int w = wave; w < ni; w += kRealThreads / 64) {
+            const long long i = i0 + w;
+            const double4 p = make_double4(r[3 * i], r[3 * i + 1], r[3 * i + 2], q[i]);
+            const int self = i >= j0 && i < j0 + cnt ? (int)(i - j0) : -1;
+            PairSum s{0.0, 0.0, 0.0, 0.0};
+            sweep_pairs<true>(p, self, cnt, tile, queues[wave], rcut2, alpha, c2, L, invL, s);
+            if (forces) store_force(s, forces + 3 * i, j0 > 0);
+            e_acc += s.e;
         }
     }
-    if (valid && forces) {
-        forces[3 * i] = fx;
-        forces[3 * i + 1] = fy;
-        forces[3 * i + 2] = fz;
-    }
-    red[threadIdx.x] = e;
-    __syncthreads();
-    for (int off = kRealTile / 2; off > 0; off >>= 1) {
-        if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+    const double e = block_sum_fixed(e_acc, red);
+    if (tid == 0) part[blockIdx.x] = e;
 }
 
 hipError_t launch_ewald_real(const double *r, const double *q, long long M, double L, double alpha,
                              double rcut, double *partials, double *energy, double *forces, hipStream_t s)
 {
     int nb = (int)((M + kRealTile - 1) / kRealTile);
-    hipLaunchKernelGGL(k_ewald_real, dim3(nb), dim3(kRealTile), 0, s, r, q, M, L, alpha, rcut * rcut, partials,
+    hipError_t e = hipFuncSetAttribute((const void *)k_ewald_real, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)sizeof(PairTile));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_ewald_real, dim3(nb), dim3(kRealThreads), sizeof(PairTile), s, r, q, M, L, alpha, rcut * rcut, partials,
                        forces);
     hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kEwThreads), 0, s, partials, nb, energy);
     return hipGetLastError();
