@@ -28,6 +28,7 @@ struct Xform {
     long long M;       // points
     long long poff;    // first sorted point of this transform (packed arrays)
     long long foff;    // first frequency of this transform (packed fhat)
+    long long goff;    // points of the box-method transforms before this one
     long long key_off; // first entry of this transform's cell_start table
     void *grid;        // n0 n1 n2 complex
     void *tmpA;        // n0 n1 N2 complex
@@ -53,8 +54,21 @@ __host__ __device__ inline int box_key(const int c[3], const int n[3], const int
 {
     return (box_of(c[0], n[0], nb[0]) * nb[1] + box_of(c[1], n[1], nb[1])) * nb[2] + box_of(c[2], n[2], nb[2]);
 }
-// Box method record header: plane c0, and (c1 << 11) | c2 (cells < 2048).
+// Record headers: plane c0, and the other two cells (below 2048).  Box method:
+// (c1 << 11) | c2.  Line method: the same shifted left by three bits, with
+// the point's line in its block of lines (0 .. 7) below.
 constexpr int kBoxCellBits = 11;
+constexpr int kLineBits = 3;
+__host__ __device__ constexpr int head_line(int y) { return y & ((1 << kLineBits) - 1); }
+struct PointHead {
+    int c0, c1, c2, xr;  // cell, line in its block
+    bool lines;          // line method: dim 0 in slot order, dim 2 in lane order
+};
+__host__ __device__ inline PointHead unpack_head(int x, int y, bool box)
+{
+    const int c = box ? y : y >> kLineBits;
+    return PointHead{x, c >> kBoxCellBits, c & ((1 << kBoxCellBits) - 1), box ? 0 : head_line(y), !box};
+}
 
 // Work item of an FFT pass: `count` pencils starting at (outer, inner0).
 struct FItem {
@@ -174,16 +188,15 @@ inline LdsLayout lds_fit(int T, int Zs, int M2, size_t R, int kind, bool comp)
 
 // Threads per workgroup the sweep kernels are compiled for.  A 1024-thread
 // workgroup leaves 128 registers per lane.  The spread fits (float64 with a
-// few spills, measured faster than 512 threads); the interpolation variants
-// that hold more window values per lane (the gradient, float64 blocked
-// lines) are compiled for 512.
+// few spills, measured faster than 512 threads); the interpolation variant
+// that holds more window values per lane (float64 blocked lines) is compiled
+// for 512.
 // Windows wider than 16 cells (m > 8) hold 2m complex values per lane in the
 // register window and are compiled for 256 threads (up to 512 registers).
 __host__ __device__ constexpr int spread_max_threads(int, int M2) { return M2 > 16 ? 256 : 1024; }
-__host__ __device__ constexpr int interp_max_threads(int real_bytes, int M2, bool grad)
+__host__ __device__ constexpr int interp_max_threads(int real_bytes, int M2)
 {
-    return M2 > 16 ? 256
-                   : (grad && (real_bytes == 8 || M2 >= 12)) || (real_bytes == 8 && block_w(M2) > 1) ? 512 : 1024;
+    return M2 > 16 ? 256 : real_bytes == 8 && block_w(M2) > 1 ? 512 : 1024;
 }
 
 // FFT pass identifiers.
@@ -222,7 +235,7 @@ hipError_t launch_spread(int m, const Xform *dxf, const SItem *items, int nitems
                          Tiling t, const unsigned char *rec, size_t rec_bytes, const R *fs, const int *cell_start,
                          hipStream_t s);
 template <typename R>
-hipError_t launch_interp(int m, bool grad, const Xform *dxf, const SItem *items, int nitems, int *queue,
+hipError_t launch_interp(int m, const Xform *dxf, const SItem *items, int nitems, int *queue,
                          Tiling t, const unsigned char *rec, size_t rec_bytes, const int *cell_start,
                          R *outs, hipStream_t s);
 // Interpolation by groups of single lines (lines.h), one transform per
@@ -248,9 +261,12 @@ template <typename R>
 hipError_t launch_spread_det(int m, const Xform *dxf, const SItem *items, int nitems, int max_cells,
                              const unsigned char *rec, size_t rec_bytes, const R *fs, const int *cell_start,
                              hipStream_t s);
+
+// Interpolation by gathering (k_gather.hip): all points, or those of the
+// transforms that use boxes; total: their number.  outs need not be cleared.
 template <typename R>
-hipError_t launch_interp_det(int m, bool grad, const Xform *dxf, int B, long long Mtot, const unsigned char *rec,
-                             size_t rec_bytes, R *outs, int cus, hipStream_t s);
+hipError_t launch_interp_gather(int m, bool grad, const Xform *dxf, int B, bool all, long long total,
+                                const unsigned char *rec, size_t rec_bytes, R *outs, hipStream_t s);
 
 // Box method (k_boxes.hip): every workgroup owns one output box of the grid
 // and takes every point whose window reaches it.
@@ -258,10 +274,6 @@ template <typename R>
 hipError_t launch_spread_box(int m, const Xform *dxf, const SItem *items, int nitems, int *queue, int max_cells,
                              const unsigned char *rec, size_t rec_bytes, const R *fs, const int *cell_start,
                              hipStream_t s);
-template <typename R>
-hipError_t launch_interp_box(int m, bool grad, const Xform *dxf, const SItem *items, int nitems, int *queue,
-                             int max_cells, const unsigned char *rec, size_t rec_bytes, const int *cell_start,
-                             R *outs, hipStream_t s);
 
 // Fixed-order sum of n float64 partials into *out (one workgroup).
 hipError_t launch_sum_partials(const double *part, int n, double *out, hipStream_t s);

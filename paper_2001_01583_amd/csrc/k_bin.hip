@@ -295,7 +295,8 @@ __device__ inline long long scatter_point(long long j, const double *__restrict_
             }
         }
     }
-    head = nb0 ? make_int2(c[0], (c[1] << kBoxCellBits) | c[2]) : make_int2(c[0], c[2] & (block_w(M2) - 1));
+    const int c12 = (c[1] << kBoxCellBits) | c[2];
+    head = make_int2(c[0], nb0 ? c12 : (c12 << kLineBits) | (c[2] & (block_w(M2) - 1)));
     return pos;
 }
 

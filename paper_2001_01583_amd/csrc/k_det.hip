@@ -215,88 +215,6 @@ __global__ __launch_bounds__(64) void k_spread_det(const Xform *__restrict__ xfs
 }
 
 // ---------------------------------------------------------------------------
-template <typename R> __device__ inline R det_wave_sum(R v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-template <typename R, bool GRAD>
-__global__ __launch_bounds__(256) void k_interp_det(const Xform *__restrict__ xfs, int B, long long Mtot, int m,
-                                                    const unsigned char *__restrict__ rec, int rec_bytes,
-                                                    R *__restrict__ outs)
-{
-    constexpr int NO = GRAD ? 4 : 1;
-    const int lane = threadIdx.x & 63, M2 = 2 * m;
-    const int off_pz = (int)rec_off_pz(M2, sizeof(R));
-    const int off_d = (int)rec_prefix(M2, sizeof(R)) / (int)sizeof(R);
-    const long long wid = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const long long nw = ((long long)gridDim.x * blockDim.x) >> 6;
-    for (long long pos = wid; pos < Mtot; pos += nw) {
-        // the transform of sorted point pos (packed in order)
-        int lo = 0, hi = B;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (xfs[mid].poff <= pos) lo = mid;
-            else hi = mid;
-        }
-        const Xform &X = xfs[lo];
-        const R *grid = reinterpret_cast<const R *>(X.grid);
-        const unsigned char *rp = rec + pos * rec_bytes;
-        const int2 hd = *reinterpret_cast<const int2 *>(rp + off_pz);
-        const int c0 = hd.x, c1 = hd.y >> kBoxCellBits, c2 = hd.y & ((1 << kBoxCellBits) - 1);
-        const R *ps = reinterpret_cast<const R *>(rp);
-        const R *dp = ps + off_d;
-        R v[2 * NO];
-#pragma unroll
-        for (int q = 0; q < 2 * NO; ++q) v[q] = R(0);
-        for (int i = lane; i < M2 * M2; i += 64) {
-            const int t1 = i / M2, t2 = i % M2;
-            int l1 = c1 - m + 1 + t1, l2 = c2 - m + 1 + t2;
-            l1 += l1 < 0 ? X.n[1] : (l1 >= X.n[1] ? -X.n[1] : 0);
-            l2 += l2 < 0 ? X.n[2] : (l2 >= X.n[2] ? -X.n[2] : 0);
-            R sr = R(0), si = R(0), dr = R(0), di = R(0);
-            for (int t0 = 0; t0 < M2; ++t0) {
-                int l0 = c0 - m + 1 + t0;
-                l0 += l0 < 0 ? X.n[0] : (l0 >= X.n[0] ? -X.n[0] : 0);
-                const size_t gi = (((size_t)l0 * X.n[1] + l1) * X.n[2] + l2) * 2;
-                const R gr = grid[gi], gim = grid[gi + 1];
-                const R w = ps[t0];
-                sr = fma(w, gr, sr);
-                si = fma(w, gim, si);
-                if constexpr (GRAD) {
-                    const R dw = dp[t0];
-                    dr = fma(dw, gr, dr);
-                    di = fma(dw, gim, di);
-                }
-            }
-            const R w1 = ps[M2 + t1], w2 = ps[2 * M2 + t2];
-            const R w12 = w1 * w2;
-            v[0] = fma(sr, w12, v[0]);
-            v[1] = fma(si, w12, v[1]);
-            if constexpr (GRAD) {
-                const R d1 = dp[M2 + t1] * w2, d2 = w1 * dp[2 * M2 + t2];
-                v[2] = fma(dr, w12, v[2]);
-                v[3] = fma(di, w12, v[3]);
-                v[4] = fma(sr, d1, v[4]);
-                v[5] = fma(si, d1, v[5]);
-                v[6] = fma(sr, d2, v[6]);
-                v[7] = fma(si, d2, v[7]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 2 * NO; ++q) v[q] = det_wave_sum(v[q]);
-        if (lane < 2 * NO) {
-            R mine = v[0];
-#pragma unroll
-            for (int q = 1; q < 2 * NO; ++q) mine = lane == q ? v[q] : mine;
-            outs[pos * (2 * NO) + lane] = mine;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 template <typename R>
 hipError_t launch_spread_det(int m, const Xform *dxf, const SItem *items, int nitems, int max_cells,
                              const unsigned char *rec, size_t rec_bytes, const R *fs, const int *cell_start,
@@ -312,25 +230,9 @@ hipError_t launch_spread_det(int m, const Xform *dxf, const SItem *items, int ni
     return hipGetLastError();
 }
 
-template <typename R>
-hipError_t launch_interp_det(int m, bool grad, const Xform *dxf, int B, long long Mtot, const unsigned char *rec,
-                             size_t rec_bytes, R *outs, int cus, hipStream_t s)
-{
-    if (Mtot <= 0) return hipSuccess;
-    const long long waves = std::min<long long>(Mtot, (long long)cus * 64);
-    const unsigned blocks = (unsigned)((waves + 3) / 4);
-    auto kern = grad ? k_interp_det<R, true> : k_interp_det<R, false>;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, dxf, B, Mtot, m, rec, (int)rec_bytes, outs);
-    return hipGetLastError();
-}
-
 template hipError_t launch_spread_det<double>(int, const Xform *, const SItem *, int, int, const unsigned char *,
                                               size_t, const double *, const int *, hipStream_t);
 template hipError_t launch_spread_det<float>(int, const Xform *, const SItem *, int, int, const unsigned char *,
                                              size_t, const float *, const int *, hipStream_t);
-template hipError_t launch_interp_det<double>(int, bool, const Xform *, int, long long, const unsigned char *,
-                                              size_t, double *, int, hipStream_t);
-template hipError_t launch_interp_det<float>(int, bool, const Xform *, int, long long, const unsigned char *, size_t,
-                                             float *, int, hipStream_t);
 
 }  // namespace hpnfft

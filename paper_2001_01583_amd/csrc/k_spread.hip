@@ -11,7 +11,7 @@ hipError_t launch_spread_wide(int m, const Xform *dxf, const SItem *items, int n
                               const unsigned char *rec, size_t rec_bytes, const R *fs, const int *cell_start,
                               hipStream_t s);
 template <typename R>
-hipError_t launch_interp_wide(int m, bool grad, const Xform *dxf, const SItem *items, int nitems, int *queue,
+hipError_t launch_interp_wide(int m, const Xform *dxf, const SItem *items, int nitems, int *queue,
                               Tiling t, const unsigned char *rec, size_t rec_bytes, const int *cs, R *outs,
                               hipStream_t s);
 template <typename R>
@@ -38,16 +38,15 @@ hipError_t launch_spread(int m, const Xform *dxf, const SItem *items, int nitems
 }
 
 template <typename R>
-hipError_t launch_interp(int m, bool grad, const Xform *dxf, const SItem *items, int nitems, int *queue,
+hipError_t launch_interp(int m, const Xform *dxf, const SItem *items, int nitems, int *queue,
                          Tiling t, const unsigned char *rec, size_t rec_bytes, const int *cs, R *outs,
                          hipStream_t s)
 {
-    if (m == 4 && !grad && t.ring && ring_tiling(8, t.T, t.Zs))
+    if (m == 4 && t.ring && ring_tiling(8, t.T, t.Zs))
         return interp_ring<R>(dxf, items, nitems, queue, t, rec, rec_bytes, cs, outs, s);
 #define HPNFFT_INTERP_CASE(MM)                                                                        \
     case MM:                                                                                          \
-        return grad ? interp_m<R, 2 * MM, true>(dxf, items, nitems, queue, t, rec, rec_bytes, cs, outs, s) \
-                    : interp_m<R, 2 * MM, false>(dxf, items, nitems, queue, t, rec, rec_bytes, cs, outs, s);
+        return interp_m<R, 2 * MM>(dxf, items, nitems, queue, t, rec, rec_bytes, cs, outs, s);
     switch (m) {
         HPNFFT_INTERP_CASE(1)
         HPNFFT_INTERP_CASE(2)
@@ -57,7 +56,7 @@ hipError_t launch_interp(int m, bool grad, const Xform *dxf, const SItem *items,
         HPNFFT_INTERP_CASE(6)
         HPNFFT_INTERP_CASE(7)
         HPNFFT_INTERP_CASE(8)
-    default: return launch_interp_wide<R>(m, grad, dxf, items, nitems, queue, t, rec, rec_bytes, cs, outs, s);
+    default: return launch_interp_wide<R>(m, dxf, items, nitems, queue, t, rec, rec_bytes, cs, outs, s);
     }
 #undef HPNFFT_INTERP_CASE
 }
@@ -78,9 +77,9 @@ template hipError_t launch_spread<double>(int, const Xform *, const SItem *, int
                                           const unsigned char *, size_t, const double *, const int *, hipStream_t);
 template hipError_t launch_spread<float>(int, const Xform *, const SItem *, int, int *, Tiling,
                                          const unsigned char *, size_t, const float *, const int *, hipStream_t);
-template hipError_t launch_interp<double>(int, bool, const Xform *, const SItem *, int, int *, Tiling,
+template hipError_t launch_interp<double>(int, const Xform *, const SItem *, int, int *, Tiling,
                                           const unsigned char *, size_t, const int *, double *, hipStream_t);
-template hipError_t launch_interp<float>(int, bool, const Xform *, const SItem *, int, int *, Tiling,
+template hipError_t launch_interp<float>(int, const Xform *, const SItem *, int, int *, Tiling,
                                          const unsigned char *, size_t, const int *, float *, hipStream_t);
 
 }  // namespace hpnfft

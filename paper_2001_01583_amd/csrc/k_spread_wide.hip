@@ -29,14 +29,13 @@ hipError_t launch_spread_wide(int m, const Xform *dxf, const SItem *items, int n
 }
 
 template <typename R>
-hipError_t launch_interp_wide(int m, bool grad, const Xform *dxf, const SItem *items, int nitems, int *queue,
+hipError_t launch_interp_wide(int m, const Xform *dxf, const SItem *items, int nitems, int *queue,
                               Tiling t, const unsigned char *rec, size_t rec_bytes, const int *cs, R *outs,
                               hipStream_t s)
 {
 #define HPNFFT_INTERP_CASE(MM)                                                                        \
     case MM:                                                                                          \
-        return grad ? interp_m<R, 2 * MM, true>(dxf, items, nitems, queue, t, rec, rec_bytes, cs, outs, s) \
-                    : interp_m<R, 2 * MM, false>(dxf, items, nitems, queue, t, rec, rec_bytes, cs, outs, s);
+        return interp_m<R, 2 * MM>(dxf, items, nitems, queue, t, rec, rec_bytes, cs, outs, s);
     switch (m) {
         HPNFFT_INTERP_CASE(9)
         HPNFFT_INTERP_CASE(10)
@@ -56,9 +55,9 @@ template hipError_t launch_spread_wide<double>(int, const Xform *, const SItem *
 template hipError_t launch_spread_wide<float>(int, const Xform *, const SItem *, int, int *, Tiling,
                                               const unsigned char *, size_t, const float *, const int *,
                                               hipStream_t);
-template hipError_t launch_interp_wide<double>(int, bool, const Xform *, const SItem *, int, int *, Tiling,
+template hipError_t launch_interp_wide<double>(int, const Xform *, const SItem *, int, int *, Tiling,
                                                const unsigned char *, size_t, const int *, double *, hipStream_t);
-template hipError_t launch_interp_wide<float>(int, bool, const Xform *, const SItem *, int, int *, Tiling,
+template hipError_t launch_interp_wide<float>(int, const Xform *, const SItem *, int, int *, Tiling,
                                               const unsigned char *, size_t, const int *, float *, hipStream_t);
 
 }  // namespace hpnfft

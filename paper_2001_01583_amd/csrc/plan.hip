@@ -82,7 +82,7 @@ struct hpnfft_plan_s {
     unsigned flags = 0;
     std::vector<Xform> hx;
     std::vector<long long> keys;
-    long long Mtot = 0, Ftot = 0;
+    long long Mtot = 0, Ftot = 0, Mbox = 0;  // points, frequencies, points of box transforms
     Tiling til{16, 16, 1024};
     hipStream_t stream = nullptr;
     char *ws = nullptr;
@@ -392,6 +392,11 @@ void choose_methods(hpnfft_plan_s *p)
         else if (p->method == HPNFFT_METHOD_BOXES) box = true;
         else box = (double)X.M < thr * (double)X.n[0] * X.n[1] * X.n[2];
         p->tbox[b] = box;
+    }
+    p->Mbox = 0;
+    for (int b = 0; b < p->B; ++b) {
+        p->hx[b].goff = p->Mbox;
+        if (p->tbox[b]) p->Mbox += p->hx[b].M;
     }
     p->any_box = std::count(p->tbox.begin(), p->tbox.end(), 1) > 0;
     p->any_lines = std::count(p->tbox.begin(), p->tbox.end(), 0) > 0;
@@ -996,9 +1001,10 @@ template <typename R> int run_forward(hpnfft_plan_s *p, const void *fhat, void *
     const Layout &L = p->L;
     hipStream_t s = p->stream;
     const Xform *dxf = p->at<Xform>(L.xf);
-    // the ring interpolation stores every point's value once; the other
-    // sweeps add partial sums into a cleared output
-    if (p->any_box || p->det() || !use_ring(p, p->til)) {
+    const bool lines = p->any_lines && !p->det();
+    // the gather and the ring interpolation store every point's value once;
+    // the other line sweeps add partial sums into a cleared output
+    if (lines && !use_ring(p, p->til)) {
         PhaseTimer t(p, HPNFFT_PH_ZERO);
         HCHECK(launch_zero(p->ws + L.outs, (size_t)p->Mtot * 2 * sizeof(R), s));
     }
@@ -1006,23 +1012,18 @@ template <typename R> int run_forward(hpnfft_plan_s *p, const void *fhat, void *
     if (rc) return rc;
     {
         PhaseTimer t(p, HPNFFT_PH_INTERP);
-        if (p->det())
-            HCHECK(launch_interp_det<R>(p->m, false, dxf, p->B, p->Mtot, p->at<unsigned char>(L.rec), L.rec_bytes,
-                                        p->at<R>(L.outs), p->cus, s));
-        else if (p->any_box)
-            HCHECK(launch_interp_box<R>(p->m, false, dxf, p->at<SItem>(L.bitems), p->nbitems,
-                                        p->at<int>(L.counters) + 1, p->max_cells, p->at<unsigned char>(L.rec),
-                                        L.rec_bytes, p->at<int>(L.cell_start), p->at<R>(L.outs), s));
-        if (p->any_lines && use_lines(p)) {
+        HCHECK(launch_interp_gather<R>(p->m, false, dxf, p->B, !lines, lines ? p->Mbox : p->Mtot,
+                                       p->at<unsigned char>(L.rec), L.rec_bytes, p->at<R>(L.outs), s));
+        if (lines && use_lines(p)) {
             for (size_t b = 0; b < p->hx.size(); ++b)
                 if (!p->tbox[b])
                     HCHECK(launch_interp_lines<R>(p->m, dxf + b, p->hx[b].n, p->at<int>(L.counters) + 1, p->til.T,
                                                   p->at<unsigned char>(L.rec), L.rec_bytes,
                                                   p->at<int>(L.cell_start), p->at<R>(L.outs), s));
-        } else if (p->any_lines) {
+        } else if (lines) {
             Tiling t = p->til;
             t.ring = use_ring(p, t);
-            HCHECK(launch_interp<R>(p->m, false, dxf, p->at<SItem>(L.items), p->nitems,
+            HCHECK(launch_interp<R>(p->m, dxf, p->at<SItem>(L.items), p->nitems,
                                     p->at<int>(L.counters) + 1, t, p->at<unsigned char>(L.rec), L.rec_bytes,
                                     p->at<int>(L.cell_start), p->at<R>(L.outs), s));
         }
@@ -1040,25 +1041,12 @@ int run_backward(hpnfft_plan_s *p, const void *f, const void *gfhat, void *grad_
     const Layout &L = p->L;
     hipStream_t s = p->stream;
     const Xform *dxf = p->at<Xform>(L.xf);
-    {
-        PhaseTimer t(p, HPNFFT_PH_ZERO);
-        HCHECK(launch_zero(p->ws + L.outs, L.outs_bytes, s));
-    }
     int rc = run_to_grid<R>(p, gfhat);
     if (rc) return rc;
     {
         PhaseTimer t(p, HPNFFT_PH_GRAD);
-        if (p->det())
-            HCHECK(launch_interp_det<R>(p->m, true, dxf, p->B, p->Mtot, p->at<unsigned char>(L.rec), L.rec_bytes,
-                                        p->at<R>(L.outs), p->cus, s));
-        else if (p->any_box)
-            HCHECK(launch_interp_box<R>(p->m, true, dxf, p->at<SItem>(L.bitems), p->nbitems,
-                                        p->at<int>(L.counters) + 1, p->max_cells, p->at<unsigned char>(L.rec),
-                                        L.rec_bytes, p->at<int>(L.cell_start), p->at<R>(L.outs), s));
-        if (p->any_lines)
-            HCHECK(launch_interp<R>(p->m, true, dxf, p->at<SItem>(L.items), p->nitems,
-                                    p->at<int>(L.counters) + 1, p->til, p->at<unsigned char>(L.rec), L.rec_bytes,
-                                    p->at<int>(L.cell_start), p->at<R>(L.outs), s));
+        HCHECK(launch_interp_gather<R>(p->m, true, dxf, p->B, true, p->Mtot, p->at<unsigned char>(L.rec),
+                                       L.rec_bytes, p->at<R>(L.outs), s));
     }
     {
         PhaseTimer t(p, HPNFFT_PH_GRAD_FIN);

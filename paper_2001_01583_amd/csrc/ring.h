@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kRingThreads, ring_spread_waves<R>()) void k_spread
                         const R a = p4 <= lastp ? f1 : R(0);
                         // column x < 8 is reached by lines j <= x, column x >= 8
                         // by lines j > x - 8 (dim 2 is stored in lane order)
-                        const R b = ((col & 7) < h.y) == (col >= 8) ? w2 : R(0);
+                        const R b = ((col & 7) < head_line(h.y)) == (col >= 8) ? w2 : R(0);
 #pragma unroll
                         for (int s = 0; s < 8; ++s) {
                             const R aw = a * (s < 4 ? w0a[s & 3] : w0b[s & 3]);
@@ -524,7 +524,7 @@ __global__ __launch_bounds__(kRingThreads, sizeof(R) == 4 ? 6 : 4) void k_interp
                     int tmin = uni(db), tmax = __builtin_amdgcn_readlane(db, lastp) + 7;
                     if (flat) tmin = tmax = 8;  // the impulse's plane only
                     // dim-2 weights of columns k4, 4 + k4, 8 + k4, 12 + k4
-                    const bool ja = k4 < h.y, jb = 4 + k4 < h.y;
+                    const bool ja = k4 < head_line(h.y), jb = 4 + k4 < head_line(h.y);
                     const R b0 = ja ? R(0) : w2a, b1 = jb ? R(0) : w2b;
                     const R b2 = ja ? w2a : R(0), b3 = jb ? w2b : R(0);
                     // per plane the contraction over the columns, its

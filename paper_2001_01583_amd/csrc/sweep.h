@@ -522,7 +522,7 @@ __global__ __launch_bounds__(spread_max_threads(sizeof(R), M2)) void k_spread(co
                 const int2 h0 = head_of(stage, a, ST16, OFF_PZ);
                 const int B0 = uni(h0.x) + m + 1;
                 const int Blast = plane_of(stage, b - 1, ST16, OFF_PZ, m);
-                int jn = uni(h0.y);
+                int jn = head_line(uni(h0.y));
                 const int f_lo = max(B0, -qshift);
                 const int nf = max(min(Blast + M2 - 1, g.zs - 1 - qshift) - f_lo + 1, 0);
                 const int p_end = max(Blast, f_lo + nf - 1);
@@ -563,7 +563,7 @@ __global__ __launch_bounds__(spread_max_threads(sizeof(R), M2)) void k_spread(co
                             last = p;
                             ++sl;
                             Bn = sl < b ? uni(hx.x) + m + 1 : kNoPlane;
-                            jn = uni(hx.y);
+                            jn = head_line(uni(hx.y));
                         }
                         if ((unsigned)(p - f_lo) < (unsigned)nf) flush(k, p);
 #pragma unroll
@@ -606,11 +606,10 @@ __global__ __launch_bounds__(spread_max_threads(sizeof(R), M2)) void k_spread(co
 }
 
 // ---------------------------------------------------------------------------
-// Interpolation.  Output per sorted point (atomically added to `outs`, which
-// the caller zeroes): one complex value, or with GRAD four complex values
-// (value, d/dx0, d/dx1, d/dx2).
-template <typename R, int M2, bool GRAD>
-__global__ __launch_bounds__(interp_max_threads(sizeof(R), M2, GRAD)) void k_interp(
+// Interpolation.  Output per sorted point: one complex value, atomically added
+// to `outs`, which the caller zeroes.
+template <typename R, int M2>
+__global__ __launch_bounds__(interp_max_threads(sizeof(R), M2)) void k_interp(
     const Xform *__restrict__ xfs, const SItem *__restrict__ items, int nitems, int *__restrict__ queue,
     int T, int Zs, int cap, const v4u *__restrict__ rec, int rs16, const int *__restrict__ cell_start,
     R *__restrict__ outs)
@@ -618,11 +617,9 @@ __global__ __launch_bounds__(interp_max_threads(sizeof(R), M2, GRAD)) void k_int
     constexpr int m = M2 / 2;
     constexpr int ROWS = M2 * M2;
     constexpr int NRG = (ROWS + 63) / 64;
-    constexpr int NO = GRAD ? 4 : 1;
     const ValueSlot vs{nullptr, 0, 0};  // interpolation does not read the values
-    constexpr int ST16 = (int)(rec_size(M2, sizeof(R), GRAD) / 16);
+    constexpr int ST16 = (int)(rec_prefix(M2, sizeof(R)) / 16);
     constexpr int OFF_PZ = (int)(rec_off_pz(M2, sizeof(R)) / 4);
-    constexpr int OFF_D = (int)(rec_prefix(M2, sizeof(R)) / sizeof(R));
     static_assert(rec_off_xr(M2, sizeof(R)) == rec_off_pz(M2, sizeof(R)) + 4 && rec_off_pz(M2, sizeof(R)) % 8 == 0,
                   "head_of reads the plane index and line offset as one int2");
     constexpr int BW = block_w(M2);
@@ -630,7 +627,7 @@ __global__ __launch_bounds__(interp_max_threads(sizeof(R), M2, GRAD)) void k_int
     extern __shared__ uint4 smem16[];
     unsigned char *smem = reinterpret_cast<unsigned char *>(smem16);
     __shared__ int s_item;
-    const LdsLayout LL = lds_layout(T, Zs, M2, sizeof(R), GRAD ? 2 : 1, false, cap);
+    const LdsLayout LL = lds_layout(T, Zs, M2, sizeof(R), 1, false, cap);
     const int LPR = T / BW;  // runs (blocks of lines) per tile row
     const int P = T + M2 - 1;
     const int plane = P * P;
@@ -644,7 +641,7 @@ __global__ __launch_bounds__(interp_max_threads(sizeof(R), M2, GRAD)) void k_int
     R *oacc = reinterpret_cast<R *>(smem + LL.out);
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int wave = uni(tid >> 6), lane = tid & 63, nwaves = nthr >> 6;
-    constexpr int PF = (sizeof(R) == 8 && M2 >= 12) || GRAD ? 2 : 4;
+    constexpr int PF = (sizeof(R) == 8 && M2 >= 12) ? 2 : 4;
 
     for (int it = next_item(queue, &s_item); it < nitems; it = next_item(queue, &s_item)) {
         const ItemGeom g = item_geom(items[it], xfs[items[it].xf], T, Zs, M2);
@@ -709,9 +706,9 @@ __global__ __launch_bounds__(interp_max_threads(sizeof(R), M2, GRAD)) void k_int
                 const int qshift = U - g.z0 - M2;
                 for (int c0 = a; c0 < b; c0 += 64) {
                     const int c1 = min(b, c0 + 64);
-                    R ores[2 * NO];
+                    R ores[2];
 #pragma unroll
-                    for (int i = 0; i < 2 * NO; ++i) ores[i] = R(0);
+                    for (int i = 0; i < 2; ++i) ores[i] = R(0);
                     for (int rg = 0; rg < NRG; ++rg) {
                         const int row = rg * 64 + lane;
                         const bool active = ROWS % 64 == 0 || row < ROWS;
@@ -752,31 +749,31 @@ __global__ __launch_bounds__(interp_max_threads(sizeof(R), M2, GRAD)) void k_int
                                 }
                             }
                         };
-                        R s0[2 * NO], s1[2 * NO], s2[2 * NO];
-                        auto feed = [&](int t, R (&v)[2 * NO]) {
+                        R s0[2], s1[2], s2[2];
+                        auto feed = [&](int t, R (&v)[2]) {
                             if (!(t & 1)) {
 #pragma unroll
-                                for (int i = 0; i < 2 * NO; ++i) s0[i] = v[i];
+                                for (int i = 0; i < 2; ++i) s0[i] = v[i];
                                 return;
                             }
 #pragma unroll
-                            for (int i = 0; i < 2 * NO; ++i) v[i] = halve32(s0[i], v[i]);
+                            for (int i = 0; i < 2; ++i) v[i] = halve32(s0[i], v[i]);
                             if (!(t & 2)) {
 #pragma unroll
-                                for (int i = 0; i < 2 * NO; ++i) s1[i] = v[i];
+                                for (int i = 0; i < 2; ++i) s1[i] = v[i];
                                 return;
                             }
 #pragma unroll
-                            for (int i = 0; i < 2 * NO; ++i) v[i] = halve16(s1[i], v[i]);
+                            for (int i = 0; i < 2; ++i) v[i] = halve16(s1[i], v[i]);
                             if (!(t & 4)) {
 #pragma unroll
-                                for (int i = 0; i < 2 * NO; ++i) s2[i] = v[i];
+                                for (int i = 0; i < 2; ++i) s2[i] = v[i];
                                 return;
                             }
                             // octet t-7 .. t complete: 8-lane group j holds
                             // point t - 7 + bitrev3(j); lane 8j + (t >> 3) keeps it
 #pragma unroll
-                            for (int i = 0; i < 2 * NO; ++i) {
+                            for (int i = 0; i < 2; ++i) {
                                 const R tot = halve8_sum(s2[i], v[i]);
                                 if ((lane & 7) == (t >> 3)) ores[i] += tot;
                             }
@@ -784,7 +781,7 @@ __global__ __launch_bounds__(interp_max_threads(sizeof(R), M2, GRAD)) void k_int
                         int sl = c0;
                         const int2 h0 = head_of(stage, c0, ST16, OFF_PZ);
                         int Bn = uni(h0.x) + m + 1;
-                        int jn = uni(h0.y);
+                        int jn = head_line(uni(h0.y));
                         int p = Bn - Bn % M2;
 #pragma unroll
                         for (int s = 0; s < M2 - 1; ++s)
@@ -820,39 +817,13 @@ __global__ __launch_bounds__(interp_max_threads(sizeof(R), M2, GRAD)) void k_int
                                     const R w1 = active ? ps[M2 + dy] : R(0);
                                     const R w2 = active ? ps[2 * M2 + xm] : R(0);
                                     const R w12 = w1 * w2;
-                                    R v[2 * NO];
+                                    R v[2];
                                     v[0] = sr * w12;
                                     v[1] = si * w12;
-                                    if constexpr (GRAD) {
-                                        const R *dp = ps + OFF_D;
-                                        R dr, di;
-                                        {
-                                            R ar[NW], ai[NW];
-#pragma unroll
-                                            for (int w = 0; w < NW; ++w) {
-                                                ar[w] = ai[w] = R(0);
-#pragma unroll
-                                                for (int s = 0; s < M2; ++s) {
-                                                    ar[w] = fma(gr[w][s], dp[s], ar[w]);
-                                                    ai[w] = fma(gi[w][s], dp[s], ai[w]);
-                                                }
-                                            }
-                                            dr = (NW > 1 && hi) ? ar[NW - 1] : ar[0];
-                                            di = (NW > 1 && hi) ? ai[NW - 1] : ai[0];
-                                        }
-                                        const R d1 = active ? dp[M2 + dy] * w2 : R(0);
-                                        const R d2 = active ? w1 * dp[2 * M2 + xm] : R(0);
-                                        v[2] = dr * w12;
-                                        v[3] = di * w12;
-                                        v[4] = sr * d1;
-                                        v[5] = si * d1;
-                                        v[6] = sr * d2;
-                                        v[7] = si * d2;
-                                    }
                                     feed(sl - c0, v);
                                     ++sl;
                                     Bn = sl < c1 ? uni(hx.x) + m + 1 : kNoPlane;
-                                    jn = uni(hx.y);
+                                    jn = head_line(uni(hx.y));
                                 }
                                 ++p;
                             }
@@ -866,9 +837,9 @@ __global__ __launch_bounds__(interp_max_threads(sizeof(R), M2, GRAD)) void k_int
                         }
                         // pad the last octet with zero partials
                         for (int t = c1 - c0; t & 7; ++t) {
-                            R v[2 * NO];
+                            R v[2];
 #pragma unroll
-                            for (int i = 0; i < 2 * NO; ++i) v[i] = R(0);
+                            for (int i = 0; i < 2; ++i) v[i] = R(0);
                             feed(t, v);
                         }
                     }
@@ -876,15 +847,15 @@ __global__ __launch_bounds__(interp_max_threads(sizeof(R), M2, GRAD)) void k_int
                     const int own = (lane & 7) * 8 + (((j8 & 1) << 2) | (j8 & 2) | (j8 >> 2));
                     if (own < c1 - c0) {
 #pragma unroll
-                        for (int i = 0; i < 2 * NO; ++i) oacc[(c0 + own) * 2 * NO + i] = ores[i];
+                        for (int i = 0; i < 2; ++i) oacc[(c0 + own) * 2 + i] = ores[i];
                     }
                 }
               }
             }
             __syncthreads();
-            for (int e = tid; e < cnt * 2 * NO; e += nthr) {
+            for (int e = tid; e < cnt * 2; e += nthr) {
                 R v = oacc[e];
-                if (v != R(0)) atomicAdd(&outs[(size_t)slot_p[e / (2 * NO)] * (2 * NO) + e % (2 * NO)], v);
+                if (v != R(0)) atomicAdd(&outs[(size_t)slot_p[e / (2)] * (2) + e % (2)], v);
             }
             __syncthreads();
             if (more) {
@@ -948,15 +919,15 @@ static hipError_t spread_m(const Xform *dxf, const SItem *items, int nitems, int
     return hipGetLastError();
 }
 
-template <typename R, int M2, bool GRAD>
+template <typename R, int M2>
 static hipError_t interp_m(const Xform *dxf, const SItem *items, int nitems, int *queue, Tiling t,
                            const unsigned char *rec, size_t rec_bytes, const int *cs, R *outs, hipStream_t s)
 {
-    LdsLayout LL = lds_fit(t.T, t.Zs, M2, sizeof(R), GRAD ? 2 : 1, false);
+    LdsLayout LL = lds_fit(t.T, t.Zs, M2, sizeof(R), 1, false);
     if (!LL.cap) return hipErrorInvalidValue;
-    int threads = std::min(t.threads, interp_max_threads(sizeof(R), M2, GRAD));
-    two_per_cu(LL, t, M2, sizeof(R), GRAD ? 2 : 1, false, threads);
-    auto kern = k_interp<R, M2, GRAD>;
+    int threads = std::min(t.threads, interp_max_threads(sizeof(R), M2));
+    two_per_cu(LL, t, M2, sizeof(R), 1, false, threads);
+    auto kern = k_interp<R, M2>;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)LL.total);
     if (e != hipSuccess) return e;
