@@ -3,6 +3,7 @@
 // kernels themselves are in sweep.h.
 #include "lines.h"
 #include "ring.h"
+#include "slab.h"
 
 namespace hpnfft {
 
@@ -28,10 +29,10 @@ hipError_t launch_spread(int m, const Xform *dxf, const SItem *items, int nitems
         HPNFFT_SPREAD_CASE(2)
         HPNFFT_SPREAD_CASE(3)
         HPNFFT_SPREAD_CASE(4)
-        HPNFFT_SPREAD_CASE(5)
-        HPNFFT_SPREAD_CASE(6)
-        HPNFFT_SPREAD_CASE(7)
-        HPNFFT_SPREAD_CASE(8)
+    case 5: return spread_slab<R, 10>(dxf, items, nitems, queue, t, rec, rec_bytes, fs, cell_start, s);
+    case 6: return spread_slab<R, 12>(dxf, items, nitems, queue, t, rec, rec_bytes, fs, cell_start, s);
+    case 7: return spread_slab<R, 14>(dxf, items, nitems, queue, t, rec, rec_bytes, fs, cell_start, s);
+    case 8: return spread_slab<R, 16>(dxf, items, nitems, queue, t, rec, rec_bytes, fs, cell_start, s);
     default: return launch_spread_wide<R>(m, dxf, items, nitems, queue, t, rec, rec_bytes, fs, cell_start, s);
     }
 #undef HPNFFT_SPREAD_CASE
