@@ -238,12 +238,13 @@ template <typename R>
 hipError_t launch_interp(int m, const Xform *dxf, const SItem *items, int nitems, int *queue,
                          Tiling t, const unsigned char *rec, size_t rec_bytes, const int *cell_start,
                          R *outs, hipStream_t s);
-// Interpolation by groups of single lines (lines.h), one transform per
-// launch: windows of 2m = 16 cells on grids whose n0 is a multiple of 2m.  xf: the transform's device descriptor; n: its grid edges; T: the
-// tile edge of the counting sort; outs: cleared, receives sums.
+// Interpolation by batches of points on a line (lines.h), one transform per
+// launch: windows of 2m = 10 .. 16 cells.  xf: the transform's device
+// descriptor; n: its grid edges; T: the tile edge of the counting sort.  outs
+// need not be cleared.
 template <typename R>
-hipError_t launch_interp_lines(int m, const Xform *xf, const int n[3], int *queue, int T, const unsigned char *rec,
-                               size_t rec_bytes, const int *cs, R *outs, hipStream_t s);
+hipError_t launch_interp_lines(int m, bool grad, const Xform *xf, const int n[3], int *queue, int T,
+                               const unsigned char *rec, size_t rec_bytes, const int *cs, R *outs, hipStream_t s);
 // odd: some grid edge has a factor 5 or 7
 template <typename R>
 hipError_t launch_fft(int pass, const Xform *dxf, const FItem *items, int nitems, int max_n, bool odd,

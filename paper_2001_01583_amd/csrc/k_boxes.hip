@@ -130,18 +130,6 @@ __device__ inline long long box_point(int k, int nruns, const int *run_p0, const
     return (long long)uni(run_p0[r]) + (k - uni(run_soff[r]));
 }
 
-// Value of v in lane l (l wave-uniform), as a lane read: the dim-0 weights of
-// a point sit one per lane, so the tap loop reads them without a memory
-// access.
-template <typename R> __device__ inline R lane_value(R v, int l)
-{
-    unsigned w[Words<R>::n];
-    Words<R>::split(v, w);
-#pragma unroll
-    for (int i = 0; i < Words<R>::n; ++i) w[i] = (unsigned)__builtin_amdgcn_readlane((int)w[i], l);
-    return Words<R>::join(w);
-}
-
 // ---------------------------------------------------------------------------
 template <typename R>
 __global__ __launch_bounds__(kBoxThreads) void k_spread_box(const Xform *__restrict__ xfs,

@@ -63,17 +63,27 @@ hipError_t launch_interp(int m, const Xform *dxf, const SItem *items, int nitems
 }
 
 template <typename R>
-hipError_t launch_interp_lines(int m, const Xform *xf, const int n[3], int *queue, int T, const unsigned char *rec,
-                               size_t rec_bytes, const int *cs, R *outs, hipStream_t s)
+hipError_t launch_interp_lines(int m, bool grad, const Xform *xf, const int n[3], int *queue, int T,
+                               const unsigned char *rec, size_t rec_bytes, const int *cs, R *outs, hipStream_t s)
 {
-    if (m != 8) return hipErrorInvalidValue;
-    return interp_lines_m<R, 16>(xf, n, queue, T, rec, rec_bytes, cs, outs, s);
+    switch (m) {
+#define HPNFFT_LINES_CASE(MM)                                                                       \
+    case MM:                                                                                        \
+        return grad ? interp_lines_m<R, 2 * MM, true>(xf, n, queue, T, rec, rec_bytes, cs, outs, s)  \
+                    : interp_lines_m<R, 2 * MM, false>(xf, n, queue, T, rec, rec_bytes, cs, outs, s);
+        HPNFFT_LINES_CASE(5)
+        HPNFFT_LINES_CASE(6)
+        HPNFFT_LINES_CASE(7)
+        HPNFFT_LINES_CASE(8)
+#undef HPNFFT_LINES_CASE
+    default: return hipErrorInvalidValue;
+    }
 }
 
-template hipError_t launch_interp_lines<double>(int, const Xform *, const int *, int *, int, const unsigned char *,
-                                                size_t, const int *, double *, hipStream_t);
-template hipError_t launch_interp_lines<float>(int, const Xform *, const int *, int *, int, const unsigned char *,
-                                               size_t, const int *, float *, hipStream_t);
+template hipError_t launch_interp_lines<double>(int, bool, const Xform *, const int *, int *, int,
+                                                const unsigned char *, size_t, const int *, double *, hipStream_t);
+template hipError_t launch_interp_lines<float>(int, bool, const Xform *, const int *, int *, int,
+                                               const unsigned char *, size_t, const int *, float *, hipStream_t);
 template hipError_t launch_spread<double>(int, const Xform *, const SItem *, int, int *, Tiling,
                                           const unsigned char *, size_t, const double *, const int *, hipStream_t);
 template hipError_t launch_spread<float>(int, const Xform *, const SItem *, int, int *, Tiling,

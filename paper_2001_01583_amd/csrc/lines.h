@@ -1,298 +1,316 @@
-// Interpolation by groups of single z-lines (the Interpolating step of
-// Algorithm 5, Section 3).  Written for windows of 2m = 10 .. 16 cells; the
-// plan selects it for 2m = 16, where it beats the staged sweep.
+// Interpolation by batches of points on a z-line, for windows of 2m = 10 ..
+// 16 cells on line-method plans (the Interpolating step of Algorithm 5,
+// Section 3), with or without the gradient.
 //
-// A work item is a group of neighbouring z-lines (2 x 2, or a row of three
-// for the widest float64 windows) and a slab of Zi planes along dim 0 (a
-// multiple of 2m).  Each point is evaluated once, by
-// the slab that holds its first tap plane.  A line's (2m)^2 tap rows are
-// spread over NRG wavefronts of 64 lanes (lane <-> one (dy, dx) row), and
-// each wavefront owns one (line, row group) for the whole slab: its register
-// window of 2m complex values along dim 0 carries from plane to plane.  The
-// planes reach the window through an LDS ring that holds one phase of 2m
-// planes of the group's footprint ((2m + 1)^2 or 2m (2m + 2) cells): per phase all threads
-// store the phase's planes (read from the grid into registers while the
-// previous phase was swept), and after a barrier each wavefront takes one
-// step per plane q: plane q enters slot q mod 2m, then the points whose
-// window starts at q - 2m + 1 are evaluated.  The per-lane partials of
-// consecutive points go through the halving steps of wave_reduce.h, and
-// every 64 points each lane adds one point's row-group sum to the output
-// (NRG adds per point, so the output is cleared first).
+// A work item is a group of 4 x 4 neighbouring z-lines and a range of their
+// planes; the workgroup goes through it in phases of DZ planes, with the
+// footprint of the points whose cells lie in a phase (DZ + 2m - 1 planes of
+// (2m + 3)^2 cells) in an LDS ring.  Every point is evaluated once, in full,
+// by one wavefront, and stored once.
 //
-// Against the staged sweep this drops the z-halo (a point is evaluated once
-// instead of by both slabs its window reaches), the record staging and its
-// barriers, and the LDS tile of the slab: the per-point values the lanes
-// share come through scalar loads straight from the records.
+// The points of a line share their tap rows and differ in their planes only,
+// so a wavefront takes up to G consecutive points of a line together: it
+// reads each plane of their windows' union from LDS once (lane <-> (dim 1,
+// dim 2) tap rows, 64 at a time) and adds it to every point whose window
+// holds it, with the dim-0 weight from a lane read.  At 0.5 points per cell
+// four points of a line span 22 planes instead of 64.  The 2 G (with the
+// gradient 8 per point) sums then go through the halving steps of
+// wave_reduce.h together.
+//
+// Bound by the float64 vector unit (290 instructions per point at 2m = 16, 128
+// of them the multiply-adds) at three or four wavefronts per SIMD.  Measured
+// (float64) against what it replaced: N = 64^3, M = 2^20, 2m = 16 1.29 -> 0.99
+// ms (groups of lines with register windows), 2m = 12 1.49 -> 0.65 ms (staged
+// sweep); 150,001 points on 96 x 72 x 120, 2m = 12 0.40 -> 0.21 ms; float32, 2m =
+// 16 0.89 -> 0.64 ms; with gradients, 200,000 points on 96^3, 2m = 16 0.47 ms
+// against 0.56 for the gather.  Tried and slower: the next batch's records
+// loaded while one is evaluated (2m = 16 1.31 ms), one plane per round (2m =
+// 12 0.76 ms), three points per batch (as fast).
 #pragma once
 
 #include "sweep.h"
 
 namespace hpnfft {
 
-constexpr int kLinesZ = 64;  // slab depth target (planes), rounded down to a multiple of 2m
+constexpr int kLineT = 4;  // lines per group along dims 1 and 2
 
-template <int M2> constexpr int lines_nrg() { return (M2 * M2 + 63) / 64; }
-// Lines per group along dims 1 (GY) and 2 (GX).  2 x 2 in general; a row of
-// three lines for float64 windows of 2m >= 14, whose 2m-slot float64 window
-// takes 4 * 2m registers per lane: twelve wavefronts per workgroup leave 168
-// registers per lane, enough to keep the next point's and the next phase's
-// loads in flight.
-template <typename R, int M2> struct LineGroup {
-    static constexpr bool wide = sizeof(R) == 8 && M2 >= 14;
-    static constexpr int GY = wide ? 1 : 2, GX = wide ? 3 : 2;
-    static constexpr int PY = M2 + GY - 1, PX = M2 + GX - 1;  // footprint rows and columns
-    static constexpr int threads = GY * GX * lines_nrg<M2>() * 64;
-    static constexpr size_t lds = (size_t)M2 * PY * PX * 2 * sizeof(R);
+template <typename R, int M2, bool GRAD> struct LineBatch {
+    static constexpr int P = kLineT + M2 - 1, PLANE = P * P;  // footprint cells of a plane
+    static constexpr int G = GRAD ? 2 : 4;                    // points per batch
+    static constexpr int RPG = 64 / M2;                       // tap rows per row group
+    static constexpr int NR = (M2 + RPG - 1) / RPG;           // row groups
+    // planes of new points per phase: a ring in half of the LDS (two
+    // workgroups per compute unit) where that leaves at least 10, else in all
+    // of it
+    static constexpr int cells(size_t bytes) { return (int)(bytes / (PLANE * 2 * sizeof(R))); }
+    static constexpr int half = cells(79 * 1024) - (M2 - 1), full = cells(158 * 1024) - (M2 - 1);
+    static constexpr bool two = half >= 10 && !(sizeof(R) == 8 && M2 >= 12);
+    static constexpr int DZ = two ? (half < 16 ? half : 16) : (full < 16 ? full : 16);
+    static constexpr int NP = DZ + M2 - 1;  // ring planes
+    // wavefronts per SIMD: the accumulators, two planes' rows and the next
+    // phase's cells take more than 128 registers for wide float64 windows
+    static constexpr int waves = sizeof(R) == 8 && M2 >= 14 ? 3 : 4;
+    static constexpr int threads = (two ? 128 : 256) * waves;
+    static constexpr size_t lds = (size_t)NP * PLANE * 2 * sizeof(R);
 };
-__host__ __device__ constexpr int lines_slab(int M2) { return (kLinesZ / M2) * M2; }
 
-template <typename R, int M2>
-__global__ __launch_bounds__((LineGroup<R, M2>::threads)) void k_interp_lines(
-    const Xform *__restrict__ xf, int nitems, int *__restrict__ queue, int T, const unsigned char *__restrict__ rec,
-    int rbytes, const int *__restrict__ cell_start, R *__restrict__ outs)
+template <typename R, int M2, bool GRAD>
+__global__ __launch_bounds__((LineBatch<R, M2, GRAD>::threads), (LineBatch<R, M2, GRAD>::waves)) void k_interp_lines(
+    const Xform *__restrict__ xf, int nitems, int *__restrict__ queue, int T, int Zi,
+    const unsigned char *__restrict__ rec, int rbytes, const int *__restrict__ cell_start, R *__restrict__ outs)
 {
-    constexpr int m = M2 / 2;
-    constexpr int NRG = lines_nrg<M2>();
-    using G = LineGroup<R, M2>;
-    constexpr int GY = G::GY, GX = G::GX, PX = G::PX;
-    constexpr int PLANE = G::PY * PX;
-    constexpr int NTH = G::threads;
-    constexpr int NPF = (M2 * PLANE + NTH - 1) / NTH;  // ring cells per thread and phase
-    constexpr int Zi = lines_slab(M2);
+    using LB = LineBatch<R, M2, GRAD>;
+    constexpr int m = M2 / 2, G = LB::G, RPG = LB::RPG, NR = LB::NR, P = LB::P, PLANE = LB::PLANE, DZ = LB::DZ, NP = LB::NP;
+    constexpr int NTH = LB::threads, NW = NTH / 64, NL = kLineT * kLineT;
+    constexpr int NPF = (DZ * PLANE + NTH - 1) / NTH;
+    constexpr int OFF_PZ = (int)rec_off_pz(M2, sizeof(R));
+    constexpr int OFF_D = (int)rec_prefix(M2, sizeof(R)) / (int)sizeof(R);
+    typedef R V2 __attribute__((ext_vector_type(2)));
     extern __shared__ uint4 smem16[];
-    R *ring = reinterpret_cast<R *>(smem16);  // [slot][footprint row][column] complex
+    V2 *ring = reinterpret_cast<V2 *>(smem16);  // [plane mod NP][row][column]
     __shared__ int s_item;
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
-    const int line = wave / NRG, rg = wave - line * NRG;
-    const int ly = line / GX, lx = line % GX;
-    const int row = rg * 64 + lane;
-    const bool active = row < M2 * M2;
-    const int dy = active ? row / M2 : 0, dx = active ? row % M2 : 0;
-    const int cell = (ly + dy) * PX + lx + dx;  // lane's cell in a ring plane
-    // batch position whose sum this lane receives (see halve8_sum)
-    const int j8 = lane >> 3;
-    const int own = (lane & 7) * 8 + (((j8 & 1) << 2) | (j8 & 2) | (j8 >> 2));
-
-    const int n0 = xf->n[0], n1 = xf->n[1], n2 = xf->n[2];
-    const int ntx = xf->ntx;
-    const int ngx = (n2 + GX - 1) / GX, ngy = (n1 + GY - 1) / GY;
+    const int n0 = xf->n[0], n1 = xf->n[1], n2 = xf->n[2], ntx = xf->ntx;
+    const int ngx = (n2 + kLineT - 1) / kLineT, ngy = (n1 + kLineT - 1) / kLineT;
     const long long poff = xf->poff;
-    const int Mx = (int)xf->M;
     const unsigned char *recb = rec + (size_t)poff * rbytes;
-    const gptr<const R> grid = as_global(reinterpret_cast<const R *>(xf->grid));
+    const gptr<const V2> grid = as_global(reinterpret_cast<const V2 *>(xf->grid));
     const size_t pstride = (size_t)n1 * n2;
-
-    struct PointData {
-        R wz[M2];
-        R wy, wx;
-    };
-    auto fetch = [&](const unsigned char *rp, PointData &d) __attribute__((always_inline)) {
-        const cptr<R> pc = as_const(reinterpret_cast<const R *>(rp));
-#pragma unroll
-        for (int s = 0; s < M2; ++s) d.wz[s] = pc[s];
-        const R *ps = reinterpret_cast<const R *>(rp);
-        d.wy = ps[M2 + dy];
-        d.wx = ps[2 * M2 + dx];
-    };
+    // the lane's column t2 and tap rows t1 + RPG k; rows past the window and
+    // the lanes left over read some cell of the footprint with weight 0
+    const int t1 = lane / M2, t2 = lane - t1 * M2;
+    const bool used = lane < RPG * M2;
+    auto row_on = [&](int k) __attribute__((always_inline)) { return used && t1 + RPG * k < M2; };
 
     for (int it = next_item(queue, &s_item); it < nitems; it = next_item(queue, &s_item)) {
         const int gx = it % ngx, r0 = it / ngx;
-        const int gy = r0 % ngy, sl = r0 / ngy;
-        const int z0 = sl * Zi, zs = min(Zi, n0 - z0);
-        const int Y0 = gy * GY, X0 = gx * GX;
-        const int y = Y0 + ly, x = X0 + lx;
-        const bool mine = y < n1 && x < n2;
-        // the line's points by plane: key (tile, row and column in the
-        // tile, plane) of the counting sort, whose tiles have edge T
-        const int q1 = y / T, q2 = x / T;
-        const int key_line = ((q1 * ntx + q2) * T + (y - q1 * T)) * T + (x - q2 * T);
-        const int *cs = cell_start + xf->key_off + (long long)key_line * n0;
-        auto plane_c = [&](int b) __attribute__((always_inline)) {
-            int c = b + (m - 1) + z0;  // within [m - 1, 2 n0)
-            c -= c >= n0 ? n0 : 0;
-            return c;
+        const int X0 = gx * kLineT, Y0 = (r0 % ngy) * kLineT;
+        const int za = (r0 / ngy) * Zi, ze = min(za + Zi, n0);  // cells of the item's points
+        const int qb = za - m + 1;                              // its first window plane
+        // sorted points of line `lane` (lanes 0 .. 15) in a phase's planes
+        const int ly = (lane & 15) / kLineT, lx = lane & (kLineT - 1);
+        const bool has = lane < NL && Y0 + ly < n1 && X0 + lx < n2;
+        const int yl = min(Y0 + ly, n1 - 1), xl = min(X0 + lx, n2 - 1);
+        const int q1 = yl / T, q2 = xl / T;
+        const int *cs = cell_start + xf->key_off +
+                        (long long)(((q1 * ntx + q2) * T + (yl - q1 * T)) * T + (xl - q2 * T)) * n0;
+        int a0 = 0, a1 = 0;  // this phase's range, the next one's loaded ahead
+        auto range = [&](int zc) __attribute__((always_inline)) {
+            const bool ok = has && zc < ze;
+            a0 = ok ? cs[zc] : 0;
+            a1 = ok ? cs[min(zc + DZ, ze)] : 0;
         };
-
-        PointData cur{};
-        int cidx = -1;
-        // partial sums of the last point evaluated, not yet reduced
-        R pvr = 0, pvi = 0;
-        int pend = -1;  // its sorted index (-1: none)
-        const unsigned char *rcur = recb;
-        R gr[M2], gi[M2];
-
-        // halving-step state: partials of the open pair, quad and octet
-        R s0r = 0, s0i = 0, s1r = 0, s1i = 0, s2r = 0, s2i = 0, orr = 0, ori = 0;
-        int t = 0;    // position of the next point in the batch of 64
-        int bsp = 0;  // lane t: sorted index of batch point t
-        auto feed = [&](R vr, R vi) __attribute__((always_inline)) {
-            if (!(t & 1)) {
-                s0r = vr;
-                s0i = vi;
-            } else {
-                vr = halve32(s0r, vr);
-                vi = halve32(s0i, vi);
-                if (!(t & 2)) {
-                    s1r = vr;
-                    s1i = vi;
-                } else {
-                    vr = halve16(s1r, vr);
-                    vi = halve16(s1i, vi);
-                    if (!(t & 4)) {
-                        s2r = vr;
-                        s2i = vi;
-                    } else {
-                        const R tr = halve8_sum(s2r, vr), ti = halve8_sum(s2i, vi);
-                        if ((lane & 7) == (t >> 3)) {
-                            orr += tr;
-                            ori += ti;
+        // footprint cells of ring planes j0 .. j0 + nz - 1 (nz <= DZ), through registers
+        V2 pf[NPF];
+        auto planes_fetch = [&](int j0, int nz) __attribute__((always_inline)) {
+            int t = tid;
+            asm volatile("" : "+v"(t));  // (indices are cheaper computed per phase than kept in registers)
+#pragma unroll
+            for (int u = 0; u < NPF; ++u) {
+                const int e = t + u * NTH;
+                const int zz = e / PLANE, c = e - zz * PLANE;
+                pf[u] = V2{0, 0};
+                if (zz < nz) {
+                    const int fy = c / P, fx = c - fy * P;
+                    int gz = qb + j0 + zz, gy = Y0 + fy - (m - 1), gx2 = X0 + fx - (m - 1);
+                    gz += gz < 0 ? n0 : 0;
+                    gz -= gz >= n0 ? n0 : 0;
+                    gz -= gz >= n0 ? n0 : 0;
+                    gy += gy < 0 ? n1 : 0;
+                    gy -= gy >= n1 ? n1 : 0;
+                    gy -= gy >= n1 ? n1 : 0;
+                    gx2 += gx2 < 0 ? n2 : 0;
+                    gx2 -= gx2 >= n2 ? n2 : 0;
+                    gx2 -= gx2 >= n2 ? n2 : 0;
+                    pf[u] = grid[(size_t)gz * pstride + (size_t)gy * n2 + gx2];
+                }
+            }
+        };
+        auto planes_store = [&](int j0, int nz) __attribute__((always_inline)) {
+            int t = tid;
+            asm volatile("" : "+v"(t));
+#pragma unroll
+            for (int u = 0; u < NPF; ++u) {
+                const int e = t + u * NTH;
+                const int zz = e / PLANE, c = e - zz * PLANE;
+                if (zz < nz) ring[((j0 + zz) % NP) * PLANE + c] = pf[u];
+            }
+        };
+        // the planes before the first phase's own
+        for (int j = 0; j < M2 - 1; j += DZ) {
+            const int nz = min(DZ, M2 - 1 - j);
+            planes_fetch(j, nz);
+            planes_store(j, nz);
+        }
+        range(za);
+        planes_fetch(M2 - 1, min(DZ, ze - za));
+        for (int zc = za, jp = 0; zc < ze; zc += DZ, jp += DZ) {  // jp: first window plane of the phase's points
+            planes_store(jp + M2 - 1, min(DZ, ze - zc));
+            // the phase's batches, numbered line by line
+            const int first = a0, cnt = a1 - a0;
+            const int nb = (cnt + G - 1) / G;
+            int incl = nb;
+#pragma unroll
+            for (int o = 1; o < NL; o <<= 1) {
+                const int y = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += y;
+            }
+            const int total = __builtin_amdgcn_readlane(incl, NL - 1);
+            __syncthreads();
+            range(zc + DZ);
+            if (zc + DZ < ze) planes_fetch(jp + DZ + M2 - 1, min(DZ, ze - zc - DZ));
+            for (int t = wave; t < total; t += NW) {
+                const int ln = __popcll(__ballot(lane < NL && incl <= t));
+                const int b = t - (__builtin_amdgcn_readlane(incl, ln) - __builtin_amdgcn_readlane(nb, ln));
+                const int p0 = __builtin_amdgcn_readlane(first, ln) + b * G;
+                const int np = min(G, __builtin_amdgcn_readlane(cnt, ln) - b * G);
+                const unsigned char *rp = recb + (size_t)p0 * rbytes;
+                // first window planes (ring numbering) and, one per lane, the dim-0 weights
+                int j1[G];
+                R wz[G], dz[GRAD ? G : 1];
+#pragma unroll
+                for (int p = 0; p < G; ++p) {
+                    const unsigned char *q = rp + (size_t)min(p, np - 1) * rbytes;
+                    const R *ps = reinterpret_cast<const R *>(q);
+                    wz[p] = ps[min(lane, M2 - 1)];
+                    if constexpr (GRAD) dz[p] = ps[OFF_D + min(lane, M2 - 1)];
+                    const int c0 = as_const(reinterpret_cast<const int *>(q + OFF_PZ))[0];
+                    j1[p] = p < np ? c0 - za : 1 << 28;
+                }
+                const int jlast = as_const(reinterpret_cast<const int *>(rp + (size_t)(np - 1) * rbytes + OFF_PZ))[0] - za;
+                const int base = (ln / kLineT) * P + (ln & (kLineT - 1));
+                // the lane's cells of a plane: cell + k RPG P (rows past the
+                // footprint's last are read from its last row)
+                const int cell = base + (used ? t1 * P + t2 : 0);
+                const int last = base + min(t1 + RPG * (NR - 1), M2 - 1) * P + (used ? t2 : 0);
+                R sr[G][NR], si[G][NR], dr[GRAD ? G : 1][GRAD ? NR : 1], di[GRAD ? G : 1][GRAD ? NR : 1];
+#pragma unroll
+                for (int p = 0; p < G; ++p)
+#pragma unroll
+                    for (int k = 0; k < NR; ++k) {
+                        sr[p][k] = si[p][k] = R(0);
+                        if constexpr (GRAD) dr[p][k] = di[p][k] = R(0);
+                    }
+                int j = j1[0];
+                int ring_p = j % NP;             // plane j's place in the ring
+                int slot = (j + qb + M2) % M2;   // its weights' slot (qb > -m)
+                auto read = [&](V2 (&c)[NR]) __attribute__((always_inline)) {
+                    const V2 *q = ring + ring_p * PLANE;
+#pragma unroll
+                    for (int k = 0; k < NR; ++k) c[k] = k + 1 < NR || M2 % RPG == 0 ? q[cell + k * RPG * P] : q[last];
+                    ring_p = ring_p + 1 == NP ? 0 : ring_p + 1;
+                };
+                auto step = [&](const V2 (&c)[NR]) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int p = 0; p < G; ++p) {
+                        if ((unsigned)(j - j1[p]) >= (unsigned)M2) continue;
+                        const R w = lane_value(wz[p], slot);
+#pragma unroll
+                        for (int k = 0; k < NR; ++k) {
+                            sr[p][k] = fma(w, c[k][0], sr[p][k]);
+                            si[p][k] = fma(w, c[k][1], si[p][k]);
+                        }
+                        if constexpr (GRAD) {
+                            const R dw = lane_value(dz[p], slot);
+#pragma unroll
+                            for (int k = 0; k < NR; ++k) {
+                                dr[p][k] = fma(dw, c[k][0], dr[p][k]);
+                                di[p][k] = fma(dw, c[k][1], di[p][k]);
+                            }
                         }
                     }
+                    slot = slot + 1 == M2 ? 0 : slot + 1;
+                    ++j;
+                };
+                // two planes per round, so that the next plane's reads go to
+                // the other one's registers (a plane past the last one only
+                // meets windows that have ended)
+                V2 ca[NR], cb[NR];
+                read(ca);
+                while (j < jlast + M2) {
+                    read(cb);
+                    step(ca);
+                    read(ca);
+                    step(cb);
                 }
-            }
-            ++t;
-        };
-        // every lane that holds the row-group sum of a point adds it to the
-        // point's output (positions padded with zeros hold no point)
-        auto drain = [&]() __attribute__((always_inline)) {
-            const int count = t;
-            while (t & 7) feed(R(0), R(0));
-            const int sp_own = __builtin_amdgcn_ds_bpermute(own << 2, bsp);
-            if (own < count) {
-                __hip_atomic_fetch_add(&outs[(size_t)sp_own * 2], orr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_fetch_add(&outs[(size_t)sp_own * 2 + 1], ori, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-            }
-            orr = ori = R(0);
-            t = 0;
-        };
-        auto reduce_pending = [&]() __attribute__((always_inline)) {
-            bsp = lane == t ? (int)(poff + pend) : bsp;
-            feed(pvr, pvi);
-            if (t == 64) drain();
-            pend = -1;
-        };
-
-        // sorted point range of base plane b (b < zs <= 64) in lane b: read
-        // with lane reads at the steps, so that the steps wait on no load
-        int rlo = 0, rhi = 0;
-        if (mine && lane < zs) {
-            const int c = plane_c(lane);
-            rlo = cs[c];
-            rhi = cs[c + 1];
-        }
-        const int zr = zs + M2 - 1;  // window planes of the slab's points
-        // step q: plane q (slot k = q mod 2m) enters from the ring (planes
-        // past the windows hold zeros); then the points whose window starts
-        // at q - 2m + 1
-        auto step = [&](const int k, const int q) __attribute__((always_inline)) {
-            {
-                const int o = (k * PLANE + cell) * 2;
-                gr[k] = ring[o];
-                gi[k] = ring[o + 1];
-            }
-            const int b = q - (M2 - 1);
-            if (b >= 0 && b < zs) {
-                const int pa = __builtin_amdgcn_readlane(rlo, b), pb = __builtin_amdgcn_readlane(rhi, b);
-                for (int sp = pa; sp < pb; ++sp) {
-                    // the previous point's reduction runs first, so that the
-                    // loads of this point (issued after the previous point's
-                    // sums, into the same registers: two sets of the shared
-                    // weights do not fit the scalar registers of the widest
-                    // windows) are in flight meanwhile
-                    if (pend >= 0) reduce_pending();
-                    if (sp != cidx) {
-                        rcur = recb + (size_t)sp * rbytes;
-                        fetch(rcur, cur);
+                const int j8 = lane >> 3, vq = ((j8 & 1) << 2) | (j8 & 2) | (j8 >> 2);  // value of the lane's group
+                if constexpr (GRAD) {
+#pragma unroll
+                    for (int p = 0; p < G; ++p) {
+                        if (p >= np) break;
+                        const R *ps = reinterpret_cast<const R *>(rp + (size_t)p * rbytes);
+                        R v[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) v[q] = R(0);
+                        const R w2 = ps[2 * M2 + t2], dw2 = ps[OFF_D + 2 * M2 + t2];
+#pragma unroll
+                        for (int k = 0; k < NR; ++k) {
+                            const int r = min(t1 + RPG * k, M2 - 1);
+                            const R w1 = row_on(k) ? ps[M2 + r] : R(0);
+                            const R d1 = (row_on(k) ? ps[OFF_D + M2 + r] : R(0)) * w2, d2 = w1 * dw2;
+                            const R w12 = w1 * w2;
+                            v[0] = fma(sr[p][k], w12, v[0]);
+                            v[1] = fma(si[p][k], w12, v[1]);
+                            v[2] = fma(dr[p][k], w12, v[2]);
+                            v[3] = fma(di[p][k], w12, v[3]);
+                            v[4] = fma(sr[p][k], d1, v[4]);
+                            v[5] = fma(si[p][k], d1, v[5]);
+                            v[6] = fma(sr[p][k], d2, v[6]);
+                            v[7] = fma(si[p][k], d2, v[7]);
+                        }
+                        const R x0 = halve32(v[0], v[1]), x1 = halve32(v[2], v[3]);
+                        const R x2 = halve32(v[4], v[5]), x3 = halve32(v[6], v[7]);
+                        const R r = halve8_sum(halve16(x0, x1), halve16(x2, x3));
+                        if ((lane & 7) == 0) outs[(size_t)(poff + p0 + p) * 8 + vq] = r;
                     }
-                    R ar = 0, ai = 0;
+                } else {
+                    R v[2 * G];
 #pragma unroll
-                    for (int s = 0; s < M2; ++s) {
-                        ar = fma(gr[s], cur.wz[s], ar);
-                        ai = fma(gi[s], cur.wz[s], ai);
+                    for (int p = 0; p < G; ++p) {
+                        const R *ps = reinterpret_cast<const R *>(rp + (size_t)min(p, np - 1) * rbytes);
+                        v[2 * p] = v[2 * p + 1] = R(0);
+                        const R w2 = ps[2 * M2 + t2];
+#pragma unroll
+                        for (int k = 0; k < NR; ++k) {
+                            const R w12 = (row_on(k) ? ps[M2 + min(t1 + RPG * k, M2 - 1)] : R(0)) * w2;
+                            v[2 * p] = fma(sr[p][k], w12, v[2 * p]);
+                            v[2 * p + 1] = fma(si[p][k], w12, v[2 * p + 1]);
+                        }
                     }
-                    const R w12 = active ? cur.wy * cur.wx : R(0);
-                    pvr = ar * w12;
-                    pvi = ai * w12;
-                    pend = sp;
-                    const bool adv = sp + 1 < Mx;
-                    rcur = adv ? rcur + rbytes : rcur;
-                    fetch(rcur, cur);
-                    cidx = adv ? sp + 1 : sp;
+                    // group j of 8 lanes ends with value bitrev3(j) = 2 p + component
+                    const R x0 = halve32(v[0], v[1]), x1 = halve32(v[2], v[3]);
+                    const R x2 = halve32(v[4], v[5]), x3 = halve32(v[6], v[7]);
+                    const R r = halve8_sum(halve16(x0, x1), halve16(x2, x3));
+                    if ((lane & 7) == 0 && (vq >> 1) < np) outs[(size_t)(poff + p0) * 2 + vq] = r;
                 }
             }
-        };
-
-        // ring cells of a phase, read from the grid one phase ahead
-        R pr[NPF], pim[NPF];
-        auto ring_fetch = [&](int ph) __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < NPF; ++u) {
-                const int e = tid + u * NTH;
-                const int zz = e / PLANE, c = e - zz * PLANE;
-                const int q = ph * M2 + zz;
-                pr[u] = pim[u] = R(0);
-                if (e < M2 * PLANE && q < zr) {
-                    const int fy = c / PX, fx = c - fy * PX;
-                    int gz = z0 + q;  // below 2 n0
-                    gz -= gz >= n0 ? n0 : 0;
-                    int gyy = Y0 + fy - (m - 1), gxx = X0 + fx - (m - 1);
-                    gyy += gyy < 0 ? n1 : 0;
-                    gyy -= gyy >= n1 ? n1 : 0;
-                    gyy -= gyy >= n1 ? n1 : 0;
-                    gxx += gxx < 0 ? n2 : 0;
-                    gxx -= gxx >= n2 ? n2 : 0;
-                    gxx -= gxx >= n2 ? n2 : 0;
-                    const size_t gidx = ((size_t)gz * pstride + (size_t)gyy * n2 + gxx) * 2;
-                    pr[u] = grid[gidx];
-                    pim[u] = grid[gidx + 1];
-                }
-            }
-        };
-
-        const int nph = (zr + M2 - 1) / M2;
-        ring_fetch(0);
-        for (int ph = 0; ph < nph; ++ph) {
-            if (ph > 0) __syncthreads();  // the previous phase's steps have read the ring
-#pragma unroll
-            for (int u = 0; u < NPF; ++u) {
-                const int e = tid + u * NTH;
-                if (e < M2 * PLANE) {
-                    ring[2 * e] = pr[u];
-                    ring[2 * e + 1] = pim[u];
-                }
-            }
-            __syncthreads();
-            if (ph + 1 < nph) ring_fetch(ph + 1);
-            if (mine) {
-#pragma unroll
-                for (int k = 0; k < M2; ++k) step(k, ph * M2 + k);
-            }
+            __syncthreads();  // the next phase's planes replace this one's first
         }
-        if (mine && pend >= 0) reduce_pending();
-        if (mine && t > 0) drain();
     }
     release_queue(queue);
 }
 
-// One launch per transform (the items of a transform are its line groups
-// times its slabs).  xf: the transform's device descriptor; n: its grid
-// edges on the host.
-template <typename R, int M2>
+// One launch per transform (its line groups times its plane ranges).  xf: the
+// transform's device descriptor; n: its grid edges on the host.
+template <typename R, int M2, bool GRAD>
 static hipError_t interp_lines_m(const Xform *xf, const int n[3], int *queue, int T, const unsigned char *rec,
                                  size_t rec_bytes, const int *cs, R *outs, hipStream_t s)
 {
-    const int nsl = (n[0] + lines_slab(M2) - 1) / lines_slab(M2);
-    using G = LineGroup<R, M2>;
-    const int nitems = nsl * ((n[1] + G::GY - 1) / G::GY) * ((n[2] + G::GX - 1) / G::GX);
-    constexpr size_t lds = G::lds;
-    auto kern = k_interp_lines<R, M2>;
-    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    using LB = LineBatch<R, M2, GRAD>;
+    auto kern = k_interp_lines<R, M2, GRAD>;
+    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LB::lds);
     if (e != hipSuccess) return e;
-    const int grid = std::min(cu_count(), nitems);
-    if (grid < 1) return hipSuccess;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(G::threads), lds, s, xf, nitems, queue, T, rec,
-                       (int)rec_bytes, cs, outs);
+    // plane ranges of whole phases, enough of them for a few items per
+    // workgroup (each range reads 2m - 1 planes more than it has)
+    const int per_cu = LB::two ? 2 : 1;
+    const int groups = ((n[1] + kLineT - 1) / kLineT) * ((n[2] + kLineT - 1) / kLineT);
+    const int phases = (n[0] + LB::DZ - 1) / LB::DZ;
+    const int ranges = std::max(1, std::min(phases, 4 * per_cu * cu_count() / groups));
+    const int Zi = (phases + ranges - 1) / ranges * LB::DZ;
+    const int nitems = groups * ((n[0] + Zi - 1) / Zi);
+    const int grid = std::min(cu_count() * per_cu, nitems);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(LB::threads), LB::lds, s, xf, nitems, queue, T, Zi, rec, (int)rec_bytes,
+                       cs, outs);
     return hipGetLastError();
 }
 

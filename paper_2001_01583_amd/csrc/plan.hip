@@ -424,13 +424,9 @@ bool use_ring(const hpnfft_plan_s *p, const Tiling &t)
     return true;
 }
 
-// Whether the forward's interpolation runs by groups of single lines
-// (lines.h): windows of 2m = 16 cells, every line-method transform with n0 a
-// multiple of 2m (HPNFFT_LINES=0 selects the staged sweep).  Measured at N =
-// 64^3, M = 2^20: float64 2.94 -> 1.34 ms, float32 1.58 -> 0.91 ms for 2m =
-// 16; for 2m = 10, 12 and 14 the staged sweep stays faster (float64 0.94,
-// 1.35, 2.26 ms against 1.24, 1.47, 2.33 ms): with fewer taps per point the
-// per-point and per-plane costs of the line groups dominate.
+// Whether the line-method transforms are interpolated by batches of points on
+// a line (lines.h): windows of 2m = 10 .. 16 cells (HPNFFT_LINES=0 selects
+// the staged sweep, and the gather for gradients).
 bool use_lines(const hpnfft_plan_s *p)
 {
     static int on = -1;
@@ -438,11 +434,7 @@ bool use_lines(const hpnfft_plan_s *p)
         const char *e = getenv("HPNFFT_LINES");
         on = (e && e[0] == '0') ? 0 : 1;
     }
-    const int M2 = p->M2();
-    if (!on || p->det() || M2 != 16) return false;
-    for (size_t b = 0; b < p->hx.size(); ++b)
-        if (!p->tbox[b] && p->hx[b].n[0] % M2) return false;
-    return true;
+    return on && !p->det() && p->M2() >= 10 && p->M2() <= 16;
 }
 
 bool tiling_fits(const hpnfft_plan_s *p, Tiling t)
@@ -1016,9 +1008,9 @@ template <typename R> int run_forward(hpnfft_plan_s *p, const void *fhat, void *
     hipStream_t s = p->stream;
     const Xform *dxf = p->at<Xform>(L.xf);
     const bool lines = p->any_lines && !p->det();
-    // the gather and the ring interpolation store every point's value once;
-    // the other line sweeps add partial sums into a cleared output
-    if (lines && !use_ring(p, p->til)) {
+    // every sweep stores each point's value once, but the staged one, which
+    // adds partial sums into a cleared output
+    if (lines && !use_lines(p) && !use_ring(p, p->til)) {
         PhaseTimer t(p, HPNFFT_PH_ZERO);
         HCHECK(launch_zero(p->ws + L.outs, (size_t)p->Mtot * 2 * sizeof(R), s));
     }
@@ -1031,7 +1023,7 @@ template <typename R> int run_forward(hpnfft_plan_s *p, const void *fhat, void *
         if (lines && use_lines(p)) {
             for (size_t b = 0; b < p->hx.size(); ++b)
                 if (!p->tbox[b])
-                    HCHECK(launch_interp_lines<R>(p->m, dxf + b, p->hx[b].n, p->at<int>(L.counters) + 1, p->til.T,
+                    HCHECK(launch_interp_lines<R>(p->m, false, dxf + b, p->hx[b].n, p->at<int>(L.counters) + 1, p->til.T,
                                                   p->at<unsigned char>(L.rec), L.rec_bytes,
                                                   p->at<int>(L.cell_start), p->at<R>(L.outs), s));
         } else if (lines) {
@@ -1059,8 +1051,16 @@ int run_backward(hpnfft_plan_s *p, const void *f, const void *gfhat, void *grad_
     if (rc) return rc;
     {
         PhaseTimer t(p, HPNFFT_PH_GRAD);
-        HCHECK(launch_interp_gather<R>(p->m, true, dxf, p->B, true, p->Mtot, p->at<unsigned char>(L.rec),
-                                       L.rec_bytes, p->at<R>(L.outs), s));
+        const bool lines = p->any_lines && use_lines(p);
+        HCHECK(launch_interp_gather<R>(p->m, true, dxf, p->B, !lines, lines ? p->Mbox : p->Mtot,
+                                       p->at<unsigned char>(L.rec), L.rec_bytes, p->at<R>(L.outs), s));
+        if (lines) {
+            for (size_t b = 0; b < p->hx.size(); ++b)
+                if (!p->tbox[b])
+                    HCHECK(launch_interp_lines<R>(p->m, true, dxf + b, p->hx[b].n, p->at<int>(L.counters) + 1,
+                                                  p->til.T, p->at<unsigned char>(L.rec), L.rec_bytes,
+                                                  p->at<int>(L.cell_start), p->at<R>(L.outs), s));
+        }
     }
     {
         PhaseTimer t(p, HPNFFT_PH_GRAD_FIN);

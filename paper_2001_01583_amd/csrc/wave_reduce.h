@@ -129,4 +129,16 @@ __device__ inline R halve8_sum(R a, R b)
     return sum8(t);
 }
 
+// Value of v in lane l (l wave-uniform), as a lane read: a point's dim-0
+// weights sit one per lane, and the loops over its planes read them without a
+// memory access.
+template <typename R> __device__ inline R lane_value(R v, int l)
+{
+    unsigned w[Words<R>::n];
+    Words<R>::split(v, w);
+#pragma unroll
+    for (int i = 0; i < Words<R>::n; ++i) w[i] = (unsigned)__builtin_amdgcn_readlane((int)w[i], l);
+    return Words<R>::join(w);
+}
+
 }  // namespace hpnfft
