@@ -264,9 +264,11 @@ hipError_t launch_spread_det(int m, const Xform *dxf, const SItem *items, int ni
                              hipStream_t s);
 
 // Interpolation by gathering (k_gather.hip): all points, or those of the
-// transforms that use boxes; total: their number.  outs need not be cleared.
+// transforms that use boxes or lines; total: their number; Zs: the line
+// method's slab depth.  outs need not be cleared.
+enum GatherSet { GATHER_ALL = 0, GATHER_BOXES, GATHER_LINES };
 template <typename R>
-hipError_t launch_interp_gather(int m, bool grad, const Xform *dxf, int B, bool all, long long total,
+hipError_t launch_interp_gather(int m, bool grad, const Xform *dxf, int B, int which, int Zs, long long total,
                                 const unsigned char *rec, size_t rec_bytes, R *outs, hipStream_t s);
 
 // Box method (k_boxes.hip): every workgroup owns one output box of the grid
@@ -275,6 +277,11 @@ template <typename R>
 hipError_t launch_spread_box(int m, const Xform *dxf, const SItem *items, int nitems, int *queue, int max_cells,
                              const unsigned char *rec, size_t rec_bytes, const R *fs, const int *cell_start,
                              hipStream_t s);
+
+// Values and gradients per output box (float32; outs cleared by the caller).
+template <typename R>
+hipError_t launch_grad_box(int m, const Xform *dxf, const SItem *items, int nitems, int *queue, int max_cells,
+                           const unsigned char *rec, size_t rec_bytes, const int *cell_start, R *outs, hipStream_t s);
 
 // Fixed-order sum of n float64 partials into *out (one workgroup).
 hipError_t launch_sum_partials(const double *part, int n, double *out, hipStream_t s);

@@ -212,6 +212,105 @@ __global__ __launch_bounds__(kBoxThreads) void k_spread_box(const Xform *__restr
 }
 
 // ---------------------------------------------------------------------------
+// Value and gradient interpolation of float32 plans with one partial sum per
+// point and box (added to the cleared outputs by one atomic each): the box is
+// loaded once, a wavefront takes one point at a time.  It is 3.7 times slower
+// than the gather (k_gather.hip) and serves the calls that ask for the values
+// too, whose float32 sums the differentiable transform returns widened to
+// float64: they stay the sums of this order.
+template <typename R>
+__global__ __launch_bounds__(kBoxThreads) void k_grad_box(const Xform *__restrict__ xfs,
+                                                          const SItem *__restrict__ items, int nitems,
+                                                          int *__restrict__ queue, int m,
+                                                          const unsigned char *__restrict__ rec, int rec_bytes,
+                                                          const int *__restrict__ cs, R *__restrict__ outs)
+{
+    constexpr int NO = 4;
+    extern __shared__ uint4 smem16[];
+    __shared__ int s_item;
+    __shared__ int run_p0[kMaxBoxRuns], run_soff[kMaxBoxRuns + 1], run_sh[3 * kMaxBoxRuns], sh_scan[36];
+    const int M2 = 2 * m;
+    const int off_pz = (int)rec_off_pz(M2, sizeof(R));
+    const int off_d = (int)rec_prefix(M2, sizeof(R)) / (int)sizeof(R);
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    const int wave = uni(tid >> 6), lane = tid & 63, nwaves = nthr >> 6;
+    R *tile = reinterpret_cast<R *>(smem16);  // interleaved (re, im) per cell
+    for (int it = next_item(queue, &s_item); it < nitems; it = next_item(queue, &s_item)) {
+        const SItem W = items[it];
+        const Xform &X = xfs[W.xf];
+        const BoxGeom g = box_geom(X, W.tile);
+        const int cells = g.w[0] * g.w[1] * g.w[2];
+        const gptr<const R> grid = as_global(reinterpret_cast<const R *>(X.grid));
+        for (int i = tid; i < cells; i += nthr) {
+            const int z = i / (g.w[1] * g.w[2]), rr = i - z * g.w[1] * g.w[2];
+            const int y = rr / g.w[2], x = rr - y * g.w[2];
+            const size_t gi = (((size_t)(g.lo[0] + z) * X.n[1] + g.lo[1] + y) * X.n[2] + g.lo[2] + x) * 2;
+            tile[2 * i] = grid[gi];
+            tile[2 * i + 1] = grid[gi + 1];
+        }
+        int nruns;
+        const int S = box_runs(X, g, cs + X.key_off, run_p0, run_soff, run_sh, sh_scan, &nruns);
+        for (int k = wave; k < S; k += nwaves) {
+            int sh[3];
+            const long long pos = box_point(k, nruns, run_p0, run_soff, run_sh, sh);
+            const unsigned char *rp = rec + pos * rec_bytes;
+            const int2 hd = *reinterpret_cast<const int2 *>(rp + off_pz);
+            Clip c;
+            if (!clip_window(make_int2(uni(hd.x), uni(hd.y)), sh, g, m, c)) continue;
+            const R *ps = reinterpret_cast<const R *>(rp);
+            const R *dp = ps + off_d;
+            // dim-0 weight (and derivative) of tap `lane`
+            const R w0l = lane < M2 ? ps[lane] : R(0);
+            const R d0l = lane < M2 ? dp[lane] : R(0);
+            R v[2 * NO];
+#pragma unroll
+            for (int q = 0; q < 2 * NO; ++q) v[q] = R(0);
+            const int n2 = c.b[2] - c.a[2], rows = (c.b[1] - c.a[1]) * n2;
+            for (int i = lane; i < rows; i += 64) {
+                const int t1 = c.a[1] + i / n2, t2 = c.a[2] + i % n2;
+                const int yx = (c.f[1] + t1 - g.lo[1]) * g.w[2] + (c.f[2] + t2 - g.lo[2]);
+                R sr = R(0), si = R(0), dr = R(0), di = R(0);
+                for (int t0 = c.a[0]; t0 < c.b[0]; ++t0) {
+                    const int o = ((c.f[0] + t0 - g.lo[0]) * g.w[1] * g.w[2] + yx) * 2;
+                    const R gr = tile[o], gim = tile[o + 1];
+                    const R w = lane_value(w0l, t0);
+                    sr = fma(w, gr, sr);
+                    si = fma(w, gim, si);
+                    const R dw = lane_value(d0l, t0);
+                    dr = fma(dw, gr, dr);
+                    di = fma(dw, gim, di);
+                }
+                const R w1 = ps[M2 + t1], w2 = ps[2 * M2 + t2];
+                const R w12 = w1 * w2;
+                v[0] = fma(sr, w12, v[0]);
+                v[1] = fma(si, w12, v[1]);
+                const R d1 = dp[M2 + t1] * w2, d2 = w1 * dp[2 * M2 + t2];
+                v[2] = fma(dr, w12, v[2]);
+                v[3] = fma(di, w12, v[3]);
+                v[4] = fma(sr, d1, v[4]);
+                v[5] = fma(si, d1, v[5]);
+                v[6] = fma(sr, d2, v[6]);
+                v[7] = fma(si, d2, v[7]);
+            }
+            // the eight sums through the halving steps of wave_reduce.h
+            // (about 10 lane exchanges per word instead of 48): the
+            // 8-lane group j ends with the sum of value bitrev3(j), which
+            // its first lane adds to the output
+            const R a0 = halve32(v[0], v[1]), a1 = halve32(v[2], v[3]);
+            const R a2 = halve32(v[4], v[5]), a3 = halve32(v[6], v[7]);
+            const R r = halve8_sum(halve16(a0, a1), halve16(a2, a3));
+            if ((lane & 7) == 0) {
+                const int j = lane >> 3;
+                const int q = ((j & 1) << 2) | (j & 2) | (j >> 2);
+                atomicAdd(&outs[pos * (2 * NO) + q], r);
+            }
+        }
+        __syncthreads();  // the next box overwrites the tile
+    }
+    release_queue(queue);
+}
+
+// ---------------------------------------------------------------------------
 static int box_cus()
 {
     static int cus = 0;
@@ -241,11 +340,30 @@ hipError_t launch_spread_box(int m, const Xform *dxf, const SItem *items, int ni
     return hipGetLastError();
 }
 
+template <typename R>
+hipError_t launch_grad_box(int m, const Xform *dxf, const SItem *items, int nitems, int *queue,
+                             int max_cells, const unsigned char *rec, size_t rec_bytes, const int *cell_start,
+                             R *outs, hipStream_t s)
+{
+    if (nitems <= 0) return hipSuccess;
+    const size_t lds = (size_t)max_cells * 2 * sizeof(R);
+    auto kern = k_grad_box<R>;
+    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const int per_cu = std::max(1, std::min(4, (int)((160 * 1024) / (lds + 12 * 1024))));
+    const int grid = std::min(box_cus() * per_cu, nitems);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBoxThreads), lds, s, dxf, items, nitems, queue, m, rec,
+                       (int)rec_bytes, cell_start, outs);
+    return hipGetLastError();
+}
+
 template hipError_t launch_spread_box<double>(int, const Xform *, const SItem *, int, int *, int,
                                               const unsigned char *, size_t, const double *, const int *,
                                               hipStream_t);
 template hipError_t launch_spread_box<float>(int, const Xform *, const SItem *, int, int *, int,
                                              const unsigned char *, size_t, const float *, const int *,
                                              hipStream_t);
+template hipError_t launch_grad_box<float>(int, const Xform *, const SItem *, int, int *, int, const unsigned char *,
+                                           size_t, const int *, float *, hipStream_t);
 
 }  // namespace hpnfft

@@ -37,10 +37,16 @@ template <typename R> struct Complex;
 template <> struct Complex<float> { typedef float T __attribute__((ext_vector_type(2))); };
 template <> struct Complex<double> { typedef double T __attribute__((ext_vector_type(2))); };
 
-// all: every point of the plan, else only those of the transforms that use
-// boxes (Xform::goff: points of such transforms before this one).
+// which: every point of the plan, or those of the transforms that use boxes
+// (Xform::goff: points of such transforms before this one) or lines.
+//
+// SPLIT (float32 gradients, 2m = 8): a line record's window is summed in the
+// parts that the slabs of Zs planes cut it into, each part over the lanes
+// first, and column slots stay on their lanes: the order in which the staged
+// line sweeps add, so that the sums (which the differentiable transform
+// returns widened to float64) do not depend on the sweep.
 template <typename R, int M2, bool GRAD>
-__global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *__restrict__ xfs, int B, int all,
+__global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *__restrict__ xfs, int B, int which, int Zs,
                                                                   long long total, long long per_xcd,
                                                                   const unsigned char *__restrict__ rec,
                                                                   int rec_bytes, R *__restrict__ outs)
@@ -48,6 +54,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *_
     constexpr int m = M2 / 2, NO = GRAD ? 4 : 1, ROWS = M2 * M2;
     constexpr int OFF_PZ = (int)rec_off_pz(M2, sizeof(R));
     constexpr int OFF_D = (int)rec_prefix(M2, sizeof(R)) / (int)sizeof(R);
+    constexpr bool SPLIT = GRAD && sizeof(R) == 4 && M2 == 8;
     using C = typename Complex<R>::T;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -55,15 +62,18 @@ __global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *_
     const long long k = (long long)(blockIdx.x / kXcds) * (kGatherThreads / 64) + wave;
     const long long g = (long long)(blockIdx.x % kXcds) * per_xcd + k;
     if (k >= per_xcd || g >= total) return;
-    // the transform of point g
+    // the transform of point g: the last whose first point is not past it
+    auto first = [&](const Xform *X) __attribute__((always_inline)) {
+        return which == GATHER_ALL ? X->poff : which == GATHER_BOXES ? X->goff : X->poff - X->goff;
+    };
     int lo = 0, hi = B;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if ((all ? xfs[mid].poff : xfs[mid].goff) <= g) lo = mid;
+        if (first(xfs + mid) <= g) lo = mid;
         else hi = mid;
     }
     const Xform *X = xfs + lo;
-    const long long pos = all ? g : X->poff + (g - X->goff);
+    const long long pos = X->poff + (g - first(X));
     const int n0 = X->n[0], n1 = X->n[1], n2 = X->n[2];
     const unsigned char *rp = rec + (size_t)pos * rec_bytes;
     const cptr<int> hd = as_const(reinterpret_cast<const int *>(rp + OFF_PZ));
@@ -89,13 +99,13 @@ __global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *_
 #pragma unroll 1
     for (int i = lane; i < ((ROWS + 63) / 64) * 64; i += 64) {
         const int ic = ROWS % 64 == 0 ? i : min(i, ROWS - 1);  // (lanes past the last row repeat it with weight 0)
-        const int t1 = ic / M2, t2 = ic - t1 * M2;
+        // (lane <-> column slot: tap t in slot (t + xr) mod 2m)
+        const int t1 = ic / M2, s2 = ic - t1 * M2;
+        const int t2 = s2 - xr + (s2 < xr ? M2 : 0);
         int l1 = h.c1 - m + 1 + t1, l2 = h.c2 - m + 1 + t2;
         l1 += l1 < 0 ? n1 : (l1 >= n1 ? -n1 : 0);
         l2 += l2 < 0 ? n2 : (l2 >= n2 ? -n2 : 0);
         const gptr<const C> row = grid + ((size_t)l1 * n2 + l2);
-        int s2 = t2 + xr;
-        s2 -= s2 >= M2 ? M2 : 0;
         const R w1 = ROWS % 64 == 0 || i < ROWS ? ps[M2 + t1] : R(0), w2 = ps[2 * M2 + s2];
         C c[M2];
 #pragma unroll
@@ -105,6 +115,38 @@ __global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *_
             int l0 = f0 + t;
             l0 += l0 < 0 ? n0 : (l0 >= n0 ? -n0 : 0);
             c[s] = row[(size_t)l0 * pstride];
+        }
+        if constexpr (SPLIT) {
+            if (h.lines) {
+                const R w12 = w1 * w2, d1 = ps[OFF_D + M2 + t1] * w2, d2 = w1 * ps[OFF_D + 2 * M2 + s2];
+                R total = R(0);
+                int ta = 0;  // taps ta .. tb - 1 end at a slab's edge, or at the wrap
+                do {
+                    int l0 = f0 + ta;
+                    l0 += l0 < 0 ? n0 : (l0 >= n0 ? -n0 : 0);
+                    const int tb = min(M2, ta + min(n0, (l0 / Zs + 1) * Zs) - l0);
+                    R sr = R(0), si = R(0), dr = R(0), di = R(0);
+#pragma unroll
+                    for (int s = 0; s < M2; ++s) {
+                        const int t = (s - rot) & (M2 - 1);
+                        if (t < ta || t >= tb) continue;
+                        const R w = pc[s], dw = pc[OFF_D + s];
+                        sr = fma(w, c[s][0], sr);
+                        si = fma(w, c[s][1], si);
+                        dr = fma(dw, c[s][0], dr);
+                        di = fma(dw, c[s][1], di);
+                    }
+                    const R a0 = halve32(sr * w12, si * w12), a1 = halve32(dr * w12, di * w12);
+                    const R a2 = halve32(sr * d1, si * d1), a3 = halve32(sr * d2, si * d2);
+                    total += halve8_sum(halve16(a0, a1), halve16(a2, a3));
+                    ta = tb;
+                } while (ta < M2);
+                if ((lane & 7) == 0) {
+                    const int j = lane >> 3;
+                    outs[pos * 8 + (((j & 1) << 2) | (j & 2) | (j >> 2))] = total;
+                }
+                return;
+            }
         }
         R sr = R(0), si = R(0), dr = R(0), di = R(0);
 #pragma unroll
@@ -152,26 +194,26 @@ __global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *_
 }
 
 template <typename R, int M2>
-static hipError_t gather_m(bool grad, const Xform *dxf, int B, bool all, long long total, const unsigned char *rec,
+static hipError_t gather_m(bool grad, const Xform *dxf, int B, int which, int Zs, long long total, const unsigned char *rec,
                            size_t rec_bytes, R *outs, hipStream_t s)
 {
     constexpr int W = kGatherThreads / 64;
     const long long per_xcd = (total + kXcds - 1) / kXcds;
     const unsigned blocks = (unsigned)((per_xcd + W - 1) / W) * kXcds;
     auto kern = grad ? k_interp_gather<R, M2, true> : k_interp_gather<R, M2, false>;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kGatherThreads), 0, s, dxf, B, all ? 1 : 0, total, per_xcd, rec,
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kGatherThreads), 0, s, dxf, B, which, Zs, total, per_xcd, rec,
                        (int)rec_bytes, outs);
     return hipGetLastError();
 }
 
 template <typename R>
-hipError_t launch_interp_gather(int m, bool grad, const Xform *dxf, int B, bool all, long long total,
+hipError_t launch_interp_gather(int m, bool grad, const Xform *dxf, int B, int which, int Zs, long long total,
                                 const unsigned char *rec, size_t rec_bytes, R *outs, hipStream_t s)
 {
     if (total <= 0) return hipSuccess;
     switch (m) {
 #define HPNFFT_GATHER_CASE(MM) \
-    case MM: return gather_m<R, 2 * MM>(grad, dxf, B, all, total, rec, rec_bytes, outs, s);
+    case MM: return gather_m<R, 2 * MM>(grad, dxf, B, which, Zs, total, rec, rec_bytes, outs, s);
         HPNFFT_GATHER_CASE(1)
         HPNFFT_GATHER_CASE(2)
         HPNFFT_GATHER_CASE(3)
@@ -192,9 +234,9 @@ hipError_t launch_interp_gather(int m, bool grad, const Xform *dxf, int B, bool 
     }
 }
 
-template hipError_t launch_interp_gather<double>(int, bool, const Xform *, int, bool, long long,
+template hipError_t launch_interp_gather<double>(int, bool, const Xform *, int, int, int, long long,
                                                  const unsigned char *, size_t, double *, hipStream_t);
-template hipError_t launch_interp_gather<float>(int, bool, const Xform *, int, bool, long long,
+template hipError_t launch_interp_gather<float>(int, bool, const Xform *, int, int, int, long long,
                                                 const unsigned char *, size_t, float *, hipStream_t);
 
 }  // namespace hpnfft

@@ -1018,7 +1018,8 @@ template <typename R> int run_forward(hpnfft_plan_s *p, const void *fhat, void *
     if (rc) return rc;
     {
         PhaseTimer t(p, HPNFFT_PH_INTERP);
-        HCHECK(launch_interp_gather<R>(p->m, false, dxf, p->B, !lines, lines ? p->Mbox : p->Mtot,
+        HCHECK(launch_interp_gather<R>(p->m, false, dxf, p->B, lines ? GATHER_BOXES : GATHER_ALL, p->til.Zs,
+                                       lines ? p->Mbox : p->Mtot,
                                        p->at<unsigned char>(L.rec), L.rec_bytes, p->at<R>(L.outs), s));
         if (lines && use_lines(p)) {
             for (size_t b = 0; b < p->hx.size(); ++b)
@@ -1047,13 +1048,27 @@ int run_backward(hpnfft_plan_s *p, const void *f, const void *gfhat, void *grad_
     const Layout &L = p->L;
     hipStream_t s = p->stream;
     const Xform *dxf = p->at<Xform>(L.xf);
+    // (the float32 box sums are added to cleared outputs, the others stored)
+    if (sizeof(R) == 4 && grad_f && p->any_box && !p->det()) {
+        PhaseTimer t(p, HPNFFT_PH_ZERO);
+        HCHECK(launch_zero(p->ws + L.outs, L.outs_bytes, s));
+    }
     int rc = run_to_grid<R>(p, gfhat);
     if (rc) return rc;
     {
         PhaseTimer t(p, HPNFFT_PH_GRAD);
         const bool lines = p->any_lines && use_lines(p);
-        HCHECK(launch_interp_gather<R>(p->m, true, dxf, p->B, !lines, lines ? p->Mbox : p->Mtot,
-                                       p->at<unsigned char>(L.rec), L.rec_bytes, p->at<R>(L.outs), s));
+        const bool boxes = sizeof(R) == 4 && grad_f && p->any_box && !p->det();
+        if (boxes)
+            HCHECK(launch_grad_box<float>(p->m, dxf, p->at<SItem>(L.bitems), p->nbitems, p->at<int>(L.counters) + 1,
+                                          p->max_cells, p->at<unsigned char>(L.rec), L.rec_bytes,
+                                          p->at<int>(L.cell_start), p->at<float>(L.outs), s));
+        if (!(lines && boxes)) {
+            const GatherSet set = lines ? GATHER_BOXES : (boxes ? GATHER_LINES : GATHER_ALL);
+            HCHECK(launch_interp_gather<R>(p->m, true, dxf, p->B, set, p->til.Zs,
+                                           set == GATHER_ALL ? p->Mtot : set == GATHER_BOXES ? p->Mbox : p->Mtot - p->Mbox,
+                                           p->at<unsigned char>(L.rec), L.rec_bytes, p->at<R>(L.outs), s));
+        }
         if (lines) {
             for (size_t b = 0; b < p->hx.size(); ++b)
                 if (!p->tbox[b])
