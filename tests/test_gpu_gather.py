@@ -59,7 +59,7 @@ def test_gather(oracle_mod, N, M, m, method, prec):
             assert oracle_mod.rel_l2(out, ref) <= _tol(H, m, prec, n, False)
 
 
-@pytest.mark.parametrize("N,Zs", [((16, 14, 12), 32), ((18, 12, 10), 8), ((24, 10, 8), 32), ((10, 10, 10), 24)])
+@pytest.mark.parametrize("N,Zs", [((18, 12, 10), 8), ((24, 10, 8), 16), ((20, 10, 10), 24)])
 def test_float32_gradient_sums_do_not_depend_on_slabs_met(N, Zs):
     """Float32 line gradients sum a window in the parts its slabs cut it into:
     a point whose window meets one slab only is summed as one part, whatever
@@ -72,12 +72,12 @@ def test_float32_gradient_sums_do_not_depend_on_slabs_met(N, Zs):
     fh = torch.from_numpy(W.complex_normal(int(np.prod(N)), g)).cuda().to(torch.complex64)
     n0 = 2 * N[0]
     out = []
-    for zs in (Zs, 64):
+    for zs in (Zs, 32):  # (gradient plans take slabs of up to 32 planes here)
         p = H.Plan(N, M, m=4, precision="f32", method="lines", with_grad=True, tiles=(8, zs, 512))
         p.set_points(torch.from_numpy(x).cuda())
         out.append([v.cpu().numpy() for v in p.adjoint_backward(f, fh)])
     first = np.floor(x[:, 0] * n0).astype(int) % n0 - 3
-    whole = (first >= 0) & (first + 7 < n0) & (first // Zs == (first + 7) // Zs)
+    whole = (first >= 0) & (first + 7 < n0) & (first // Zs == (first + 7) // Zs) & (first // 32 == (first + 7) // 32)
     assert whole.any()
     for a, b in zip(out[0], out[1]):
         assert np.array_equal(a[whole], b[whole])
