@@ -12,6 +12,7 @@ constexpr int kWave = 64;          // CDNA wavefront width
 constexpr int kMaxM2 = 30;         // 2m <= 30  (m <= 15)
 constexpr int kMaxN = 1024;        // largest oversampled grid edge
 constexpr int kLdsBytes = 160 * 1024;  // gfx950 local data share per CU
+constexpr int kXcds = 8;           // L2 caches of the chip; consecutive workgroups go to consecutive ones
 
 // One transform of a plan (a plan over B transforms holds B of these in
 // device memory).  Grid storage is C order over (l0, l1, l2), l2 fastest, with
@@ -29,6 +30,7 @@ struct Xform {
     long long poff;    // first sorted point of this transform (packed arrays)
     long long foff;    // first frequency of this transform (packed fhat)
     long long goff;    // points of the box-method transforms before this one
+    int boff;          // output boxes (box method spread) of the transforms before this one
     long long key_off; // first entry of this transform's cell_start table
     void *grid;        // n0 n1 n2 complex
     void *tmpA;        // n0 n1 N2 complex
@@ -264,24 +266,20 @@ hipError_t launch_spread_det(int m, const Xform *dxf, const SItem *items, int ni
                              hipStream_t s);
 
 // Interpolation by gathering (k_gather.hip): all points, or those of the
-// transforms that use boxes or lines; total: their number; Zs: the line
-// method's slab depth.  outs need not be cleared.
-enum GatherSet { GATHER_ALL = 0, GATHER_BOXES, GATHER_LINES };
+// transforms that use boxes; total: their number; Zs: the line method's slab
+// depth, 0 in deterministic plans.  outs need not be cleared.
+enum GatherSet { GATHER_ALL = 0, GATHER_BOXES };
 template <typename R>
 hipError_t launch_interp_gather(int m, bool grad, const Xform *dxf, int B, int which, int Zs, long long total,
                                 const unsigned char *rec, size_t rec_bytes, R *outs, hipStream_t s);
 
 // Box method (k_boxes.hip): every workgroup owns one output box of the grid
 // and takes every point whose window reaches it.
+// nboxes: output boxes of all transforms that use boxes (Xform::boff).
+int spread_boxes(const Xform &X);
 template <typename R>
-hipError_t launch_spread_box(int m, const Xform *dxf, const SItem *items, int nitems, int *queue, int max_cells,
-                             const unsigned char *rec, size_t rec_bytes, const R *fs, const int *cell_start,
-                             hipStream_t s);
-
-// Values and gradients per output box (float32; outs cleared by the caller).
-template <typename R>
-hipError_t launch_grad_box(int m, const Xform *dxf, const SItem *items, int nitems, int *queue, int max_cells,
-                           const unsigned char *rec, size_t rec_bytes, const int *cell_start, R *outs, hipStream_t s);
+hipError_t launch_spread_box(int m, const Xform *dxf, int B, int nboxes, const unsigned char *rec, size_t rec_bytes,
+                             const R *fs, const int *cell_start, hipStream_t s);
 
 // Fixed-order sum of n float64 partials into *out (one workgroup).
 hipError_t launch_sum_partials(const double *part, int n, double *out, hipStream_t s);

@@ -16,7 +16,7 @@
 //
 // Bound by the caches' read rate and latency: 64 KB per point (float64, 2m =
 // 16) arrive at 17 TB/s.  Measured, with gradients: 165,888 ions on a 256^3
-// grid 1.11 -> 0.64 ms (float64, 2m = 16) and 0.33 -> 0.09 ms (float32, 2m =
+// grid 1.11 -> 0.64 ms (float64, 2m = 16) and 0.32 -> 0.18 ms (float32, 2m =
 // 8) against boxes of the grid in LDS that every point's window meets about
 // eight of; 200,000 points on 96^3, 1.54 -> 0.56 ms (2m = 16), 1.01 -> 0.33 ms
 // (2m = 12) and 0.130 -> 0.077 ms (float32, 2m = 8) against the staged line
@@ -31,20 +31,22 @@
 namespace hpnfft {
 
 constexpr int kGatherThreads = 256;
-constexpr int kXcds = 8;  // L2 caches of the chip; consecutive workgroups go to consecutive ones
 
 template <typename R> struct Complex;
 template <> struct Complex<float> { typedef float T __attribute__((ext_vector_type(2))); };
 template <> struct Complex<double> { typedef double T __attribute__((ext_vector_type(2))); };
 
 // which: every point of the plan, or those of the transforms that use boxes
-// (Xform::goff: points of such transforms before this one) or lines.
+// (Xform::goff: points of such transforms before this one).
 //
 // SPLIT (float32 gradients, 2m = 8): a line record's window is summed in the
 // parts that the slabs of Zs planes cut it into, each part over the lanes
 // first, and column slots stay on their lanes: the order in which the staged
-// line sweeps add, so that the sums (which the differentiable transform
-// returns widened to float64) do not depend on the sweep.
+// line sweeps add, so that the sums (which the differentiable transform and
+// the Ewald forces return widened to float64) do not depend on the sweep.
+// A box record's window likewise (Zs > 0), in the parts that the boxes of gbox
+// bins cut it into, the rows of a part on consecutive lanes (165,888 ions on
+// 256^3: 0.18 ms, 0.09 ms as one sum per window).
 template <typename R, int M2, bool GRAD>
 __global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *__restrict__ xfs, int B, int which, int Zs,
                                                                   long long total, long long per_xcd,
@@ -64,7 +66,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *_
     if (k >= per_xcd || g >= total) return;
     // the transform of point g: the last whose first point is not past it
     auto first = [&](const Xform *X) __attribute__((always_inline)) {
-        return which == GATHER_ALL ? X->poff : which == GATHER_BOXES ? X->goff : X->poff - X->goff;
+        return which == GATHER_ALL ? X->poff : X->goff;
     };
     int lo = 0, hi = B;
     while (hi - lo > 1) {
@@ -96,6 +98,74 @@ __global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *_
     for (int q = 0; q < 2 * NO; ++q) v[q] = R(0);
     const gptr<const C> grid = as_global(reinterpret_cast<const C *>(X->grid));
     const size_t pstride = (size_t)n1 * n2;
+    if constexpr (SPLIT) {
+        if (!h.lines && Zs > 0) {
+            // taps that begin a box or the grid: lane 8 d + t <-> tap t of dim d
+            const int d = lane >> 3;
+            const int n = d == 0 ? n0 : d == 1 ? n1 : n2;
+            const int nb = d == 0 ? X->nbox[0] : d == 1 ? X->nbox[1] : X->nbox[2];
+            const int gb = d == 0 ? X->gbox[0] : d == 1 ? X->gbox[1] : X->gbox[2];
+            int l = (d == 0 ? f0 : (d == 1 ? h.c1 : h.c2) - m + 1) + (lane & 7);
+            l += l < 0 ? n : (l >= n ? -n : 0);
+            const int bin = box_of(l, n, nb);
+            const unsigned cuts = (unsigned)__ballot(bin % gb == 0 && box_lo(bin, n, nb) == l);
+            auto next = [&](int d, int t) __attribute__((always_inline)) {  // (tap M2 ends the window)
+                return __builtin_ctz((cuts >> (8 * d) & 0xfe | 0x100) >> (t + 1)) + t + 1;
+            };
+            R sum = R(0);
+            for (int a1 = 0, b1; a1 < M2; a1 = b1) {
+                b1 = next(1, a1);
+                for (int a2 = 0, b2; a2 < M2; a2 = b2) {
+                    b2 = next(2, a2);
+                    const int w = b2 - a2;
+                    const bool in = lane < (b1 - a1) * w;
+                    // lane / w = lane inv >> 9
+                    const int inv = __builtin_amdgcn_readfirstlane((int)(512.0f * __builtin_amdgcn_rcpf((float)w))) + 1;
+                    const int r1 = in ? lane * inv >> 9 : 0, t1 = a1 + r1, t2 = a2 + (in ? lane - r1 * w : 0);
+                    int l1 = h.c1 - m + 1 + t1, l2 = h.c2 - m + 1 + t2;
+                    l1 += l1 < 0 ? n1 : (l1 >= n1 ? -n1 : 0);
+                    l2 += l2 < 0 ? n2 : (l2 >= n2 ? -n2 : 0);
+                    const gptr<const C> row = grid + ((size_t)l1 * n2 + l2);
+                    const R w1 = ps[M2 + t1], w2 = ps[2 * M2 + t2];
+                    const R e1 = ps[OFF_D + M2 + t1], e2 = ps[OFF_D + 2 * M2 + t2];
+                    C c[M2];
+                    if (in) {
+#pragma unroll
+                        for (int t = 0; t < M2; ++t) {
+                            int l0 = f0 + t;
+                            l0 += l0 < 0 ? n0 : (l0 >= n0 ? -n0 : 0);
+                            c[t] = row[(size_t)l0 * pstride];
+                        }
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < M2; ++t) c[t] = C{0, 0};
+                    }
+                    const R w12 = w1 * w2, d1 = e1 * w2, d2 = w1 * e2;
+                    for (int a0 = 0, b0; a0 < M2; a0 = b0) {
+                        b0 = next(0, a0);
+                        R sr = R(0), si = R(0), dr = R(0), di = R(0);
+#pragma unroll
+                        for (int t = 0; t < M2; ++t) {
+                            if (t < a0 || t >= b0) continue;
+                            const R w = pc[t], dw = pc[OFF_D + t];
+                            sr = fma(w, c[t][0], sr);
+                            si = fma(w, c[t][1], si);
+                            dr = fma(dw, c[t][0], dr);
+                            di = fma(dw, c[t][1], di);
+                        }
+                        const R p0 = halve32(sr * w12, si * w12), p1 = halve32(dr * w12, di * w12);
+                        const R p2 = halve32(sr * d1, si * d1), p3 = halve32(sr * d2, si * d2);
+                        sum += halve8_sum(halve16(p0, p1), halve16(p2, p3));
+                    }
+                }
+            }
+            if ((lane & 7) == 0) {
+                const int j = lane >> 3;
+                outs[pos * 8 + (((j & 1) << 2) | (j & 2) | (j >> 2))] = sum;
+            }
+            return;
+        }
+    }
 #pragma unroll 1
     for (int i = lane; i < ((ROWS + 63) / 64) * 64; i += 64) {
         const int ic = ROWS % 64 == 0 ? i : min(i, ROWS - 1);  // (lanes past the last row repeat it with weight 0)

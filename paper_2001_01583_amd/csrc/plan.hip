@@ -103,7 +103,8 @@ struct hpnfft_plan_s {
     bool any_lines = true;         // some transform uses the line sweeps
     std::vector<char> tbox;        // per transform: box method
     int max_cells = 0;
-    int nbitems = 0;               // box work items (one per output box)
+    int nbitems = 0;               // box work items (one per block of bins)
+    int nboxes = 0;                // output boxes of the box method's spread
     std::vector<SItem> h_box_items;
     int cus = 256;
     char arch[64] = "unknown";
@@ -394,9 +395,13 @@ void choose_methods(hpnfft_plan_s *p)
         p->tbox[b] = box;
     }
     p->Mbox = 0;
+    p->nboxes = 0;
     for (int b = 0; b < p->B; ++b) {
         p->hx[b].goff = p->Mbox;
-        if (p->tbox[b]) p->Mbox += p->hx[b].M;
+        p->hx[b].boff = p->nboxes;
+        if (!p->tbox[b]) continue;
+        p->Mbox += p->hx[b].M;
+        p->nboxes += spread_boxes(p->hx[b]);
     }
     p->any_box = std::count(p->tbox.begin(), p->tbox.end(), 1) > 0;
     p->any_lines = std::count(p->tbox.begin(), p->tbox.end(), 0) > 0;
@@ -969,9 +974,8 @@ template <typename R> int run_adjoint(hpnfft_plan_s *p, const void *f, void *fha
                                         p->at<unsigned char>(L.rec), L.rec_bytes, p->at<R>(L.fs),
                                         p->at<int>(L.cell_start), s));
         else if (p->any_box)
-            HCHECK(launch_spread_box<R>(p->m, dxf, p->at<SItem>(L.bitems), p->nbitems, p->at<int>(L.counters),
-                                        p->max_cells, p->at<unsigned char>(L.rec), L.rec_bytes, p->at<R>(L.fs),
-                                        p->at<int>(L.cell_start), s));
+            HCHECK(launch_spread_box<R>(p->m, dxf, p->B, p->nboxes, p->at<unsigned char>(L.rec), L.rec_bytes,
+                                        p->at<R>(L.fs), p->at<int>(L.cell_start), s));
         if (p->any_lines) {
             Tiling t = p->til;
             t.ring = use_ring(p, t);
@@ -1048,27 +1052,14 @@ int run_backward(hpnfft_plan_s *p, const void *f, const void *gfhat, void *grad_
     const Layout &L = p->L;
     hipStream_t s = p->stream;
     const Xform *dxf = p->at<Xform>(L.xf);
-    // (the float32 box sums are added to cleared outputs, the others stored)
-    if (sizeof(R) == 4 && grad_f && p->any_box && !p->det()) {
-        PhaseTimer t(p, HPNFFT_PH_ZERO);
-        HCHECK(launch_zero(p->ws + L.outs, L.outs_bytes, s));
-    }
     int rc = run_to_grid<R>(p, gfhat);
     if (rc) return rc;
     {
         PhaseTimer t(p, HPNFFT_PH_GRAD);
         const bool lines = p->any_lines && use_lines(p);
-        const bool boxes = sizeof(R) == 4 && grad_f && p->any_box && !p->det();
-        if (boxes)
-            HCHECK(launch_grad_box<float>(p->m, dxf, p->at<SItem>(L.bitems), p->nbitems, p->at<int>(L.counters) + 1,
-                                          p->max_cells, p->at<unsigned char>(L.rec), L.rec_bytes,
-                                          p->at<int>(L.cell_start), p->at<float>(L.outs), s));
-        if (!(lines && boxes)) {
-            const GatherSet set = lines ? GATHER_BOXES : (boxes ? GATHER_LINES : GATHER_ALL);
-            HCHECK(launch_interp_gather<R>(p->m, true, dxf, p->B, set, p->til.Zs,
-                                           set == GATHER_ALL ? p->Mtot : set == GATHER_BOXES ? p->Mbox : p->Mtot - p->Mbox,
-                                           p->at<unsigned char>(L.rec), L.rec_bytes, p->at<R>(L.outs), s));
-        }
+        HCHECK(launch_interp_gather<R>(p->m, true, dxf, p->B, lines ? GATHER_BOXES : GATHER_ALL, p->det() ? 0 : p->til.Zs,
+                                       lines ? p->Mbox : p->Mtot, p->at<unsigned char>(L.rec), L.rec_bytes,
+                                       p->at<R>(L.outs), s));
         if (lines) {
             for (size_t b = 0; b < p->hx.size(); ++b)
                 if (!p->tbox[b])
