@@ -3,14 +3,26 @@
 // with the crop to I_N and the division by the window's Fourier coefficients
 // ("Scaling"; "Subdividing" on the way back) fused into the first / last pass.
 //
-// One pass transforms all pencils along one dimension.  A workgroup loads
-// `count` pencils (coalesced: a run of contiguous elements per pencil row),
-// runs a mixed-radix (8, 4, 2, 3, 5, 7) Stockham autosort FFT in LDS with FP64
-// twiddles (rounded once for the float path), and stores only the outputs the
-// next step needs.  The stages run in place in one LDS buffer (each thread
-// reads its butterflies' inputs into registers before any output is
-// written), so more workgroups fit on a compute unit.  The passes are HBM-bound; pruning keeps the traffic at
-// about 2.6 grid volumes per transform instead of 6.
+// One pass transforms all pencils along one dimension.  A workgroup runs a
+// mixed-radix (8, 4, 2, 3, 5, 7) Stockham autosort FFT of `count` pencils with
+// FP64 twiddles (rounded once for the float path), one or more butterflies per
+// thread and stage.  The first stage takes its inputs from global memory and
+// the last one stores its outputs there (only those that the next step
+// needs), so LDS holds the data only between stages: a pass of s stages writes
+// and reads it s - 1 times.  Stages between run in place in one buffer (each
+// thread reads its butterflies' inputs into registers before any output is
+// written).  Lanes run along the pencil where its elements are contiguous
+// (dim 2) and across pencils otherwise, in global memory and in LDS.  Pruning
+// keeps the traffic at about 2.6 grid volumes per transform instead of 6.
+//
+// Bound by memory where the grid is large: 402 MB of the first adjoint pass over
+// 256^3 complex128 in 81 us (5.0 TB/s, the rate of a copy).  Measured against
+// loading every pencil to LDS, all stages in LDS with runtime divisions, and
+// storing from LDS: the six passes over 256^3 float32 326 -> 171 us, float64
+// 489 -> 326 us, 500^3 float64 5.14 -> 2.83 ms, a batch of 48 float32 grids 1.70
+// -> 0.73 ms, 32^3 float32 (all launch) 47 -> 29 us.  The arithmetic of a stage
+// is the same wherever its inputs lie (rounded()), and so are the results, bit
+// for bit.
 //
 // Adjoint (sign -):  grid[n0][n1][n2] --dim2--> A[n0][n1][N2] --dim1--> B[n0][N1][N2]
 //                    --dim0, x 1/c_k--> fhat[N0][N1][N2]
@@ -24,8 +36,7 @@
 namespace hpnfft {
 
 constexpr int kFftThreads = 256;
-constexpr int kFftCap = 2048;  // complex elements per LDS buffer (count * n)
-constexpr int kLoadU = 8;      // loads in flight per thread: kLoadU * kFftThreads >= kFftCap
+constexpr int kFftCap = 2048;  // complex elements per workgroup (count * n)
 
 template <typename R> struct C2 { R x, y; };
 // loads and stores through global pointers, member by member (the compiler
@@ -43,6 +54,12 @@ template <typename R> __device__ inline C2<R> cmul(C2<R> a, C2<R> b)
 }
 template <typename R> __device__ inline C2<R> cadd(C2<R> a, C2<R> b) { return {a.x + b.x, a.y + b.y}; }
 template <typename R> __device__ inline C2<R> csub(C2<R> a, C2<R> b) { return {a.x - b.x, a.y - b.y}; }
+// A product that stays one: it is not contracted with a sum that follows.
+template <typename R> __device__ inline C2<R> rounded(C2<R> a)
+{
+    asm volatile("" : "+v"(a.x), "+v"(a.y));
+    return a;
+}
 // multiply by i*S (S = +1 or -1)
 template <int S, typename R> __device__ inline C2<R> mul_is(C2<R> a) { return {-S * a.y, S * a.x}; }
 
@@ -146,53 +163,6 @@ template <int P, int S, typename R> __device__ inline void dft_odd(C2<R> *v)
     for (int r = 0; r < P; ++r) v[r] = out[r];
 }
 
-// One in-place Stockham stage of radix RAD for `count` pencils of length n:
-// every thread first reads the inputs of its butterflies into registers,
-// then (after a barrier) writes their outputs to the same buffer, so one LDS
-// buffer serves all stages.
-template <int RAD, int S, typename R>
-__device__ inline void stage(C2<R> *buf, const C2<R> *tw, int n, int ld, int count, int Ns)
-{
-    constexpr int MAXB = (kFftCap + RAD * kFftThreads - 1) / (RAD * kFftThreads);  // butterflies per thread
-    const int nb = n / RAD;
-    const int tstep = n / (Ns * RAD);
-    const int total = count * nb;
-    C2<R> v[MAXB][RAD];
-    int dst[MAXB];
-#pragma unroll
-    for (int q = 0; q < MAXB; ++q) {
-        const int t = threadIdx.x + q * kFftThreads;
-        dst[q] = -1;
-        if (t < total) {
-            const int pen = t / nb, j = t - pen * nb;
-            const int k = j % Ns;
-            const C2<R> *sp = buf + pen * ld;
-#pragma unroll
-            for (int r = 0; r < RAD; ++r) v[q][r] = sp[j + r * nb];
-            if (Ns > 1) {
-#pragma unroll
-                for (int r = 1; r < RAD; ++r) v[q][r] = cmul(v[q][r], tw[k * r * tstep]);
-            }
-            if (RAD == 2) dft2<S>(v[q]);
-            if (RAD == 3) dft3<S>(v[q]);
-            if (RAD == 4) dft4<S>(v[q]);
-            if (RAD == 8) dft8<S>(v[q]);
-            if (RAD == 5) dft_odd<5, S>(v[q]);
-            if (RAD == 7) dft_odd<7, S>(v[q]);
-            dst[q] = pen * ld + (j / Ns) * Ns * RAD + k;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < MAXB; ++q) {
-        if (dst[q] >= 0) {
-#pragma unroll
-            for (int r = 0; r < RAD; ++r) buf[dst[q] + r * Ns] = v[q][r];
-        }
-    }
-    __syncthreads();
-}
-
 struct PassGeom {
     int dim, n, N, Lin, Lout, inner;
     long long outer_len;  // number of outer indices
@@ -241,147 +211,222 @@ template <typename R> __device__ inline PassArrays<R> pass_arrays(int pass, cons
     return a;
 }
 
-// element (pencil p, position j) of an array with L positions per pencil
-__device__ inline long long pass_addr(const FItem &W, int inner, int p, int j, int L)
-{
-    if (inner == 1) return ((long long)W.outer + p) * L + j;
-    return ((long long)W.outer * L + j) * inner + W.inner0 + p;
-}
+// floor(a / d) for 0 <= a < 2^20 from rd = 1 / d to within 2^-22: (a + 1/2) / d
+// is at least 1 / (2 d) from an integer.
+__device__ inline int div_small(int a, float rd) { return (int)(((float)a + 0.5f) * rd); }
 
-// One item's input, in registers: kLoadU values per thread and their LDS
-// positions (-1: none).  Crop passes load all n positions of each pencil;
-// pad passes load the N nonzero ones (with the roll-off factors of the
-// Subdividing step in the first forward pass) into their FFT bins.
-template <typename R> struct PassLoad {
-    R vx[kLoadU], vy[kLoadU];
-    int at[kLoadU];
-};
-template <typename R>
-__device__ inline void pass_issue(int pass, const Xform &X, const FItem &W, void *fhat_base, PassLoad<R> &L)
-{
-    const PassGeom g = pass_geom(pass, X);
-    const PassArrays<R> a = pass_arrays<R>(pass, X, fhat_base);
-    const int n = g.n, ld = n, cnt = W.count, inner = g.inner;
-    const int Lin = g.crop ? n : g.N;
-    const int tot = cnt * Lin;
-    const int tid = threadIdx.x, nthr = blockDim.x;
-#pragma unroll
-    for (int u = 0; u < kLoadU; ++u) {
-        const int e = tid + u * nthr;
-        const int ec = e < tot ? e : tot - 1;  // clamped: no branch around the load
-        int p, j;
-        if (inner == 1) {
-            p = ec / Lin;
-            j = ec - p * Lin;
-        } else {
-            j = ec / cnt;
-            p = ec - j * cnt;
-        }
-        C2<R> w = gload<R>(a.src + pass_addr(W, inner, p, j, Lin));
-        if (!g.crop) {
-            if (g.roll_in) {
-                const int ii = W.inner0 + p;
-                const double f = as_global(X.roll[0])[j] * as_global(X.roll[1])[ii / X.N[2]] *
-                                 as_global(X.roll[2])[ii % X.N[2]];
-                w.x = (R)(w.x * f);
-                w.y = (R)(w.y * f);
-            }
-            int bin = j - g.N / 2;
-            if (bin < 0) bin += n;
-            j = bin;
-        }
-        L.vx[u] = w.x;
-        L.vy[u] = w.y;
-        L.at[u] = e < tot ? p * ld + j : -1;
+// Lanes run along the pencil (ROWS) or across pencils; SCALE: with the factors
+// of the Scaling / Subdividing step (dim 0).
+enum PassKind { ROWS, COLS, SCALE };
+
+// A workgroup's pencils: element j of pencil p of the input lies at src + j
+// stride + p src_p (stride 1 in ROWS, src_p 1 otherwise), the output likewise.
+template <typename R> struct Pencils {
+    int n, N, cnt;
+    float rcnt;  // 1 / cnt
+    gptr<const C2<R>> src;
+    gptr<C2<R>> dst;
+    int stride, src_p, dst_p;
+    gptr<const double> roll0, roll1, roll2;
+    int inner0, N2;
+    // factor of position j (dim 0) and pencil p
+    __device__ inline double factor(int j, int p) const
+    {
+        const int ii = inner0 + p;
+        return roll0[j] * roll1[ii / N2] * roll2[ii % N2];
     }
+    __host__ __device__ static inline int pad(int n) { return n + (n + 7) / 8; }
+};
+
+// One Stockham stage of radix RAD: inputs from global memory (FIRST) or LDS,
+// outputs to LDS or (LAST) global memory.
+enum StageAt { FIRST, MIDDLE, LAST };
+template <StageAt AT, int RAD, int S, PassKind KIND, typename R>
+__device__ __forceinline__ void stage(const Pencils<R> &P, C2<R> *buf, const C2<R> *tw, int Ns)
+{
+    constexpr bool CROP = S < 0;  // adjoint passes keep N of n outputs, forward ones have N of n inputs
+    constexpr int MAXB = (kFftCap + RAD * kFftThreads - 1) / (RAD * kFftThreads);  // butterflies per thread
+    const int n = P.n, nb = n / RAD;
+    const int total = P.cnt * nb;
+    const int h0 = P.N - P.N / 2, h1 = n - P.N / 2;  // bins [h0, h1) are cropped
+    const float rnb = __builtin_amdgcn_rcpf((float)nb), rNs = __builtin_amdgcn_rcpf((float)Ns);
+    // LDS position of element i of pencil p: a gap of one element in 8 spreads
+    // the strides of the stages over the banks
+    auto at = [&](int i, int p) __attribute__((always_inline)) {
+        const int k = i + (i >> 3);
+        return KIND == ROWS ? p * Pencils<R>::pad(n) + k : k * P.cnt + p;
+    };
+    C2<R> v[MAXB][RAD];
+    int pen[MAXB], jj[MAXB];
+    // (an opaque thread index: the positions of every radix would otherwise be
+    // kept in registers over the loop of stages)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+#pragma unroll
+    for (int q = 0; q < MAXB; ++q) {
+        const int t = tid + q * kFftThreads;
+        if (KIND == ROWS) {
+            pen[q] = div_small(t, rnb);
+            jj[q] = t - pen[q] * nb;
+        } else {
+            jj[q] = div_small(t, P.rcnt);
+            pen[q] = t - jj[q] * P.cnt;
+        }
+        if (t >= total) continue;
+        if constexpr (AT == FIRST) {
+            const gptr<const C2<R>> sp = P.src + (KIND == ROWS ? pen[q] * P.src_p : pen[q]);
+#pragma unroll
+            for (int r = 0; r < RAD; ++r) {
+                const int bin = jj[q] + r * nb;
+                if (CROP) {
+                    v[q][r] = gload<R>(sp + (KIND == ROWS ? bin : (long long)bin * P.stride));
+                } else {
+                    v[q][r] = C2<R>{R(0), R(0)};
+                    if (bin < h0 || bin >= h1) {
+                        const int j = bin < h0 ? bin + P.N / 2 : bin - h1;
+                        v[q][r] = gload<R>(sp + (KIND == ROWS ? j : (long long)j * P.stride));
+                        if (KIND == SCALE) {
+                            const double f = P.factor(j, pen[q]);
+                            v[q][r] = rounded(C2<R>{(R)(v[q][r].x * f), (R)(v[q][r].y * f)});
+                        }
+                    }
+                }
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < RAD; ++r) v[q][r] = buf[at(jj[q] + r * nb, pen[q])];
+            if (RAD > 1) {
+                const int k = jj[q] - div_small(jj[q], rNs) * Ns;
+                const int tstep = AT == LAST ? 1 : n / (Ns * RAD);
+#pragma unroll
+                for (int r = 1; r < RAD; ++r) v[q][r] = rounded(cmul(v[q][r], tw[k * r * tstep]));
+            }
+        }
+    }
+    if (AT == MIDDLE) __syncthreads();
+#pragma unroll
+    for (int q = 0; q < MAXB; ++q) {
+        if (tid + q * kFftThreads >= total) continue;
+        if (AT == FIRST && !CROP)
+#pragma unroll
+            for (int r = 0; r < RAD; ++r) v[q][r] = rounded(v[q][r]);
+        if (RAD == 2) dft2<S>(v[q]);
+        if (RAD == 3) dft3<S>(v[q]);
+        if (RAD == 4) dft4<S>(v[q]);
+        if (RAD == 8) dft8<S>(v[q]);
+        if (RAD == 5) dft_odd<5, S>(v[q]);
+        if (RAD == 7) dft_odd<7, S>(v[q]);
+#pragma unroll
+        for (int r = 0; r < RAD; ++r) v[q][r] = rounded(v[q][r]);
+        if constexpr (AT == LAST) {
+            const gptr<C2<R>> dp = P.dst + (KIND == ROWS ? pen[q] * P.dst_p : pen[q]);
+#pragma unroll
+            for (int r = 0; r < RAD; ++r) {
+                const int bin = jj[q] + r * nb;  // (the last stage has Ns = nb)
+                int o = bin;
+                if (CROP) {
+                    if (bin >= h0 && bin < h1) continue;
+                    o = bin < h0 ? bin + P.N / 2 : bin - h1;
+                }
+                C2<R> w = v[q][r];
+                if (CROP && KIND == SCALE) {
+                    const double f = P.factor(o, pen[q]);
+                    w.x = (R)(w.x * f);
+                    w.y = (R)(w.y * f);
+                }
+                gstore<R>(dp + (KIND == ROWS ? o : (long long)o * P.stride), w);
+            }
+        } else {
+            const int b = AT == FIRST ? jj[q] : div_small(jj[q], rNs), k = AT == FIRST ? 0 : jj[q] - b * Ns;
+#pragma unroll
+            for (int r = 0; r < RAD; ++r) buf[at(b * Ns * RAD + k + r * Ns, pen[q])] = v[q][r];
+        }
+    }
+    if (AT != LAST) __syncthreads();
 }
 
 // ODD: grids with factors 5 or 7 (their stages hold more values per thread;
 // the other grids run a variant without them, with fewer registers).
-template <typename R, int S, bool ODD>
+template <StageAt AT, int S, PassKind KIND, bool ODD, typename R>
+__device__ __forceinline__ void stage_of(int rad, const Pencils<R> &P, C2<R> *buf, const C2<R> *tw, int Ns)
+{
+    switch (rad) {
+    case 8: stage<AT, 8, S, KIND, R>(P, buf, tw, Ns); break;
+    case 4: stage<AT, 4, S, KIND, R>(P, buf, tw, Ns); break;
+    case 2: stage<AT, 2, S, KIND, R>(P, buf, tw, Ns); break;
+    case 3: stage<AT, 3, S, KIND, R>(P, buf, tw, Ns); break;
+    case 1:
+        if constexpr (AT != MIDDLE) stage<AT, 1, S, KIND, R>(P, buf, tw, Ns);
+        break;
+    default:
+        if constexpr (ODD) {
+            if (rad == 5) stage<AT, 5, S, KIND, R>(P, buf, tw, Ns);
+            else stage<AT, 7, S, KIND, R>(P, buf, tw, Ns);
+        }
+        break;
+    }
+}
+
+template <typename R, int S, PassKind KIND, bool ODD>
 __global__ __launch_bounds__(kFftThreads) void k_fft(int pass, const Xform *__restrict__ xfs,
-                                                     const FItem *__restrict__ items, int nitems, void *fhat_base)
+                                                     const FItem *__restrict__ items, int nitems, int per_xcd,
+                                                     void *fhat_base)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    // neighbouring items on one XCD (workgroups go round robin over them)
+    const int k8 = blockIdx.x / kXcds, it = (int)(blockIdx.x % kXcds) * per_xcd + k8;
+    if (k8 >= per_xcd || it >= nitems) return;
+    const FItem W = items[it];
+    const Xform &X = xfs[W.xf];
+    const PassGeom g = pass_geom(pass, X);
+    const PassArrays<R> a = pass_arrays<R>(pass, X, fhat_base);
+    const int n = g.n;
+    Pencils<R> P;
+    P.n = n;
+    P.N = g.N;
+    P.cnt = W.count;
+    P.rcnt = __builtin_amdgcn_rcpf((float)W.count);
+    P.src = a.src + (long long)W.outer * g.Lin * g.inner + W.inner0;  // (ROWS: inner 1, inner0 0)
+    P.dst = a.dst + (long long)W.outer * g.Lout * g.inner + W.inner0;
+    P.stride = g.inner;
+    P.src_p = g.Lin;
+    P.dst_p = g.Lout;
+    P.roll0 = as_global(X.roll[0]);
+    P.roll1 = as_global(X.roll[1]);
+    P.roll2 = as_global(X.roll[2]);
+    P.inner0 = W.inner0;
+    P.N2 = X.N[2];
     C2<R> *buf = reinterpret_cast<C2<R> *>(smem);
-    C2<R> *tw = buf + kFftCap;
-    const int tid = threadIdx.x, nthr = blockDim.x;
-    for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-        const FItem W = items[it];
-        const Xform &X = xfs[W.xf];
-        const PassGeom g = pass_geom(pass, X);
-        const int n = g.n, ld = n, cnt = W.count;
-        // all of the item's loads are issued before any LDS write
-        PassLoad<R> ld_regs;
-        pass_issue<R>(pass, X, W, fhat_base, ld_regs);
-        // twiddles exp(S 2 pi i j / n) of this dimension (the table holds
-        // exp(-2 pi i j / n))
-        const gptr<const C2<R>> twg = as_global(reinterpret_cast<const C2<R> *>(X.tw[g.dim]));
-        for (int j = tid; j < n; j += nthr) {
-            C2<R> w = gload<R>(twg + j);
-            if (S > 0) w.y = -w.y;
-            tw[j] = w;
-        }
-        // pad passes: the positions no input lands on are zero
-        if (!g.crop) {
-            const int z0 = g.N - g.N / 2, z1 = n - g.N / 2;  // [z0, z1) holds no data
-            const int zw = z1 - z0;
-            for (int e = tid; e < cnt * zw; e += nthr) {
-                const int p = e / zw, j = z0 + (e - p * zw);
-                buf[p * ld + j] = C2<R>{R(0), R(0)};
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kLoadU; ++u)
-            if (ld_regs.at[u] >= 0) buf[ld_regs.at[u]] = C2<R>{ld_regs.vx[u], ld_regs.vy[u]};
-        __syncthreads();
-
-        // ---- Stockham stages: radix 8 first, then 4, 2, 3, 5, 7 ----
-        int rem = n, Ns = 1;
-        while (rem > 1) {
-            const int rad = (rem % 8 == 0) ? 8 : (rem % 4 == 0) ? 4 : (rem % 2 == 0) ? 2 : (rem % 3 == 0) ? 3
-                          : (rem % 5 == 0) ? 5 : 7;
-            switch (rad) {
-            case 8: stage<8, S, R>(buf, tw, n, ld, cnt, Ns); break;
-            case 4: stage<4, S, R>(buf, tw, n, ld, cnt, Ns); break;
-            case 2: stage<2, S, R>(buf, tw, n, ld, cnt, Ns); break;
-            case 3: stage<3, S, R>(buf, tw, n, ld, cnt, Ns); break;
-            default:
-                if constexpr (ODD) {
-                    if (rad == 5) stage<5, S, R>(buf, tw, n, ld, cnt, Ns);
-                    else stage<7, S, R>(buf, tw, n, ld, cnt, Ns);
-                }
-                break;
-            }
-            Ns *= rad;
-            rem /= rad;
-        }
-
-        // ---- store (crop to I_N and Scaling in the last adjoint pass) ----
-        const PassArrays<R> a = pass_arrays<R>(pass, X, fhat_base);
-        const gptr<const double> roll0 = as_global(X.roll[0]), roll1 = as_global(X.roll[1]),
-                                 roll2 = as_global(X.roll[2]);
-        const int Lout = g.Lout, tot = cnt * Lout, inner = g.inner;
-        for (int e = tid; e < tot; e += nthr) {
-            int p, o;
-            if (inner == 1) { p = e / Lout; o = e - p * Lout; }
-            else { o = e / cnt; p = e - o * cnt; }
-            int bin = o;
-            if (g.crop) {
-                bin = o - g.N / 2;
-                if (bin < 0) bin += n;
-            }
-            C2<R> v = buf[p * ld + bin];
-            if (g.roll_out) {
-                const int ii = W.inner0 + p;
-                const double f = roll0[o] * roll1[ii / X.N[2]] * roll2[ii % X.N[2]];
-                v.x = (R)(v.x * f);
-                v.y = (R)(v.y * f);
-            }
-            gstore<R>(a.dst + pass_addr(W, inner, p, o, Lout), v);
-        }
-        __syncthreads();  // the next item writes the buffer
+    C2<R> *tw = buf + P.cnt * Pencils<R>::pad(n);
+    // twiddles exp(S 2 pi i j / n) of this dimension (the table holds
+    // exp(-2 pi i j / n)); the first stage, which uses none, ends with a barrier
+    const gptr<const C2<R>> twg = as_global(reinterpret_cast<const C2<R> *>(X.tw[g.dim]));
+    for (int j = threadIdx.x; j < n; j += kFftThreads) {
+        C2<R> w = gload<R>(twg + j);
+        if (S > 0) w.y = -w.y;
+        tw[j] = w;
     }
+    // radix 8 first, then 4, 2, 3, 5, 7 (a single stage is followed by a copy)
+    auto radix = [](int rem) __attribute__((always_inline)) {
+        return (rem % 8 == 0) ? 8 : (rem % 4 == 0) ? 4 : (rem % 2 == 0) ? 2 : (rem % 3 == 0) ? 3
+             : (rem % 5 == 0) ? 5 : (rem % 7 == 0) ? 7 : 1;
+    };
+    int rad = radix(n), Ns = rad, rem = n / rad;
+    stage_of<FIRST, S, KIND, ODD, R>(rad, P, buf, tw, 1);
+    for (rad = radix(rem); rem > rad; rad = radix(rem)) {
+        stage_of<MIDDLE, S, KIND, ODD, R>(rad, P, buf, tw, Ns);
+        Ns *= rad;
+        rem /= rad;
+    }
+    stage_of<LAST, S, KIND, ODD, R>(rad, P, buf, tw, Ns);
+}
+
+template <typename R, int S, bool ODD>
+static auto fft_kernel(int pass)
+{
+    return pass == P_ADJ0 || pass == P_FWD2   ? k_fft<R, S, ROWS, ODD>
+           : pass == P_ADJ1 || pass == P_FWD1 ? k_fft<R, S, COLS, ODD>
+                                              : k_fft<R, S, SCALE, ODD>;
 }
 
 template <typename R>
@@ -389,25 +434,16 @@ hipError_t launch_fft(int pass, const Xform *dxf, const FItem *items, int nitems
                       void *fhat_base, hipStream_t s)
 {
     if (nitems <= 0) return hipSuccess;
-    const size_t lds = (size_t)(kFftCap + max_n) * 2 * sizeof(R);
+    const size_t lds = (size_t)(kFftCap + kFftCap / 8 + max_n + 16) * 2 * sizeof(R);
     const bool adj = pass <= P_ADJ2;
-    auto kern = adj ? (odd ? k_fft<R, -1, true> : k_fft<R, -1, false>)
-                    : (odd ? k_fft<R, 1, true> : k_fft<R, 1, false>);
+    auto kern = adj ? (odd ? fft_kernel<R, -1, true>(pass) : fft_kernel<R, -1, false>(pass))
+                    : (odd ? fft_kernel<R, 1, true>(pass) : fft_kernel<R, 1, false>(pass));
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
-    static int cus = 0;
-    if (!cus) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-    }
-    // one workgroup per item up to a few rounds of the chip (LDS, 8 x 256
-    // threads per CU); beyond that workgroups take several items in turn
-    const int per_cu = std::max(1, std::min(8, (int)((160 * 1024) / (lds + 512))));
-    const int grid = std::min(nitems, cus * per_cu * 4);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kFftThreads), lds, s, pass, dxf, items, nitems, fhat_base);
+    const int per_xcd = (nitems + kXcds - 1) / kXcds;
+    hipLaunchKernelGGL(kern, dim3((unsigned)per_xcd * kXcds), dim3(kFftThreads), lds, s, pass, dxf, items, nitems, per_xcd,
+                       fhat_base);
     return hipGetLastError();
 }
 
