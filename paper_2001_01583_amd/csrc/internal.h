@@ -31,6 +31,9 @@ struct Xform {
     long long foff;    // first frequency of this transform (packed fhat)
     long long goff;    // points of the box-method transforms before this one
     int boff;          // output boxes (box method spread) of the transforms before this one
+    int wave0;         // wavefronts of 64 points of the transforms before this one
+    int ioff;          // (tile, slab) pairs of the line-method transforms before this one
+    long long coff;    // first entry of this transform's run costs (a multiple of 64)
     long long key_off; // first entry of this transform's cell_start table
     void *grid;        // n0 n1 n2 complex
     void *tmpA;        // n0 n1 N2 complex
@@ -38,6 +41,20 @@ struct Xform {
     const double *roll[3];  // 1/c_k for k = -N_t/2 .. N_t/2-1
     const void *tw[3];      // n_t twiddles exp(-2 pi i j / n_t), plan precision
 };
+
+// The transform of entry e of a packed array: the last one whose first entry
+// (member `first`) is not past e.
+template <typename T, typename E>
+__device__ inline int xform_of(const Xform *xfs, int B, T Xform::*first, E e)
+{
+    int lo = 0, hi = B;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (xfs[mid].*first <= e) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
 
 // Work item of the spread / interpolation kernels: lines [lb, le) of one
 // tile, restricted to one slab of planes along dim 0.
@@ -214,17 +231,20 @@ hipError_t launch_copy(void *dst, const void *src, size_t bytes, int cus, hipStr
 // them as M x 3 with the flat dims zero.
 // Box-method plans (X.nbox[0] > 0) sort by output box instead of by line.
 // keys_out (if not null) receives every point's sort key.
-hipError_t launch_bin_count(const double *x, const float *xf32, long long M, const Xform &X, int T, int BW,
-                            int flat, int *counts, int *rank, int *err, double *xs_out, int *keys_out,
-                            hipStream_t s);
-hipError_t launch_scan(int *data, long long n, int *tmp, hipStream_t s);
-// fixed_pos (if not null): sorted positions already in ipos (deterministic
-// mode); perm and ipos are then left as they are.
+// Wavefronts w0 .. w0 + nwaves - 1 of the plan's points (Xform::wave0).  x or
+// x32: the caller's points (both null: xs holds them); err: the domain check;
+// rank: each point's rank in its cell; counts: from Xform::key_off on.
+hipError_t launch_bin_count(const double *x, const float *x32, const Xform *dxf, int B, int w0, int nwaves, int T, int BW,
+                            double *xs, int *counts, int *rank, int *err, int *keys_out, hipStream_t s);
+// Exclusive sums in place; with xfs, entries of transform b (Xform::key_off) less
+// its first point.
+hipError_t launch_scan(int *data, long long n, int *tmp, hipStream_t s, const Xform *xfs = nullptr, int B = 0);
+// ipos: the points' ranks on entry, their sorted positions on return; fixed:
+// it holds the sorted positions already (deterministic mode), and perm is set.
 template <typename R>
-hipError_t launch_bin_scatter(const double *x, const float *xf32, long long M, const Xform &X, int T, int m,
-                              const WindowParams &wp, const double *poly, const int *cell_start, const int *rank, int *perm,
-                              int *ipos, unsigned char *rec, size_t rec_bytes, bool grad, const int *fixed_pos,
-                              hipStream_t s);
+hipError_t launch_bin_scatter(const double *xs, const Xform *dxf, int B, int nwaves, int T, int m, const WindowParams &wp,
+                              const double *poly, const int *cell_start, int *perm, int *ipos, unsigned char *rec,
+                              size_t rec_bytes, bool grad, bool fixed, hipStream_t s);
 template <typename R>
 hipError_t launch_gather(const void *f, const int *perm, long long total, R *fs, hipStream_t s);
 template <typename R>

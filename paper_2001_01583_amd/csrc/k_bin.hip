@@ -69,39 +69,49 @@ __device__ inline int sort_key(const int c[3], int T, int ntx, int n0, int BW)
 // autotuner) read.  xs_out may be null when x already is that copy.
 // Plans of d < 3 dimensions (flat = 3 - d leading dims without a
 // coordinate) read d values per point and store three, the flat ones zero.
+//
+// One launch for all transforms of a plan: wavefronts of 64 points, each of
+// one transform (a batch of 48 float32 transforms, all of set_points: 1.72 ms
+// in 290 launches of a few microseconds each, 0.56 ms in seven).
 template <typename XT>
-__global__ void k_bin_count(const XT *__restrict__ x, long long M, int n0, int n1, int n2, int T, int ntx,
-                            int BW, int flat, int nb0, int nb1, int nb2, int *__restrict__ counts,
-                            int *__restrict__ rank, int *__restrict__ err, double *__restrict__ xs_out,
-                            int *__restrict__ keys_out)
+__global__ __launch_bounds__(256) void k_bin_count(const XT *__restrict__ xin, const Xform *__restrict__ xfs, int B,
+                                                   int w0, int nwaves, int T, int BW, double *__restrict__ xs,
+                                                   int *__restrict__ counts, int *__restrict__ rank,
+                                                   int *__restrict__ err, int *__restrict__ keys_out)
 {
-    long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int w = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w >= nwaves) return;
+    const Xform &X = xfs[xform_of(xfs, B, &Xform::wave0, w0 + w)];
+    const long long M = X.M, j = (long long)(w0 + w - X.wave0) * 64 + (threadIdx.x & 63);
     if (j >= M) return;
-    const int n[3] = {n0, n1, n2};
-    const int nbox[3] = {nb0, nb1, nb2};
+    const int n[3] = {X.n[0], X.n[1], X.n[2]};
+    const int nbox[3] = {X.nbox[0], X.nbox[1], X.nbox[2]};
+    const int flat = xin ? X.flat : 0;  // (the stored copy holds three values per point)
     const int d = 3 - flat;
+    const XT *x = xin ? xin + X.poff * d : nullptr;
+    double *xb = xs + X.poff * 3;
     bool bad = false;
     int c[3];
     double xv[3];
     for (int t = 0; t < 3; ++t) {
-        xv[t] = t < flat ? 0.0 : (double)x[j * d + (t - flat)];
+        xv[t] = t < flat ? 0.0 : x ? (double)x[j * d + (t - flat)] : xb[j * 3 + t];
         double u;
         c[t] = cell_of(xv[t], n[t], &u, &bad);
     }
-    if (xs_out) {
+    if (x) {
         if (flat == 0) {
             // the copy runs over the flat array (words j, j + M, j + 2M), so
             // every store instruction writes one contiguous span
 #pragma unroll
-            for (int t = 0; t < 3; ++t) xs_out[j + t * M] = (double)x[j + t * M];
+            for (int t = 0; t < 3; ++t) xb[j + t * M] = (double)x[j + t * M];
         } else {
 #pragma unroll
-            for (int t = 0; t < 3; ++t) xs_out[j * 3 + t] = xv[t];
+            for (int t = 0; t < 3; ++t) xb[j * 3 + t] = xv[t];
         }
     }
     if (bad) atomicOr(err, 1);
-    const int key = nb0 ? box_key(c, n, nbox) : sort_key(c, T, ntx, n0, BW);
-    rank[j] = atomicAdd(&counts[key], 1);
+    const int key = nbox[0] ? box_key(c, n, nbox) : sort_key(c, T, X.ntx, n[0], BW);
+    rank[X.poff + j] = atomicAdd(&counts[X.key_off + key], 1);
     if (keys_out) keys_out[j] = key;
 }
 
@@ -144,34 +154,31 @@ __device__ inline double horner(const double *__restrict__ c, double v)
     return r;
 }
 
-// Point j's sorted position (written to perm and ipos unless the positions
-// are fixed), window tables in record slot order and record header.
+// Point j's sorted position (its rank in ipos on entry; written to perm and
+// ipos unless the positions are fixed), window tables in record slot order and record header.
 template <typename R, int M2, bool GRAD>
-__device__ inline long long scatter_point(long long j, const double *__restrict__ xd, const float *__restrict__ xf,
-                                          long long poff, int n0, int n1, int n2, int T, int ntx,
-                                          const int *__restrict__ cell_start, const int *__restrict__ rank,
-                                          int *__restrict__ perm, int *__restrict__ ipos, const WindowParams &wp,
-                                          const double *__restrict__ poly, int flat, int nb0, int nb1, int nb2,
-                                          const int *__restrict__ fixed_pos, R (&w)[3 * M2],
+__device__ inline long long scatter_point(long long j, const double *__restrict__ xs, const Xform &X, int T,
+                                          const int *__restrict__ cell_start, int *__restrict__ perm,
+                                          int *__restrict__ ipos, const WindowParams &wp,
+                                          const double *__restrict__ poly, bool fixed, R (&w)[3 * M2],
                                           R (&dw)[GRAD ? 3 * M2 : 1], int2 &head)
 {
+    const long long poff = X.poff;
+    const int flat = X.flat, nb0 = X.nbox[0];
     constexpr int m = M2 / 2;
     constexpr int NC = sizeof(R) == 4 ? kPolyF32 : kPolyF64;
-    const int n[3] = {n0, n1, n2};
+    const int n[3] = {X.n[0], X.n[1], X.n[2]};
     bool bad = false;
     int c[3];
     double u[3];
     for (int t = 0; t < 3; ++t) {
-        const double xv = xd ? xd[j * 3 + t] : (double)xf[j * 3 + t];
-        c[t] = cell_of(xv, n[t], &u[t], &bad);
+        c[t] = cell_of(xs[(poff + j) * 3 + t], n[t], &u[t], &bad);
     }
-    const int nbox[3] = {nb0, nb1, nb2};
-    const int key = nb0 ? box_key(c, n, nbox) : sort_key(c, T, ntx, n0, block_w(M2));
-    long long pos;
-    if (fixed_pos) {
-        pos = fixed_pos[poff + j];
-    } else {
-        pos = poff + cell_start[key] + rank[j];
+    const int nbox[3] = {nb0, X.nbox[1], X.nbox[2]};
+    const int key = nb0 ? box_key(c, n, nbox) : sort_key(c, T, X.ntx, n[0], block_w(M2));
+    long long pos = ipos[poff + j];  // (the rank in its cell, unless fixed)
+    if (!fixed) {
+        pos += poff + cell_start[X.key_off + key];
         perm[pos] = (int)(poff + j);
         ipos[poff + j] = (int)pos;
     }
@@ -303,24 +310,23 @@ __device__ inline long long scatter_point(long long j, const double *__restrict_
 // One thread per point, each storing its own record (gradient plans, whose
 // records carry the derivative tables too).
 template <typename R, int M2, bool GRAD>
-__global__ __launch_bounds__(256) void k_bin_scatter(const double *__restrict__ xd, const float *__restrict__ xf,
-                                                     long long M, long long poff, int n0, int n1, int n2, int T,
-                                                     int ntx, const int *__restrict__ cell_start,
-                                                     const int *__restrict__ rank, int *__restrict__ perm,
-                                                     int *__restrict__ ipos, unsigned char *__restrict__ rec,
-                                                     size_t rec_bytes, WindowParams wp,
-                                                     const double *__restrict__ poly, int flat, int nb0, int nb1,
-                                                     int nb2, const int *__restrict__ fixed_pos)
+__global__ __launch_bounds__(256) void k_bin_scatter(const double *__restrict__ xs, const Xform *__restrict__ xfs,
+                                                     int B, int nwaves, int T, const int *__restrict__ cell_start,
+                                                     int *__restrict__ perm, int *__restrict__ ipos,
+                                                     unsigned char *__restrict__ rec, size_t rec_bytes,
+                                                     WindowParams wp, const double *__restrict__ poly, int fixed)
 {
     constexpr int NW = 3 * M2;
     static_assert((NW * sizeof(R)) % 8 == 0, "window block is a whole number of 8-byte units");
-    const long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= M) return;
+    const int wv = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wv >= nwaves) return;
+    const Xform &X = xfs[xform_of(xfs, B, &Xform::wave0, wv)];
+    const long long j = (long long)(wv - X.wave0) * 64 + (threadIdx.x & 63);
+    if (j >= X.M) return;
     R w[NW];
     R dw[GRAD ? NW : 1];
     int2 head;
-    const long long pos = scatter_point<R, M2, GRAD>(j, xd, xf, poff, n0, n1, n2, T, ntx, cell_start, rank, perm,
-                                                     ipos, wp, poly, flat, nb0, nb1, nb2, fixed_pos, w, dw, head);
+    const long long pos = scatter_point<R, M2, GRAD>(j, xs, X, T, cell_start, perm, ipos, wp, poly, fixed, w, dw, head);
     unsigned char *rp = rec + pos * rec_bytes;
     store_block<NW * sizeof(R)>(rp, w);
     *reinterpret_cast<int2 *>(rp + rec_off_pz(M2, sizeof(R))) = head;
@@ -333,14 +339,11 @@ __global__ __launch_bounds__(256) void k_bin_scatter(const double *__restrict__ 
 // records instead of one 16-byte piece of 64 records.  The value slot is
 // left zero (the sweeps that stage records fill it per call).
 template <typename R, int M2>
-__global__ __launch_bounds__(64) void k_bin_scatter_lds(const double *__restrict__ xd, const float *__restrict__ xf,
-                                                        long long M, long long poff, int n0, int n1, int n2, int T,
-                                                        int ntx, const int *__restrict__ cell_start,
-                                                        const int *__restrict__ rank, int *__restrict__ perm,
-                                                        int *__restrict__ ipos, unsigned char *__restrict__ rec,
-                                                        size_t rec_bytes, WindowParams wp,
-                                                        const double *__restrict__ poly, int flat, int nb0, int nb1,
-                                                        int nb2, const int *__restrict__ fixed_pos)
+__global__ __launch_bounds__(64) void k_bin_scatter_lds(const double *__restrict__ xs, const Xform *__restrict__ xfs,
+                                                        int B, int T, const int *__restrict__ cell_start,
+                                                        int *__restrict__ perm, int *__restrict__ ipos,
+                                                        unsigned char *__restrict__ rec, size_t rec_bytes,
+                                                        WindowParams wp, const double *__restrict__ poly, int fixed)
 {
     constexpr int NW = 3 * M2;
     constexpr int RB = (int)rec_prefix(M2, sizeof(R));  // record bytes staged
@@ -349,15 +352,15 @@ __global__ __launch_bounds__(64) void k_bin_scatter_lds(const double *__restrict
     extern __shared__ uint4 sm[];  // 64 records, then 64 positions
     int *spos = reinterpret_cast<int *>(sm + 64 * U);
     const int lane = threadIdx.x;
-    const long long j0 = (long long)blockIdx.x * 64;
+    const Xform &X = xfs[xform_of(xfs, B, &Xform::wave0, (int)blockIdx.x)];
+    const long long M = X.M, j0 = (long long)((int)blockIdx.x - X.wave0) * 64;
     const long long j = j0 + lane;
     if (j < M) {
         R w[NW];
         R dw[1];
         int2 head;
-        const long long pos = scatter_point<R, M2, false>(j, xd, xf, poff, n0, n1, n2, T, ntx, cell_start, rank,
-                                                          perm, ipos, wp, poly, flat, nb0, nb1, nb2, fixed_pos, w,
-                                                          dw, head);
+        const long long pos = scatter_point<R, M2, false>(j, xs, X, T, cell_start, perm, ipos, wp, poly, fixed, w, dw,
+                                                          head);
         uint4 *lp = sm + lane * U;
         constexpr int NU32 = NW * (int)sizeof(R) / 4;  // words of the window tables
         unsigned wv[NU32];
@@ -449,8 +452,11 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const int *__restr
 
 // offs: block totals (direct: their prefix is summed here) or, when
 // !direct, already-scanned block offsets; null for a single block.
+// xfs: the points of the transforms before an entry's own are taken off its
+// sum (a thread's entries belong to one transform: key_off is a multiple of 64).
 __global__ __launch_bounds__(kScanThreads) void k_scan_apply(int *__restrict__ data, long long n,
-                                                             const int *__restrict__ offs, int direct)
+                                                             const int *__restrict__ offs, int direct,
+                                                             const Xform *__restrict__ xfs, int B)
 {
     __shared__ int sh[kScanThreads / 64];
     int base = 0;
@@ -484,6 +490,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(int *__restrict__ d
     for (int i = 0; i < kScanPer; ++i) s += v[i];
     int total;
     int run = base + scan_block256(s, sh, &total);
+    if (B > 1) run -= (int)xfs[xform_of(xfs, B, &Xform::key_off, e0)].poff;
 #pragma unroll
     for (int i = 0; i < kScanPer; ++i) {
         const int c = v[i];
@@ -502,12 +509,13 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(int *__restrict__ d
 }
 
 // data must be 16-byte aligned; tmp holds nb + nb / 2048 + 64 ints.
-hipError_t launch_scan(int *data, long long n, int *tmp, hipStream_t s)
+hipError_t launch_scan(int *data, long long n, int *tmp, hipStream_t s, const Xform *xfs, int B)
 {
     if (n <= 0) return hipSuccess;
     const long long nb = (n + kScanBlock - 1) / kScanBlock;
     if (nb <= 1) {
-        hipLaunchKernelGGL(k_scan_apply, dim3(1), dim3(kScanThreads), 0, s, data, n, (const int *)nullptr, 0);
+        hipLaunchKernelGGL(k_scan_apply, dim3(1), dim3(kScanThreads), 0, s, data, n, (const int *)nullptr, 0,
+                           xfs, B);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, data, n, tmp);
@@ -517,58 +525,51 @@ hipError_t launch_scan(int *data, long long n, int *tmp, hipStream_t s)
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(kScanThreads), 0, s, data, n, (const int *)tmp,
-                       direct ? 1 : 0);
+                       direct ? 1 : 0, xfs, B);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-hipError_t launch_bin_count(const double *x, const float *xf32, long long M, const Xform &X, int T, int BW,
-                            int flat, int *counts, int *rank, int *err, double *xs_out, int *keys_out,
-                            hipStream_t s)
+hipError_t launch_bin_count(const double *x, const float *x32, const Xform *dxf, int B, int w0, int nwaves, int T, int BW,
+                            double *xs, int *counts, int *rank, int *err, int *keys_out, hipStream_t s)
 {
-    if (M <= 0) return hipSuccess;
-    const unsigned nb = (unsigned)((M + 255) / 256);
-    if (x)
-        hipLaunchKernelGGL(k_bin_count<double>, dim3(nb), dim3(256), 0, s, x, M, X.n[0], X.n[1], X.n[2], T,
-                           X.ntx, BW, flat, X.nbox[0], X.nbox[1], X.nbox[2], counts, rank, err, xs_out, keys_out);
+    if (nwaves <= 0) return hipSuccess;
+    const unsigned nb = (unsigned)((nwaves + 3) / 4);
+    if (x32)
+        hipLaunchKernelGGL(k_bin_count<float>, dim3(nb), dim3(256), 0, s, x32, dxf, B, w0, nwaves, T, BW, xs, counts, rank,
+                           err, keys_out);
     else
-        hipLaunchKernelGGL(k_bin_count<float>, dim3(nb), dim3(256), 0, s, xf32, M, X.n[0], X.n[1], X.n[2], T,
-                           X.ntx, BW, flat, X.nbox[0], X.nbox[1], X.nbox[2], counts, rank, err, xs_out, keys_out);
+        hipLaunchKernelGGL(k_bin_count<double>, dim3(nb), dim3(256), 0, s, x, dxf, B, w0, nwaves, T, BW, xs, counts, rank,
+                           err, keys_out);
     return hipGetLastError();
 }
 
 template <typename R, int M2>
-static void scatter_m(const double *x, const float *xf32, long long M, const Xform &X, int T,
-                      const int *cell_start, const int *rank, int *perm, int *ipos, unsigned char *rec,
-                      size_t rec_bytes, const WindowParams &wp, const double *poly, bool grad, const int *fixed_pos,
-                      hipStream_t s)
+static void scatter_m(const double *xs, const Xform *dxf, int B, int nwaves, int T, const int *cell_start, int *perm,
+                      int *ipos, unsigned char *rec, size_t rec_bytes, const WindowParams &wp, const double *poly,
+                      bool grad, bool fixed, hipStream_t s)
 {
     if (!grad) {
         constexpr size_t lds = 64 * rec_prefix(M2, sizeof(R)) + 64 * 4;
-        const unsigned nb = (unsigned)((M + 63) / 64);
         auto kl = k_bin_scatter_lds<R, M2>;
-        hipLaunchKernelGGL(kl, dim3(nb), dim3(64), lds, s, x, xf32, M, X.poff, X.n[0],
-                           X.n[1], X.n[2], T, X.ntx, cell_start, rank, perm, ipos, rec, rec_bytes, wp, poly, X.flat,
-                           X.nbox[0], X.nbox[1], X.nbox[2], fixed_pos);
+        hipLaunchKernelGGL(kl, dim3((unsigned)nwaves), dim3(64), lds, s, xs, dxf, B, T, cell_start, perm, ipos, rec,
+                           rec_bytes, wp, poly, fixed ? 1 : 0);
         return;
     }
-    const unsigned nb = (unsigned)((M + 255) / 256);
     auto kg = k_bin_scatter<R, M2, true>;
-    hipLaunchKernelGGL(kg, dim3(nb), dim3(256), 0, s, x, xf32, M, X.poff, X.n[0], X.n[1],
-                       X.n[2], T, X.ntx, cell_start, rank, perm, ipos, rec, rec_bytes, wp, poly, X.flat, X.nbox[0],
-                       X.nbox[1], X.nbox[2], fixed_pos);
+    hipLaunchKernelGGL(kg, dim3((unsigned)((nwaves + 3) / 4)), dim3(256), 0, s, xs, dxf, B, nwaves, T, cell_start, perm,
+                       ipos, rec, rec_bytes, wp, poly, fixed ? 1 : 0);
 }
 
 template <typename R>
-hipError_t launch_bin_scatter(const double *x, const float *xf32, long long M, const Xform &X, int T, int m,
-                              const WindowParams &wp, const double *poly, const int *cell_start, const int *rank,
-                              int *perm, int *ipos, unsigned char *rec, size_t rec_bytes, bool grad,
-                              const int *fixed_pos, hipStream_t s)
+hipError_t launch_bin_scatter(const double *xs, const Xform *dxf, int B, int nwaves, int T, int m, const WindowParams &wp,
+                              const double *poly, const int *cell_start, int *perm, int *ipos, unsigned char *rec,
+                              size_t rec_bytes, bool grad, bool fixed, hipStream_t s)
 {
-    if (M <= 0) return hipSuccess;
+    if (nwaves <= 0) return hipSuccess;
     switch (m) {
 #define HPNFFT_SCATTER_CASE(MM) \
-    case MM: scatter_m<R, 2 * MM>(x, xf32, M, X, T, cell_start, rank, perm, ipos, rec, rec_bytes, wp, poly, grad, fixed_pos, s); break;
+    case MM: scatter_m<R, 2 * MM>(xs, dxf, B, nwaves, T, cell_start, perm, ipos, rec, rec_bytes, wp, poly, grad, fixed, s); break;
         HPNFFT_SCATTER_CASE(1)
         HPNFFT_SCATTER_CASE(2)
         HPNFFT_SCATTER_CASE(3)
@@ -590,11 +591,11 @@ hipError_t launch_bin_scatter(const double *x, const float *xf32, long long M, c
     return hipGetLastError();
 }
 
-template hipError_t launch_bin_scatter<double>(const double *, const float *, long long, const Xform &, int, int,
-                                               const WindowParams &, const double *, const int *, const int *, int *, int *,
-                                               unsigned char *, size_t, bool, const int *, hipStream_t);
-template hipError_t launch_bin_scatter<float>(const double *, const float *, long long, const Xform &, int, int,
-                                              const WindowParams &, const double *, const int *, const int *, int *, int *,
-                                              unsigned char *, size_t, bool, const int *, hipStream_t);
+template hipError_t launch_bin_scatter<double>(const double *, const Xform *, int, int, int, int, const WindowParams &,
+                                               const double *, const int *, int *, int *, unsigned char *, size_t, bool,
+                                               bool, hipStream_t);
+template hipError_t launch_bin_scatter<float>(const double *, const Xform *, int, int, int, int, const WindowParams &,
+                                              const double *, const int *, int *, int *, unsigned char *, size_t, bool,
+                                              bool, hipStream_t);
 
 }  // namespace hpnfft

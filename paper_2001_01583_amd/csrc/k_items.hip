@@ -29,27 +29,32 @@ __device__ inline int line_cost(const int *cs_line, int n0, int z0, int zs, int 
     return c;
 }
 
-// One thread per (tile, slab, run): the run's cost goes to
-// lcost[(tile * nslab + slab) * nl + run] (consecutive threads, consecutive
-// words) and into the grand total (one atomic per workgroup: atomics on one
-// address serialise).
+// One thread per (tile, slab, run) of the line-method transforms: the run's
+// cost goes to lcost[coff + (tile * nslab + slab) * nl + run] (consecutive
+// threads, consecutive words) and into the grand total (one atomic per
+// workgroup: atomics on one address serialise).
 constexpr int kCostThreads = 1024;
-__global__ __launch_bounds__(kCostThreads) void k_tile_cost(const int *__restrict__ cell_start, int n0, int T,
-                                                            int Zs, int m, int BW, int nslab, long long n,
-                                                            int *__restrict__ lcost,
+__global__ __launch_bounds__(kCostThreads) void k_tile_cost(const int *__restrict__ cell_start,
+                                                            const Xform *__restrict__ xfs, int B, long long entries,
+                                                            int T, int Zs, int m, int BW, int *__restrict__ lcost,
                                                             unsigned long long *__restrict__ total)
 {
     __shared__ int wsum[kCostThreads / 64];
-    const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    // (a wavefront's entries belong to one transform: coff is a multiple of 64)
+    const long long e = (long long)blockIdx.x * blockDim.x + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
     const int nl = T * T / BW;
     int c = 0;
-    if (g < n) {
-        const int li = (int)(g % nl);
-        const long long ts = g / nl;
-        const int slab = (int)(ts % nslab), tile = (int)(ts / nslab);
-        const int z0 = slab * Zs, zs = min(Zs, n0 - z0);
-        c = line_cost(cell_start + ((long long)tile * nl + li) * n0 * BW, n0, z0, zs, m, BW);
-        lcost[g] = c;
+    if (e < entries) {
+        const Xform &X = xfs[xform_of(xfs, B, &Xform::coff, e)];
+        const long long g = e - X.coff + (threadIdx.x & 63);
+        if (g < (long long)X.ntx * X.nty * X.nslab * nl && X.nbox[0] == 0) {
+            const int li = (int)(g % nl), n0 = X.n[0];
+            const long long ts = g / nl;
+            const int slab = (int)(ts % X.nslab), tile = (int)(ts / X.nslab);
+            const int z0 = slab * Zs, zs = min(Zs, n0 - z0);
+            c = line_cost(cell_start + X.key_off + ((long long)tile * nl + li) * n0 * BW, n0, z0, zs, m, BW);
+            lcost[X.coff + g] = c;
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
@@ -68,22 +73,25 @@ __global__ __launch_bounds__(kCostThreads) void k_tile_cost(const int *__restric
 // cap becomes one item).  The workgroup counts its items first and reserves
 // their slots in the list with one atomic.
 constexpr int kItemWaves = 16;
-__global__ __launch_bounds__(kItemWaves * 64) void k_make_items(const int *__restrict__ lcost, int xf, int T, int BW,
-                                                                int ntiles, int nslab,
+__global__ __launch_bounds__(kItemWaves * 64) void k_make_items(const int *__restrict__ lcost,
+                                                                const Xform *__restrict__ xfs, int B, int pairs,
+                                                                int T, int BW,
                                                                 const unsigned long long *__restrict__ total,
                                                                 int cap_div, int min_cap, int max_items,
                                                                 SItem *__restrict__ items, int *__restrict__ nitems,
                                                                 int *__restrict__ overflow)
 {
     __shared__ int wcount[kItemWaves], wbase[kItemWaves];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int g = blockIdx.x * kItemWaves + w;
-    const bool valid = g < ntiles * nslab;
-    const int tile = valid ? g / nslab : 0, slab = valid ? g % nslab : 0;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool valid = (int)blockIdx.x * kItemWaves + w < pairs;
+    const int gp = valid ? blockIdx.x * kItemWaves + w : 0;
+    const int xf = xform_of(xfs, B, &Xform::ioff, gp);
+    const int nslab = xfs[xf].nslab, g = gp - xfs[xf].ioff;
+    const int tile = g / nslab, slab = g % nslab;
     const long long capl = (long long)(*total / (unsigned long long)cap_div);
     const int cap = capl < min_cap ? min_cap : (int)capl;
     const int nl = T * T / BW;
-    const int *lc_pair = lcost + (long long)(valid ? g : 0) * nl;
+    const int *lc_pair = lcost + xfs[xf].coff + (long long)g * nl;
     int c = 0;
     if (valid)
         for (int li = lane; li < nl; li += 64) c += lc_pair[li];
@@ -158,26 +166,22 @@ __global__ __launch_bounds__(kItemWaves * 64) void k_make_items(const int *__res
     });
 }
 
-hipError_t launch_tile_cost(const int *cell_start, const Xform &X, int T, int Zs, int m, int *lcost,
-                            unsigned long long *total, hipStream_t s)
+hipError_t launch_tile_cost(const int *cell_start, const Xform *dxf, int B, long long entries, int T, int Zs, int m,
+                            int *lcost, unsigned long long *total, hipStream_t s)
 {
-    const int BW = block_w(2 * m);
-    const long long n = (long long)X.ntx * X.nty * X.nslab * (T * T / BW);
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tile_cost, dim3((unsigned)((n + kCostThreads - 1) / kCostThreads)), dim3(kCostThreads), 0, s,
-                       cell_start, X.n[0], T, Zs, m, BW, X.nslab, n, lcost, total);
+    if (entries <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_tile_cost, dim3((unsigned)((entries + kCostThreads - 1) / kCostThreads)), dim3(kCostThreads), 0, s,
+                       cell_start, dxf, B, entries, T, Zs, m, block_w(2 * m), lcost, total);
     return hipGetLastError();
 }
 
-hipError_t launch_make_items(const int *lcost, int xf, const Xform &X, int T, int m, const unsigned long long *total,
-                             int cap_div, int min_cap, int max_items, SItem *items, int *nitems, int *overflow,
-                             hipStream_t s)
+hipError_t launch_make_items(const int *lcost, const Xform *dxf, int B, long long pairs, int T, int m,
+                             const unsigned long long *total, int cap_div, int min_cap, int max_items, SItem *items,
+                             int *nitems, int *overflow, hipStream_t s)
 {
-    const long long pairs = (long long)X.ntx * X.nty * X.nslab;  // one wavefront per pair
-    if (pairs <= 0) return hipSuccess;
+    if (pairs <= 0) return hipSuccess;  // one wavefront per pair
     hipLaunchKernelGGL(k_make_items, dim3((unsigned)((pairs + kItemWaves - 1) / kItemWaves)), dim3(kItemWaves * 64), 0, s,
-                       lcost, xf, T,
-                       block_w(2 * m), X.ntx * X.nty, X.nslab, total, cap_div, min_cap, max_items, items, nitems,
+                       lcost, dxf, B, (int)pairs, T, block_w(2 * m), total, cap_div, min_cap, max_items, items, nitems,
                        overflow);
     return hipGetLastError();
 }

@@ -29,11 +29,11 @@
 #include "window.h"
 
 namespace hpnfft {
-hipError_t launch_tile_cost(const int *cell_start, const Xform &X, int T, int Zs, int m, int *lcost,
-                            unsigned long long *total, hipStream_t s);
-hipError_t launch_make_items(const int *lcost, int xf, const Xform &X, int T, int m, const unsigned long long *total,
-                             int cap_div, int min_cap, int max_items, SItem *items, int *nitems, int *overflow,
-                             hipStream_t s);
+hipError_t launch_tile_cost(const int *cell_start, const Xform *dxf, int B, long long entries, int T, int Zs, int m,
+                            int *lcost, unsigned long long *total, hipStream_t s);
+hipError_t launch_make_items(const int *lcost, const Xform *dxf, int B, long long pairs, int T, int m,
+                             const unsigned long long *total, int cap_div, int min_cap, int max_items, SItem *items,
+                             int *nitems, int *overflow, hipStream_t s);
 }  // namespace hpnfft
 
 using namespace hpnfft;
@@ -62,12 +62,12 @@ int fft_count(int n)
 }
 
 struct Layout {
-    size_t counters, setp, grids, tmpA, tmpB, cell_start, scan_tmp, rank, perm, ipos, fs, xs, rec, outs, tcost, poly,
+    size_t counters, setp, grids, tmpA, tmpB, cell_start, scan_tmp, perm, ipos, fs, xs, rec, outs, tcost, poly,
         items, fit[3], ewald, roll, tw, xf, total;
     size_t dkeys = 0, dkeys_out = 0, dvals = 0, dvals_out = 0, dsort = 0, dsort_bytes = 0;  // deterministic sort
     size_t bitems = 0;  // box work items
     size_t rec_bytes = 0;
-    std::vector<size_t> grid_off, tmpA_off, tmpB_off, key_off, tcost_off, roll_off;
+    std::vector<size_t> grid_off, tmpA_off, tmpB_off, key_off, roll_off;
     std::map<int, size_t> tw_off;
     int max_items = 0, nfit[3] = {0, 0, 0}, ew_blocks = 0;
     size_t grids_bytes = 0, outs_bytes = 0;
@@ -83,6 +83,7 @@ struct hpnfft_plan_s {
     std::vector<Xform> hx;
     std::vector<long long> keys;
     long long Mtot = 0, Ftot = 0, Mbox = 0;  // points, frequencies, points of box transforms
+    long long pairs = 0, costs = 0;          // (tile, slab) pairs and run costs of the line transforms
     Tiling til{16, 16, 1024};
     hipStream_t stream = nullptr;
     char *ws = nullptr;
@@ -539,13 +540,10 @@ void build_layout(hpnfft_plan_s *p)
         off = align256(off + bytes);
         return o;
     };
-    L.counters = take(256);
-    L.setp = take(256);
     // the float64 copy of the points sits at the same offset in every layout
     // (it depends on the point count only), so a re-tiled plan keeps it
     L.xs = take((size_t)p->Mtot * 24);
-    size_t gbytes = 0;
-    long long maxkeys = 0, maxM = 0, pairs = 0, maxF = 0;
+    long long maxM = 0, pairs = 0, maxF = 0;
     p->h_box_items.clear();
     p->max_cells = 0;
     for (int b = 0; b < p->B; ++b) {
@@ -571,20 +569,22 @@ void build_layout(hpnfft_plan_s *p)
             for (long long q = 0; q < nboxes; ++q) p->h_box_items.push_back(SItem{b, (int)q, 0, 0, 0, 0, 0, 0});
             p->max_cells = std::max(p->max_cells, (int)cells);
         }
-        maxkeys = std::max(maxkeys, p->keys[b]);
         maxM = std::max(maxM, X.M);
         if (!p->tbox[b]) pairs += (long long)X.ntx * X.nty * X.nslab;
         maxF = std::max(maxF, (long long)X.N[0] * X.N[1] * X.N[2]);
     }
-    // grids (contiguous, zeroed by one launch)
+    // grids, those of the line method first (zeroed by one launch; the box
+    // method writes every cell)
     L.grids = off;
-    for (int b = 0; b < p->B; ++b) {
-        const Xform &X = p->hx[b];
-        L.grid_off.push_back(off);
-        gbytes += align256((size_t)X.n[0] * X.n[1] * X.n[2] * C);
-        off = align256(off + (size_t)X.n[0] * X.n[1] * X.n[2] * C);
+    L.grid_off.resize(p->B);
+    for (int box = 0; box < 2; ++box) {
+        for (int b = 0; b < p->B; ++b)
+            if ((p->tbox[b] != 0) == (box != 0)) {
+                const Xform &X = p->hx[b];
+                L.grid_off[b] = take((size_t)X.n[0] * X.n[1] * X.n[2] * C);
+            }
+        if (!box) L.grids_bytes = off - L.grids;
     }
-    L.grids_bytes = off - L.grids;
     L.tmpA = off;
     for (int b = 0; b < p->B; ++b) {
         const Xform &X = p->hx[b];
@@ -595,11 +595,14 @@ void build_layout(hpnfft_plan_s *p)
         const Xform &X = p->hx[b];
         L.tmpB_off.push_back(take((size_t)X.n[0] * X.N[1] * X.N[2] * C));
     }
+    // status words, queue counters and the cell counts of all transforms:
+    // cleared by one launch, and scanned by one
+    L.counters = take(256);
+    L.setp = take(256);
     L.cell_start = off;
     for (int b = 0; b < p->B; ++b) L.key_off.push_back(take((size_t)p->keys[b] * 4));
-    long long nb = (maxkeys + 4095) / 4096;
+    const long long nb = ((long long)(off - L.cell_start) / 4 + 4095) / 4096;
     L.scan_tmp = take((size_t)(nb + nb / 2048 + 64) * 4);
-    L.rank = take((size_t)maxM * 4);
     L.perm = take((size_t)p->Mtot * 4);
     L.ipos = take((size_t)p->Mtot * 4);
     L.fs = take((size_t)p->Mtot * C);
@@ -615,11 +618,18 @@ void build_layout(hpnfft_plan_s *p)
         L.dsort_bytes = det_sort_bytes(maxM);
         L.dsort = take(L.dsort_bytes);
     }
-    L.tcost = off;
+    p->costs = p->pairs = 0;
     for (int b = 0; b < p->B; ++b) {
-        const Xform &X = p->hx[b];
-        L.tcost_off.push_back(take(p->tbox[b] ? 0 : (size_t)X.ntx * X.nty * X.nslab * (T * T / block_w(p->M2())) * 4));
+        Xform &X = p->hx[b];
+        X.wave0 = b ? p->hx[b - 1].wave0 + (int)((p->hx[b - 1].M + 63) / 64) : 0;
+        X.coff = p->costs;
+        X.ioff = (int)p->pairs;
+        if (p->tbox[b]) continue;
+        const long long n = (long long)X.ntx * X.nty * X.nslab;
+        p->pairs += n;
+        p->costs += (n * (T * T / block_w(p->M2())) + 63) / 64 * 64;
     }
+    L.tcost = take((size_t)p->costs * 4);
     L.max_items = (int)std::min<long long>(pairs + (long long)p->cus * 4 + 64, 0x7fffffffLL / 64);
     L.items = take((size_t)L.max_items * sizeof(SItem));
     L.bitems = take(std::max<size_t>(1, p->h_box_items.size()) * sizeof(SItem));
@@ -651,7 +661,6 @@ void build_layout(hpnfft_plan_s *p)
         }
     L.xf = take((size_t)p->B * sizeof(Xform));
     L.total = off + 256;
-    (void)gbytes;
 }
 
 // Window values along one dimension as polynomials: for tap t the function
@@ -881,52 +890,42 @@ int bin_points(hpnfft_plan_s *p, const double *x = nullptr, const float *x32 = n
     const Layout &L = p->L;
     hipStream_t s = p->stream;
     int *setp = p->at<int>(L.setp);  // [0] err, [1] nitems, [2] overflow, [4..5] total (u64)
-    // the status words and the sweeps' work-queue counters (adjacent; the
-    // sweeps reset their counters themselves after every launch)
-    HCHECK(launch_zero(p->ws + L.counters, L.setp + 256 - L.counters, s));
+    // the status words, the sweeps' work-queue counters (the sweeps reset their
+    // counters themselves after every launch) and the cell counts
+    HCHECK(launch_zero(p->ws + L.counters, L.key_off[p->B - 1] + (size_t)p->keys[p->B - 1] * 4 - L.counters, s));
     double *xs = p->at<double>(L.xs);
-    const bool stored = !x && !x32;
-    unsigned long long *total = reinterpret_cast<unsigned long long *>(setp + 4);
-    for (int b = 0; b < p->B; ++b) {
-        const Xform &X = p->hx[b];
-        int *cs = p->at<int>(L.key_off[b]);
-        HCHECK(launch_zero(cs, (size_t)p->keys[b] * 4, s));
-        double *xb = xs + X.poff * 3;
-        // the caller's points have 3 - flat coordinates each; the stored copy three
-        const int dc = 3 - X.flat;
-        HCHECK(launch_bin_count(stored ? xb : (x ? x + X.poff * dc : nullptr), x32 ? x32 + X.poff * dc : nullptr,
-                                X.M, X, p->til.T, block_w(p->M2()), stored ? 0 : X.flat, cs, p->at<int>(L.rank),
-                                setp, stored ? nullptr : xb, p->det() ? p->at<int>(L.dkeys) : nullptr, s));
-        HCHECK(launch_scan(cs, p->keys[b], p->at<int>(L.scan_tmp), s));
-        if (p->det()) {
-            // stable order within each bin: sort (bin, input index)
+    const Xform *dxf = p->at<Xform>(L.xf);
+    int *cs = p->at<int>(L.cell_start), *perm = p->at<int>(L.perm), *ipos = p->at<int>(L.ipos);
+    const Xform &Z = p->hx[p->B - 1];
+    const int nwaves = Z.wave0 + (int)((Z.M + 63) / 64);
+    const int BW = block_w(p->M2());
+    if (p->det()) {
+        // stable order within each bin: sort (bin, input index)
+        for (int b = 0; b < p->B; ++b) {
+            const Xform &X = p->hx[b];
+            HCHECK(launch_bin_count(x, x32, dxf, p->B, X.wave0, (int)((X.M + 63) / 64), p->til.T, BW, xs, cs, ipos, setp,
+                                    p->at<int>(L.dkeys), s));
             int bits = 1;
             while ((1LL << bits) < p->keys[b]) ++bits;
             HCHECK(launch_det_sort(p->at<int>(L.dkeys), X.M, bits, p->at<int>(L.dkeys_out), p->at<int>(L.dvals),
-                                   p->at<int>(L.dvals_out), p->ws + L.dsort, L.dsort_bytes, X.poff,
-                                   p->at<int>(L.perm), p->at<int>(L.ipos), s));
+                                   p->at<int>(L.dvals_out), p->ws + L.dsort, L.dsort_bytes, X.poff, perm, ipos, s));
         }
-        const int *fixed = p->det() ? p->at<int>(L.ipos) : nullptr;
-        if (p->prec == HPNFFT_F32)
-            HCHECK(launch_bin_scatter<float>(xb, nullptr, X.M, X, p->til.T, p->m, p->wp,
-                                             p->poly_ok ? p->at<double>(L.poly) : nullptr, cs,
-                                             p->at<int>(L.rank), p->at<int>(L.perm), p->at<int>(L.ipos),
-                                             p->at<unsigned char>(L.rec), L.rec_bytes, p->grad(), fixed, s));
-        else
-            HCHECK(launch_bin_scatter<double>(xb, nullptr, X.M, X, p->til.T, p->m, p->wp,
-                                              p->poly_ok ? p->at<double>(L.poly) : nullptr, cs,
-                                              p->at<int>(L.rank), p->at<int>(L.perm), p->at<int>(L.ipos),
-                                              p->at<unsigned char>(L.rec), L.rec_bytes, p->grad(), fixed, s));
-        if (!p->tbox[b])
-            HCHECK(launch_tile_cost(cs, X, p->til.T, p->til.Zs, p->m, p->at<int>(L.tcost_off[b]), total, s));
+    } else {
+        HCHECK(launch_bin_count(x, x32, dxf, p->B, 0, nwaves, p->til.T, BW, xs, cs, ipos, setp, nullptr, s));
     }
-    const int cap_div = p->cus * 4;
-    for (int b = 0; b < p->B; ++b) {
-        if (p->tbox[b]) continue;
-        const Xform &X = p->hx[b];
-        HCHECK(launch_make_items(p->at<int>(L.tcost_off[b]), b, X, p->til.T, p->m, total, cap_div, kMinCap,
-                                 L.max_items, p->at<SItem>(L.items), setp + 1, setp + 2, s));
-    }
+    HCHECK(launch_scan(cs, (long long)(L.key_off[p->B - 1] - L.cell_start) / 4 + p->keys[p->B - 1],
+                       p->at<int>(L.scan_tmp), s, dxf, p->B));
+    const double *poly = p->poly_ok ? p->at<double>(L.poly) : nullptr;
+    if (p->prec == HPNFFT_F32)
+        HCHECK(launch_bin_scatter<float>(xs, dxf, p->B, nwaves, p->til.T, p->m, p->wp, poly, cs, perm, ipos,
+                                         p->at<unsigned char>(L.rec), L.rec_bytes, p->grad(), p->det(), s));
+    else
+        HCHECK(launch_bin_scatter<double>(xs, dxf, p->B, nwaves, p->til.T, p->m, p->wp, poly, cs, perm, ipos,
+                                          p->at<unsigned char>(L.rec), L.rec_bytes, p->grad(), p->det(), s));
+    unsigned long long *total = reinterpret_cast<unsigned long long *>(setp + 4);
+    HCHECK(launch_tile_cost(cs, dxf, p->B, p->costs, p->til.T, p->til.Zs, p->m, p->at<int>(L.tcost), total, s));
+    HCHECK(launch_make_items(p->at<int>(L.tcost), dxf, p->B, p->pairs, p->til.T, p->m, total, p->cus * 4, kMinCap,
+                             L.max_items, p->at<SItem>(L.items), setp + 1, setp + 2, s));
     // err, nitems, overflow, pad, total cost (u64).  The copy goes to pinned
     // memory and the host polls its event: a blocking wait would leave the
     // GPU idle for the wake-up latency as well.
