@@ -154,8 +154,38 @@ __device__ inline double horner(const double *__restrict__ c, double v)
     return r;
 }
 
-// Point j's sorted position (its rank in ipos on entry; written to perm and
-// ipos unless the positions are fixed), window tables in record slot order and record header.
+// Point j's cell and offsets, and its sorted position (its rank in ipos on
+// entry; written to perm and ipos unless the positions are fixed).
+template <int M2>
+__device__ inline long long place_point(long long j, const double *__restrict__ xs, const Xform &X, int T,
+                                        const int *__restrict__ cell_start, int *__restrict__ perm,
+                                        int *__restrict__ ipos, bool fixed, int (&c)[3], double (&u)[3])
+{
+    const long long poff = X.poff;
+    const int n[3] = {X.n[0], X.n[1], X.n[2]};
+    bool bad = false;
+    for (int t = 0; t < 3; ++t) c[t] = cell_of(xs[(poff + j) * 3 + t], n[t], &u[t], &bad);
+    const int nbox[3] = {X.nbox[0], X.nbox[1], X.nbox[2]};
+    const int key = nbox[0] ? box_key(c, n, nbox) : sort_key(c, T, X.ntx, n[0], block_w(M2));
+    long long pos = ipos[poff + j];  // (the rank in its cell, unless fixed)
+    if (!fixed) {
+        pos += poff + cell_start[X.key_off + key];
+        perm[pos] = (int)(poff + j);
+        ipos[poff + j] = (int)pos;
+    }
+    return pos;
+}
+
+// Record header of a point of cell c.
+template <int M2>
+__device__ inline int2 point_head(const int (&c)[3], bool box)
+{
+    const int c12 = (c[1] << kBoxCellBits) | c[2];
+    return make_int2(c[0], box ? c12 : (c12 << kLineBits) | (c[2] & (block_w(M2) - 1)));
+}
+
+// Point j's sorted position, window tables in record slot order and record
+// header.
 template <typename R, int M2, bool GRAD>
 __device__ inline long long scatter_point(long long j, const double *__restrict__ xs, const Xform &X, int T,
                                           const int *__restrict__ cell_start, int *__restrict__ perm,
@@ -163,25 +193,13 @@ __device__ inline long long scatter_point(long long j, const double *__restrict_
                                           const double *__restrict__ poly, bool fixed, R (&w)[3 * M2],
                                           R (&dw)[GRAD ? 3 * M2 : 1], int2 &head)
 {
-    const long long poff = X.poff;
     const int flat = X.flat, nb0 = X.nbox[0];
     constexpr int m = M2 / 2;
     constexpr int NC = sizeof(R) == 4 ? kPolyF32 : kPolyF64;
     const int n[3] = {X.n[0], X.n[1], X.n[2]};
-    bool bad = false;
     int c[3];
     double u[3];
-    for (int t = 0; t < 3; ++t) {
-        c[t] = cell_of(xs[(poff + j) * 3 + t], n[t], &u[t], &bad);
-    }
-    const int nbox[3] = {nb0, X.nbox[1], X.nbox[2]};
-    const int key = nb0 ? box_key(c, n, nbox) : sort_key(c, T, X.ntx, n[0], block_w(M2));
-    long long pos = ipos[poff + j];  // (the rank in its cell, unless fixed)
-    if (!fixed) {
-        pos += poff + cell_start[X.key_off + key];
-        perm[pos] = (int)(poff + j);
-        ipos[poff + j] = (int)pos;
-    }
+    const long long pos = place_point<M2>(j, xs, X, T, cell_start, perm, ipos, fixed, c, u);
 
     int rot = (c[0] - m + 1) % M2;
     if (rot < 0) rot += M2;
@@ -302,8 +320,7 @@ __device__ inline long long scatter_point(long long j, const double *__restrict_
             }
         }
     }
-    const int c12 = (c[1] << kBoxCellBits) | c[2];
-    head = make_int2(c[0], nb0 ? c12 : (c12 << kLineBits) | (c[2] & (block_w(M2) - 1)));
+    head = point_head<M2>(c, nb0 != 0);
     return pos;
 }
 
@@ -331,6 +348,72 @@ __global__ __launch_bounds__(256) void k_bin_scatter(const double *__restrict__ 
     store_block<NW * sizeof(R)>(rp, w);
     *reinterpret_cast<int2 *>(rp + rec_off_pz(M2, sizeof(R))) = head;
     if constexpr (GRAD) store_block<NW * sizeof(R)>(rp + rec_prefix(M2, sizeof(R)), dw);
+}
+
+// Gradient records in float64, whose derivatives are evaluated: lane <-> table
+// entry (dim, slot) of the wavefront's 16 points, consecutive lanes on
+// consecutive words of a record.  A lane of its own for every entry keeps the
+// long serial evaluations apart and the tables out of scratch memory.  Bound by
+// the evaluations.  Measured against one thread per point, 2m = 16: 165,888
+// points 155 -> 64 us, 200,000 points 192 -> 74 us, 393,216 points 300 -> 131 us
+// (of these 23, 23 and 40 us for the unused values beside the derivatives and
+// for divisions by the constants of the series).
+constexpr int kTablePoints = 16;
+template <int M2>
+__global__ __launch_bounds__(256) void k_bin_tables(const double *__restrict__ xs, const Xform *__restrict__ xfs, int B,
+                                                    int T, const int *__restrict__ cell_start, int *__restrict__ perm,
+                                                    int *__restrict__ ipos, unsigned char *__restrict__ rec,
+                                                    size_t rec_bytes, WindowParams wp, const double *__restrict__ poly,
+                                                    int fixed)
+{
+    constexpr int m = M2 / 2, NC = kPolyF64, NW = 3 * M2;
+    static_assert(kTablePoints * 4 == 64, "a workgroup of four wavefronts takes the 64 points of one unit");
+    __shared__ double coef[M2 * NC], su[4][kTablePoints][3];
+    __shared__ int spos[4][kTablePoints], srot[4][kTablePoints];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const Xform &X = xfs[xform_of(xfs, B, &Xform::wave0, (int)blockIdx.x)];
+    const long long j0 = (long long)((int)blockIdx.x - X.wave0) * 64 + wave * kTablePoints;
+    const bool box = X.nbox[0] > 0;
+    if (poly)
+        for (int i = threadIdx.x; i < M2 * NC; i += 256) coef[i] = poly[i];
+    if (lane < kTablePoints && j0 + lane < X.M) {
+        int c[3];
+        double u[3];
+        const long long pos = place_point<M2>(j0 + lane, xs, X, T, cell_start, perm, ipos, fixed, c, u);
+        *reinterpret_cast<int2 *>(rec + pos * rec_bytes + rec_off_pz(M2, sizeof(double))) = point_head<M2>(c, box);
+        // slot = (tap + rotation) mod 2m: dim 0 by plane, dim 2 by the line in
+        // its block (line method)
+        int rot = (c[0] - m + 1) % M2;
+        rot += rot < 0 ? M2 : 0;
+        spos[wave][lane] = (int)pos;
+        srot[wave][lane] = box ? 0 : rot | (c[2] & (block_w(M2) - 1)) << 16;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) su[wave][lane][t] = u[t];
+    }
+    __syncthreads();
+    const int np = (int)min((long long)kTablePoints, X.M - j0);
+    for (int i = lane; i < np * NW; i += 64) {
+        const int p = i / NW, e = i - p * NW, dim = e / M2;
+        int t = e - dim * M2 - (dim == 0 ? srot[wave][p] & 0xffff : dim == 2 ? srot[wave][p] >> 16 : 0);
+        t += t < 0 ? M2 : 0;
+        const double u = su[wave][p][dim];
+        double w = 0.0, d = 0.0;
+        if (dim < X.flat) {
+            w = t == m - 1 ? 1.0 : 0.0;
+        } else {
+            const double dist = u + (double)(m - 1 - t);
+            if (poly) {
+                win_eval(wp, dist, nullptr, &d);
+                w = horner<NC>(coef + t * NC, 2.0 * u - 1.0);
+            } else {
+                win_eval(wp, dist, &w, &d);
+            }
+            d *= (double)X.n[dim];
+        }
+        unsigned char *rp = rec + (size_t)spos[wave][p] * rec_bytes;
+        reinterpret_cast<double *>(rp)[e] = w;
+        reinterpret_cast<double *>(rp + rec_prefix(M2, sizeof(double)))[e] = d;
+    }
 }
 
 // Records without derivative tables: each wavefront assembles its 64
@@ -556,9 +639,14 @@ static void scatter_m(const double *xs, const Xform *dxf, int B, int nwaves, int
                            rec_bytes, wp, poly, fixed ? 1 : 0);
         return;
     }
-    auto kg = k_bin_scatter<R, M2, true>;
-    hipLaunchKernelGGL(kg, dim3((unsigned)((nwaves + 3) / 4)), dim3(256), 0, s, xs, dxf, B, nwaves, T, cell_start, perm,
-                       ipos, rec, rec_bytes, wp, poly, fixed ? 1 : 0);
+    if constexpr (sizeof(R) == 8) {
+        hipLaunchKernelGGL(k_bin_tables<M2>, dim3((unsigned)nwaves), dim3(256), 0, s, xs, dxf, B, T, cell_start, perm, ipos,
+                           rec, rec_bytes, wp, poly, fixed ? 1 : 0);
+        return;
+    } else {
+        hipLaunchKernelGGL((k_bin_scatter<R, M2, true>), dim3((unsigned)((nwaves + 3) / 4)), dim3(256), 0, s, xs, dxf, B, nwaves, T,
+                           cell_start, perm, ipos, rec, rec_bytes, wp, poly, fixed ? 1 : 0);
+    }
 }
 
 template <typename R>

@@ -46,6 +46,7 @@ HPNFFT_HD double sinhc_d(double x)
         // sum_{k>=1} x^(2k-2) * 2k / (2k+1)!
         const double z2 = x * x;
         double term = 1.0, acc = 0.0, fact = 6.0;
+#pragma unroll  // (the divisions are of constants then)
         for (int k = 1; k <= 10; ++k) {
             acc += term * (2.0 * k) / fact;
             term *= z2;
@@ -163,26 +164,27 @@ HPNFFT_HD void bspline_eval(int p, double t, double *val, double *der)
 
 HPNFFT_HD double sincd(double x) { return fabs(x) < 1e-8 ? 1.0 - x * x / 6.0 : sin(x) / x; }
 
-// Normalised window and its derivative d phi / dt at distance t (0 beyond m).
+// Normalised window and its derivative d phi / dt at distance t (0 beyond m);
+// either may be null.
 HPNFFT_HD void win_eval(const WindowParams &w, double t, double *phi, double *dphi)
 {
     const int m = w.m;
     if (fabs(t) > (double)m * (1.0 + 1e-12)) {
-        *phi = 0.0;
+        if (phi) *phi = 0.0;
         if (dphi) *dphi = 0.0;
         return;
     }
     switch (w.kind) {
     case W_GAUSSIAN: {
         const double v = exp(-t * t / w.b);
-        *phi = v;
+        if (phi) *phi = v;
         if (dphi) *dphi = -2.0 * t / w.b * v;
         return;
     }
     case W_BSPLINE: {
         double v, d;
         bspline_eval(2 * m, t, &v, &d);
-        *phi = v * w.inv_peak;
+        if (phi) *phi = v * w.inv_peak;
         if (dphi) *dphi = d * w.inv_peak;
         return;
     }
@@ -191,7 +193,7 @@ HPNFFT_HD void win_eval(const WindowParams &w, double t, double *phi, double *dp
         const double sc = sincd(x);
         double p1 = 1.0;  // sinc^(2m - 1)
         for (int i = 0; i < 2 * m - 1; ++i) p1 *= sc;
-        *phi = p1 * sc;
+        if (phi) *phi = p1 * sc;
         if (dphi) {
             // d/dx sinc(x) = (x cos x - sin x) / x^2, ~ -x/3 near 0
             const double ds = fabs(x) < 1e-4 ? -x / 3.0 : (x * cos(x) - sin(x)) / (x * x);
@@ -200,7 +202,7 @@ HPNFFT_HD void win_eval(const WindowParams &w, double t, double *phi, double *dp
         return;
     }
     default:
-        *phi = kb_phi(t, m, w.b, w.inv_peak);
+        if (phi) *phi = kb_phi(t, m, w.b, w.inv_peak);
         if (dphi) *dphi = kb_dphi(t, m, w.b, w.inv_peak);
         return;
     }
