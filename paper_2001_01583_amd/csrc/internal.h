@@ -138,11 +138,11 @@ __host__ __device__ constexpr size_t rec_off_xr(int M2, size_t R) { return 3 * M
 // points of 8 lines instead of one.  Other windows use single lines.
 __host__ __device__ constexpr int block_w(int M2) { return M2 == 8 ? 8 : 1; }
 
-// Ring sweep of the 2m = 8 spread (ring.h): tiles of kRingT x kRingT lines,
-// phases of kRingZp planes, slabs of a multiple of 2m planes.  The records store the
+// Ring sweeps of 2m = 8 plans (ring.h): tiles of kRingT x kRingT lines, phases
+// of kRingZp planes, slabs of a multiple of 2m planes.  The records store the
 // dim-0 weights rotated by the absolute plane (mod 2m) while the ring counts
-// planes from the slab start through the periodic images, so the plan also
-// requires n0 to be a multiple of 2m.
+// planes from the slab start through the periodic images; where n0 is no
+// multiple of 2m the images' records are turned as they are staged.
 constexpr int kRingT = 8;
 constexpr int kRingZp = 8;
 __host__ __device__ constexpr bool ring_tiling(int M2, int T, int Zs)

@@ -414,9 +414,22 @@ void choose_methods(hpnfft_plan_s *p)
 // line sweeps), 16 cells.
 Tiling box_tiling(const hpnfft_plan_s *p, Tiling t) { return p->boxes ? t : Tiling{16, 16, 512}; }
 
-// Whether the line spread of this plan runs as the ring sweep: a 2m = 8
-// plan with a ring tiling whose line-method transforms all have n0 a
-// multiple of 2m (HPNFFT_RING=0 turns the ring sweep off).
+// Whether every line-method grid of a 2m = 8 plan has n0 a multiple of 8.
+bool whole_groups(const hpnfft_plan_s *p)
+{
+    for (size_t b = 0; b < p->hx.size(); ++b)
+        if (!p->tbox[b] && p->hx[b].n[0] % 8) return false;
+    return true;
+}
+
+// Whether the line sweeps of this plan run as ring sweeps: a 2m = 8 plan with a
+// ring tiling whose line-method grids have n0 a multiple of 8 or at least 16
+// (HPNFFT_RING=0 turns them off).  Against the staged sweeps where n0 is no
+// multiple of 8: set_points, adjoint and forward at N = 30 x 20 x 112, 124,905
+// points, float32 252 -> 194 us; adjoint and forward at 90 x 98 x 100, 10^6
+// clustered points, float32 1380 -> 734 us.  Gradient plans with such grids
+// keep the staged spread: their tiling sets the order of the float32
+// gradients' sums.
 bool use_ring(const hpnfft_plan_s *p, const Tiling &t)
 {
     static int on = -1;
@@ -425,8 +438,10 @@ bool use_ring(const hpnfft_plan_s *p, const Tiling &t)
         on = (e && e[0] == '0') ? 0 : 1;
     }
     if (!on || !ring_tiling(p->M2(), t.T, t.Zs)) return false;
+    if (whole_groups(p)) return true;
+    if (p->grad()) return false;
     for (size_t b = 0; b < p->hx.size(); ++b)
-        if (!p->tbox[b] && p->hx[b].n[0] % p->M2()) return false;
+        if (!p->tbox[b] && p->hx[b].n[0] % 8 && p->hx[b].n[0] < 16) return false;
     return true;
 }
 
@@ -457,7 +472,7 @@ bool tiling_fits(const hpnfft_plan_s *p, Tiling t)
     }
     if (t.T % block_w(p->M2())) return false;  // whole blocks of lines per tile row
     bool comp = p->prec == HPNFFT_F32;
-    if (!use_ring(p, t) && !lds_fit(t.T, t.Zs, p->M2(), p->rbytes(), 0, comp).cap) return false;
+    if (!(use_ring(p, t) && whole_groups(p)) && !lds_fit(t.T, t.Zs, p->M2(), p->rbytes(), 0, comp).cap) return false;
     if (!lds_fit(t.T, t.Zs, p->M2(), p->rbytes(), 1, false).cap) return false;
     if (p->grad() && !lds_fit(t.T, t.Zs, p->M2(), p->rbytes(), 2, false).cap) return false;
     return true;
@@ -490,8 +505,10 @@ Tiling default_tiling(const hpnfft_plan_s *p)
     // per cell (32 planes; float32 0.215 + 0.152 ms, float64 0.303 + 0.259
     // ms at N = 64^3, M = 2^20)
     if (block_w(M2) > 1) {
-        const Tiling r{kRingT, 32, 512};
-        if (use_ring(p, r) && tiling_fits(p, r)) return r;
+        for (int Zs : {32, 16, 8}) {
+            const Tiling r{kRingT, Zs, 512};
+            if (use_ring(p, r) && tiling_fits(p, r)) return r;
+        }
     }
     // 2m = 10 .. 16: the slab spread runs fastest with tiles of 8 x 8 lines
     // and 8 planes, which leave two workgroups to a compute unit (N = 64^3, M

@@ -56,14 +56,16 @@ constexpr int kRingWaves = kRingThreads / 64;
 // worked off in chunks of CH points; no chunk crosses from run to run.
 struct RingRun {
     int pa, na, pb, nb;  // first point and length of each run
+    int ua, ub;          // planes by which the run's image lies past its points
     template <int CH> __device__ inline int chunks() const { return (na + CH - 1) / CH + (nb + CH - 1) / CH; }
-    template <int CH> __device__ inline void chunk(int k, int &first, int &cnt) const
+    template <int CH> __device__ inline void chunk(int k, int &first, int &cnt, int &u) const
     {
         const int ka = (na + CH - 1) / CH;
         const bool in_a = k < ka;
         const int o = CH * (in_a ? k : k - ka);
         first = (in_a ? pa : pb) + o;
         cnt = min(CH, (in_a ? na : nb) - o);
+        u = in_a ? ua : ub;
     }
 };
 // c: grid plane of the group's first base plane (its point planes are c .. c
@@ -71,11 +73,12 @@ struct RingRun {
 __device__ inline RingRun ring_run(const int *cs, int c, int len, int n0)
 {
     constexpr int BW = 8;
-    c += c < 0 ? n0 : 0;
-    c -= c >= n0 ? n0 : 0;
+    RingRun r;
+    r.ua = c < 0 ? -n0 : (c >= n0 ? n0 : 0);
+    r.ub = r.ua + n0;
+    c -= r.ua;
     const int e1 = min(c + len, n0), e2 = max(c + len - n0, 0);
     const cptr<int> k = as_const(cs);
-    RingRun r;
     r.pa = k[c * BW];
     r.na = k[e1 * BW] - r.pa;
     r.pb = k[0];
@@ -128,6 +131,21 @@ template <typename R, int CH, bool VALUES> struct RingStage {
             if (lane < CH) *reinterpret_cast<V2 *>(st + lane * RB + F) = value;
     }
 };
+
+// Staged records of a periodic image u planes further, where u is no multiple
+// of 8: plane and dim-0 slot order of the image (slot s: plane = s mod 8).
+template <typename R>
+__device__ inline void ring_image(unsigned char *st, int cnt, int u, int lane)
+{
+    if (lane >= cnt) return;
+    unsigned char *rp = st + lane * (int)rec_prefix(8, sizeof(R));
+    R *ps = reinterpret_cast<R *>(rp), w[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) w[s] = ps[s];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) ps[(s + u) & 7] = w[s];
+    *reinterpret_cast<int *>(rp + rec_off_pz(8, sizeof(R))) += u;
+}
 
 constexpr int kRingChunk = 36;  // points a wavefront of the spread stages at a time
 
@@ -199,20 +217,20 @@ __global__ __launch_bounds__(kRingThreads, ring_spread_waves<R>()) void k_spread
         // anything, from the window images that start before the slab.
         auto group_run = [&](int g) __attribute__((always_inline)) {
             const int first = g < 0 ? -(M2 - 1) : kRingZp * g;
-            RingRun r = ring_run(cs, first + (m - 1) + z0, kRingZp * (g + 1) - first, n0);
+            RingRun r = ring_run(cs, first + (m - 1) + z0, min(kRingZp * (g + 1), zs) - first, n0);
             if (flat && g >= 0) r.na = r.nb = 0;
             return r;
         };
-        const int ng = zs / kRingZp;
+        const int ng = (zs + kRingZp - 1) / kRingZp;
         RingRun rn{};
         Stage sg;
         // loads chunk k of run r, or the first chunk of the next group's run
         auto load_next = [&](const RingRun &r, int k) __attribute__((always_inline)) {
             const bool same = k < r.chunks<kRingChunk>();
             if (!same && sub >= rn.chunks<kRingChunk>()) return;
-            int first, cnt;
-            if (same) r.chunk<kRingChunk>(k, first, cnt);
-            else rn.chunk<kRingChunk>(sub, first, cnt);
+            int first, cnt, u;
+            if (same) r.chunk<kRingChunk>(k, first, cnt, u);
+            else rn.chunk<kRingChunk>(sub, first, cnt, u);
             sg.load(first, cnt, recb, rbytes, fsb, lane);
         };
         if (mine) {
@@ -227,9 +245,10 @@ __global__ __launch_bounds__(kRingThreads, ring_spread_waves<R>()) void k_spread
                 const int nch = r.chunks<kRingChunk>();
                 if (sub >= nch) load_next(r, nch);
                 for (int ch = sub; ch < nch; ch += wpr) {
-                    int first, cnt;
-                    r.chunk<kRingChunk>(ch, first, cnt);
+                    int first, cnt, u;
+                    r.chunk<kRingChunk>(ch, first, cnt, u);
                     sg.store(st, lane);
+                    if (u & 7) ring_image<R>(st, cnt, u, lane);
                     load_next(r, ch + wpr);
                     for (int c = 0; c < cnt; c += 4) {
                         const int lastp = min(cnt - 1 - c, 3);
@@ -238,7 +257,7 @@ __global__ __launch_bounds__(kRingThreads, ring_spread_waves<R>()) void k_spread
                         const V4 w0a = reinterpret_cast<const V4 *>(rp)[0], w0b = reinterpret_cast<const V4 *>(rp)[1];
                         const int2 h = *reinterpret_cast<const int2 *>(rp + OFF_PZ);
                         const R f1 = ps[3 * M2 + ac] * ps[M2 + ay], w2 = ps[2 * M2 + (col & 7)];
-                        // first tap plane in its group (slabs and n0 are multiples of 8)
+                        // first tap plane in its group (slabs begin at multiples of 8)
                         const int db = (h.x - (m - 1)) & 7;
                         int dmin = uni(db), dmax = __builtin_amdgcn_readlane(db, 16 * lastp);
                         if (flat) {  // slot 0 of the next group only
@@ -265,7 +284,7 @@ __global__ __launch_bounds__(kRingThreads, ring_spread_waves<R>()) void k_spread
                 __syncthreads();
                 const size_t pstride = (size_t)n1 * n2;
                 const gptr<R> grid = as_global(reinterpret_cast<R *>(X->grid));
-                const int zb = z0 + kRingZp * g;
+                const int zb = z0 + kRingZp * g, zn = zs - kRingZp * g;  // (the grid's last group may hold fewer planes)
                 auto cell = [&](int z, int y, int x, int c) __attribute__((always_inline)) {
                     int gy = Y0 + y - (m - 1), gx = X0 + x - (m - 1);
                     gy += gy < 0 ? n1 : 0;
@@ -307,7 +326,7 @@ __global__ __launch_bounds__(kRingThreads, ring_spread_waves<R>()) void k_spread
                                     if (y >= 0 && y < 8) out[y] += (double)v[k];
                                 }
                             }
-                        if (x < kRingP) {
+                        if (x < kRingP && z < zn) {
 #pragma unroll
                             for (int k = 0; k < 8; ++k)
                                 if (r0 + k < kRingP) add(z, r0 + k, x, c, out[k]);
@@ -322,7 +341,7 @@ __global__ __launch_bounds__(kRingThreads, ring_spread_waves<R>()) void k_spread
                     for (int i = t; i < kRingZp * kRingP * 32; i += kRingThreads) {
                         const int c = i & 1, x = (i >> 1) & 15, zy = i >> 5;
                         const int z = zy / kRingP, y = zy - z * kRingP;
-                        if (x >= kRingP) continue;
+                        if (x >= kRingP || z >= zn) continue;
                         double v = 0.0;
                         for (int w = 0; w < nrow * wpr; ++w) {
                             const int yy = y - (W.lb + w / wpr);
@@ -445,20 +464,20 @@ __global__ __launch_bounds__(kRingThreads, sizeof(R) == 4 ? 6 : 4) void k_interp
         using Stage = RingStage<R, CH, false>;
         unsigned char *st = reinterpret_cast<unsigned char *>(ring + 2 * kRingZp * PLANE) + wave * CH * Stage::RB;
 
-        const int ng = zs / kRingZp;
+        const int ng = (zs + kRingZp - 1) / kRingZp;
         RingRun rn{};
         Stage sg;
         auto load_next = [&](const RingRun &r, int k) __attribute__((always_inline)) {
             const bool same = k < r.chunks<CH>();
             if (!same && sub >= rn.chunks<CH>()) return;
-            int first, cnt;
-            if (same) r.chunk<CH>(k, first, cnt);
-            else rn.chunk<CH>(sub, first, cnt);
+            int first, cnt, u;
+            if (same) r.chunk<CH>(k, first, cnt, u);
+            else rn.chunk<CH>(sub, first, cnt, u);
             sg.load(first, cnt, recb, rbytes, nullptr, lane);
         };
         planes_fetch(0);
         if (mine) {
-            rn = ring_run(cs, (m - 1) + z0, kRingZp, n0);
+            rn = ring_run(cs, (m - 1) + z0, min(kRingZp, zs), n0);
             load_next(rn, sub);
         }
         planes_store(0);
@@ -470,16 +489,17 @@ __global__ __launch_bounds__(kRingThreads, sizeof(R) == 4 ? 6 : 4) void k_interp
             if (mine) {
                 const RingRun r = rn;
                 rn.na = rn.nb = 0;
-                if (g + 1 < ng) rn = ring_run(cs, kRingZp * (g + 1) + (m - 1) + z0, kRingZp, n0);
+                if (g + 1 < ng) rn = ring_run(cs, kRingZp * (g + 1) + (m - 1) + z0, min(kRingZp, zs - kRingZp * (g + 1)), n0);
                 const int nch = r.chunks<CH>();
                 if (sub >= nch) load_next(r, nch);
                 // planes 8 g + t: t < 8 in one half of the ring, t >= 8 in the other
                 const R *ra = ring + (li + ay) * 2 * PITCH + ac * PITCH + k4;
                 const R *rlo = ra + (g & 1) * kRingZp * PLANE, *rhi = ra + ((g & 1) ^ 1) * kRingZp * PLANE;
                 for (int ch = sub; ch < nch; ch += wpr) {
-                    int first, cnt;
-                    r.chunk<CH>(ch, first, cnt);
+                    int first, cnt, u;
+                    r.chunk<CH>(ch, first, cnt, u);
                     sg.store(st, lane);
+                    if (u & 7) ring_image<R>(st, cnt, u, lane);
                     load_next(r, ch + wpr);
                   for (int c = 0; c < cnt; c += 16) {
                     const int lastp = min(cnt - 1 - c, 15);
