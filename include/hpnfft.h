@@ -128,16 +128,16 @@ int hpnfft_set_stream(hpnfft_plan plan, void *hip_stream);
 /* Sweep method of the spread and the interpolation (the Spreading and
  * Interpolating steps of Section 3).  Must be called before
  * hpnfft_set_workspace; resets the tiling to the method's default.
- *   HPNFFT_METHOD_LINES  points sorted into runs along dim 0 and swept with
- *                        register windows; LDS tiles with a halo of 2m - 1
- *                        cells flushed with global atomic adds (dense
- *                        point sets)
- *   HPNFFT_METHOD_BOXES  every workgroup owns one output box (>= m cells per
- *                        edge) and takes the points of the 27 boxes around
- *                        it; the grid is written once, with plain stores
+ *   HPNFFT_METHOD_LINES  points sorted into runs along dim 0 and swept by
+ *                        tiles of lines; tiles with a halo of 2m - 1 cells
+ *                        flushed with global atomic adds (dense point sets)
+ *   HPNFFT_METHOD_BOXES  the spread's workgroups own one output box of 16^3
+ *                        cells each and take the points of the bins around
+ *                        it; the grid is written once, with plain stores;
+ *                        the interpolation gathers each point's window
  *                        (sparse point sets)
  *   HPNFFT_METHOD_AUTO   (the default) per transform: boxes below 0.1
- *                        (float64) or 0.05 (float32) points per grid cell
+ *                        (float64) or 0.02 (float32) points per grid cell
  *                        (environment variable HPNFFT_BOX_DENSITY overrides),
  *                        so a batch may mix the two (its tiling then sets the
  *                        line sweeps; its box transforms use 16-cell boxes)
@@ -153,20 +153,22 @@ int hpnfft_get_method(hpnfft_plan plan, int *method);
 /* Spread/interpolation tiling: tile edge in the two fastest grid dimensions
  * (cells, 4..32), slab depth along the slowest dimension (cells, 2..64) and
  * threads per workgroup (multiple of 64, <= 1024).  Pass 0 to keep a value.
- * With the box method, tile and slab are the target box edges (>= m) in
- * dims 1, 2 and in dim 0; threads is not used (512).
+ * With the box method, tile and slab are the edges (>= m) of the boxes of
+ * bins in dims 1, 2 and in dim 0 (of the output boxes in deterministic plans);
+ * threads is not used (512).
  * Must be called before hpnfft_set_workspace.  EINVAL if the tile does not
  * fit the 160 KiB local data share, or if 2m = 8 and the tile edge is not a
  * multiple of 8 (those plans sort points in blocks of 8 lines).
  * With 2m = 8, a tile edge of 8 and a slab depth that is a multiple of 8
- * (the default: 8, 32), and every line-method grid's n0 a multiple of 8, the
- * spread and the interpolation run as ring sweeps (one wavefront per block
- * of 8 lines through the whole slab; environment variable HPNFFT_RING=0
- * selects the staged sweeps instead); threads is then 512 whatever is
- * passed.  With 2m = 16 and every line-method grid's n0 a multiple of 16,
- * the forward's interpolation runs by groups of lines over 64-plane slabs
- * whatever the tiling (environment variable HPNFFT_LINES=0 selects the
- * staged sweep); the spread keeps the tiling. */
+ * (the default: 8, 32), and every line-method grid's n0 a multiple of 8 or at
+ * least 16 (gradient plans: a multiple of 8), the spread and the interpolation
+ * run as ring sweeps (one wavefront per block of 8 lines through the whole
+ * slab; environment variable HPNFFT_RING=0 selects the staged sweeps
+ * instead); threads is then 512 whatever is passed.  With 2m = 10 .. 16 (the
+ * default: 8, 8, or 4, 8 for small grids) the spread keeps the tiling, and
+ * the interpolation runs by batches of points on a line whatever the tiling
+ * (environment variable HPNFFT_LINES=0 selects the staged sweep, and the
+ * gather for gradients). */
 int hpnfft_set_tiles(hpnfft_plan plan, int tile, int slab, int threads);
 int hpnfft_get_tiles(hpnfft_plan plan, int *tile, int *slab, int *threads);
 

@@ -10,10 +10,9 @@
 //     one after the other, in sorted order.  Within a point every lane owns
 //     distinct cells, so the LDS updates are plain read-modify-writes (float32:
 //     the compensated (sum, error) pair, TwoSum); the box is stored once.
-//   * Interpolation: one wavefront owns one point.  Its lanes take the tap
-//     rows of the point's window, read the grid cells directly (L2-cached),
-//     and the lane partials are summed by a fixed butterfly; the point's
-//     outputs are plain stores.
+//   * Interpolation: the gather (k_gather.hip), one wavefront per point: its
+//     lanes take the tap rows of the point's window, read the grid cells
+//     directly, and sum in a fixed order; the outputs are plain stores.
 // The FFT passes and the gather / scatter kernels have no atomics.
 #include <hipcub/hipcub.hpp>
 

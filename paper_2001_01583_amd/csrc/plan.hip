@@ -361,17 +361,22 @@ long long box_max_cells(const hpnfft_plan_s *p, Tiling t)
     return best;
 }
 
-// Method in use: the box method below a density of points per grid cell
-// (or when requested).  Its float64 taps are single native LDS atomic adds;
-// float32 taps need a compensated compare-and-swap each (gfx950's LDS
-// float32 atomic add runs at 0.33 lanes per clock per compute unit against
-// 7.6 for float64 and 3.5 for the 64-bit swap), so float32 switches later.
-// Measured on MI355X: at 0.5 points per cell the line sweeps are 3.5-10x
-// faster; at 0.01 (the 24^3-cell Ewald lattice on a 256^3 grid) the boxes
-// are 2.2x (float64) and 1.3x (float32) faster.  The 256-transform float32
-// batch (0.0001 - 4 points per cell per transform) runs fastest with the
-// float32 switch at 0.02 now that its dense transforms take the 2m = 8 ring
-// sweeps (25.05 ms; 25.8 at 0.05, 26.0 at 0.01, 27.2 at 0.005).
+// Method in use: the box method below a density of points per grid cell (or
+// when requested).  Its spread and its gathering interpolation take time per
+// point, the line sweeps also per tile and plane.  Measured (MI355X,
+// set_points + adjoint + forward, boxes against lines, us):
+//   float64, 2m = 16, N = 64^3: 597 / 791 at 0.04, 951 / 910 at 0.07, 1303 /
+//   1005 at 0.1; N = 108^3 the same crossing (4059 / 4043 at 0.07)
+//   float64, 2m = 12: 768 / 807 at 0.1 (64^3), 3542 / 3723 (108^3); 2m = 8: 383 /
+//   400 and 1684 / 1625 at 0.1
+//   float32, 2m = 8, N = 64^3: 153 / 255 at 0.02, 224 / 275 at 0.05, 342 / 293 at
+//   0.1; but in a batch, whose line sweeps fill the chip together, the switch
+//   at 0.02 is the fastest: 48 transforms 3364 us, 3628 at 0.05, 3804 at 0.08
+// A grid with fewer output boxes than compute units leaves some idle: at 32^3
+// (64 boxes) the lines win from 0.035 on with 2m = 16 (234 / 218 at 0.04) and
+// from 0.05 with 2m = 12 (209 / 197 at 0.055).  The switch stays at one density
+// per precision all the same: a tiling that a program sets is one of boxes or
+// of lines, and is accepted for the method that its density has selected.
 constexpr double kBoxDensityF64 = 0.1;
 constexpr double kBoxDensityF32 = 0.02;
 // The method of every transform (a batch may mix them: sparse transforms
@@ -466,7 +471,8 @@ bool tiling_fits(const hpnfft_plan_s *p, Tiling t)
         // box edges (dims 1, 2: T; dim 0: Zs) of at least m cells
         const Tiling bt = box_tiling(p, t);
         if (bt.T < p->m || bt.Zs < p->m) return false;
-        // the box tile in LDS beside the run lists (12 KiB of static LDS)
+        // 16 bytes per cell of a box (the deterministic spread's tile) beside
+        // run lists, in LDS
         if (box_max_cells(p, bt) * 16 + 12 * 1024 > (long long)kLdsLimit) return false;
         if (p->boxes) return true;
     }
@@ -478,8 +484,8 @@ bool tiling_fits(const hpnfft_plan_s *p, Tiling t)
     return true;
 }
 
-// Default tiling.  Measured on MI355X at 0.5 points per grid cell: single-
-// line sweeps run fastest with slabs of 16 planes and tiles whose LDS
+// Default tiling.  Measured on MI355X at 0.5 points per grid cell: staged
+// single-line sweeps run fastest with slabs of 16 planes and tiles whose LDS
 // footprint side P = T + 2m - 1 is about 20-21 cells (float64 m = 8: T = 6);
 // larger tiles cut the halo traffic but leave too little LDS for staging
 // points, smaller ones re-read more halo.  Blocked sweeps (2m = 8) take one
@@ -495,15 +501,14 @@ Tiling default_tiling(const hpnfft_plan_s *p)
         if (tiling_fits(p, Tiling{Tb, Tb, 64})) return Tiling{Tb, Tb, 64};
     }
     if (p->boxes) {
-        // boxes of 16 cells per edge (16 KiB of (sum, error) or float64 pairs
-        // per 1024 cells: 64 KiB, two workgroups per compute unit)
+        // boxes of 16 cells per edge: they set the bins; the spread's own
+        // boxes have 16 cells whatever the tiling
         for (int Tb : {16, 12, 8})
             if (tiling_fits(p, Tiling{Tb, Tb, 512})) return Tiling{Tb, Tb, 512};
     }
-    // 2m = 8: the ring sweeps (tiles of 8 x 8 lines) with the slab depth
-    // that measured fastest for spread plus interpolation at 0.5 points
-    // per cell (32 planes; float32 0.215 + 0.152 ms, float64 0.303 + 0.259
-    // ms at N = 64^3, M = 2^20)
+    // 2m = 8: the ring sweeps (tiles of 8 x 8 lines) with slabs of 32 planes
+    // (N = 64^3, M = 2^20: float32 spread 135 us, interpolation 102 us), or
+    // the deepest ones that fit
     if (block_w(M2) > 1) {
         for (int Zs : {32, 16, 8}) {
             const Tiling r{kRingT, Zs, 512};

@@ -1,5 +1,8 @@
-// Spreading (the Spreading step of Algorithm 2, Section 3) and interpolation
-// (the Interpolating step of Algorithm 5) on gfx950.
+// Staged sweeps: spreading (the Spreading step of Algorithm 2, Section 3) and
+// interpolation (the Interpolating step of Algorithm 5) of line-method plans
+// whose window no other kernel serves: 2m below 8, above 16, and 2m = 8 with
+// tilings that the ring sweeps (ring.h) do not take.  (2m = 10 .. 16: slab.h and
+// lines.h; gradients: k_gather.hip and lines.h.)
 //
 // The paper assigns one thread per point and adds every window tap to the
 // grid with an atomic operation.  Here points are sorted into runs: a z-line
