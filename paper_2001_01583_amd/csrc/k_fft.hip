@@ -235,7 +235,8 @@ template <typename R> struct Pencils {
         const int ii = inner0 + p;
         return roll0[j] * roll1[ii / N2] * roll2[ii % N2];
     }
-    __host__ __device__ static inline int pad(int n) { return n + (n + 7) / 8; }
+    // LDS elements of a pencil, at most 9/8 n (see stage(): element i lies at i + i / 8)
+    __host__ __device__ static inline int pad(int n) { return n + n / 8; }
 };
 
 // One Stockham stage of radix RAD: inputs from global memory (FIRST) or LDS,

@@ -19,6 +19,8 @@ pytestmark = pytest.mark.gpu
 EDGES = [(2, 2, 4), (4, 8, 16), (32, 4, 8), (6, 10, 14), (18, 50, 14), (98, 6, 10), (12, 60, 56)]
 SIZES = [tuple(N) for e in EDGES for N in dict.fromkeys(itertools.islice(itertools.permutations(e), 0, 5, 2))]
 SIZES += [(100,), (14,), (30, 84)]
+# many pencils of 4 and of one element per workgroup, along rows and columns
+SIZES += [(32, 32, 2), (2, 2, 500), (2, 500), (500, 2)]
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32"])
