@@ -518,15 +518,19 @@ Tiling default_tiling(const hpnfft_plan_s *p)
     // 2m = 10 .. 16: the slab spread runs fastest with tiles of 8 x 8 lines
     // and 8 planes, which leave two workgroups to a compute unit (N = 64^3, M
     // = 2^20, 2m = 16, float64: 0.83 ms against 0.90 with 16 planes, 0.99
-    // with 6 x 6 lines and 16 planes, 1.10 with 4 x 4 and 8).  Grids with
-    // fewer such tiles than two per compute unit take 4 x 4 lines (32^3 grid,
-    // 4096 points: 28 us against 45 us).
+    // with 6 x 6 lines and 16 planes, 1.10 with 4 x 4 and 8).  Float64 grids
+    // with fewer such tiles than two per compute unit take 4 x 4 lines (32^3
+    // grid, 4096 points: 28 us against 45 us).  Not float32 ones: a cell of the
+    // grid receives one rounded sum per tile that reaches it, ((T + 2m - 1) /
+    // T)^2 of them, 18 instead of 6 at 2m = 12 (20,000 points, 40^3 grid, 2m =
+    // 12: error against 64 bits 2.8e-3 with 4 x 4 lines, 1.9e-3 with 8 x 8; 57
+    // and 59 us).
     if (M2 >= 10 && M2 <= 16) {
         long long tiles = 0;
         for (int b = 0; b < p->B; ++b)
             if (!p->tbox[b])
                 tiles += (long long)((p->hx[b].n[0] + 7) / 8) * ((p->hx[b].n[1] + 7) / 8) * ((p->hx[b].n[2] + 7) / 8);
-        const Tiling t{tiles < 2LL * p->cus ? 4 : 8, 8, 1024};
+        const Tiling t{p->prec == HPNFFT_F64 && tiles < 2LL * p->cus ? 4 : 8, 8, 1024};
         if (tiling_fits(p, t)) return t;
     }
     // blocked 2m = 8 sweeps: tiles of one block of lines per row fit best

@@ -13,9 +13,13 @@
 // goes through the points whose windows reach them (2m + 3 planes of the
 // line's sorted points, up to three runs with the periodic images) and adds
 // the planes to the slab's tile in LDS once: 512 native LDS float64 adds per
-// plane and line, however many points the line holds.  Float32 sums are added
-// up in the tile in float64 too (the LDS float32 add is 13 times slower) and
-// rounded once.  Then all threads add the tile to the grid.
+// plane and line.  Float32 sums are added up in the tile in float64 too (the
+// LDS float32 add is 13 times slower) and rounded once, and at most kSlabRun
+// points of a line are added up in float32 before they join the tile: a crowded
+// line's sums lost precision otherwise (400,000 points, half of them in 16
+// clusters, N = 32^3, 2m = 14: error against 64 bits 7.0e-7 with whole lines,
+// 3.2e-7 with runs of 64, 4.4e-7 for the staged sweep; both 0.33 ms).  Then all
+// threads add the tile to the grid.
 //
 // Loads run one batch ahead, across tasks: the run bounds of the next task
 // (six values, one per lane) are loaded while a task is worked off.
@@ -34,6 +38,7 @@
 namespace hpnfft {
 
 constexpr int kSlabQuad = 4;  // planes per task
+constexpr int kSlabRun = 64;  // points added up in float32 (a multiple of 4)
 __host__ __device__ constexpr size_t slab_lds(int T, int Zs, int M2)
 {
     return (size_t)Zs * (T + M2 - 1) * (T + M2 - 1) * 16;
@@ -172,6 +177,26 @@ __global__ __launch_bounds__(1024) void k_spread_slab(const Xform *__restrict__ 
             V4 re[Q], ie[Q];
 #pragma unroll
             for (int q = 0; q < Q; ++q) re[q] = ie[q] = V4{0, 0, 0, 0};
+            // the planes to the tile, and the accumulators cleared; the lane's
+            // rows of a result: y0 + YS k
+            constexpr int YS = sizeof(R) == 4 ? 1 : 4;
+            const int y0 = sizeof(R) == 4 ? 4 * p4 : p4;
+            double *cre = acc + (z - z0) * plane + (ly + y0) * P + lx + col, *cim = cre + im;
+            auto flush = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    if (z + q < z0 + zs) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            if (on && y0 + YS * k < M2) {
+                                atomicAdd(&cre[q * plane + YS * k * P], (double)re[q][k]);
+                                atomicAdd(&cim[q * plane + YS * k * P], (double)ie[q][k]);
+                            }
+                        }
+                    }
+                    re[q] = ie[q] = V4{0, 0, 0, 0};
+                }
+            };
             const int n = r.n;
             for (int i = 0; i < n; i += 4) {
                 const int last = min(n - 1 - i, 3);
@@ -199,22 +224,9 @@ __global__ __launch_bounds__(1024) void k_spread_slab(const Xform *__restrict__ 
                     re[q] = Mat<R>::mul(wr[q], b, re[q]);
                     ie[q] = Mat<R>::mul(wi[q], b, ie[q]);
                 }
+                if (sizeof(R) == 4 && i % kSlabRun == kSlabRun - 4 && i + 4 < n) flush();
             }
-            // the lane's rows of a result: y0 + YS k
-            constexpr int YS = sizeof(R) == 4 ? 1 : 4;
-            const int y0 = sizeof(R) == 4 ? 4 * p4 : p4;
-            double *cre = acc + (z - z0) * plane + (ly + y0) * P + lx + col, *cim = cre + im;
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                if (z + q >= z0 + zs) break;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    if (on && y0 + YS * k < M2) {
-                        atomicAdd(&cre[q * plane + YS * k * P], (double)re[q][k]);
-                        atomicAdd(&cim[q * plane + YS * k * P], (double)ie[q][k]);
-                    }
-                }
-            }
+            flush();
         }
         __syncthreads();
         // the tile to the grid; consecutive lanes add to consecutive reals
