@@ -103,6 +103,19 @@ struct Tiling {
     int ring = 0;      // spread by the ring sweep (set per launch by the plan)
 };
 
+// A launch of `groups` workgroups whose number grows with the problem.  HIP
+// refuses 2^32 threads and more per grid dimension, so long launches get several
+// rows: workgroup i is group_index(), and there may be more than `groups`.  Rows
+// are a multiple of kXcds long, so that the group's XCD stays i mod kXcds.
+inline dim3 launch_grid(long long groups, int threads)
+{
+    const long long most = 0xffffffffLL / threads / kXcds * kXcds, rows = (groups + most - 1) / most;
+    if (rows <= 1) return dim3((unsigned)groups);
+    const long long cols = ((groups + rows - 1) / rows + kXcds - 1) / kXcds * kXcds;
+    return dim3((unsigned)cols, (unsigned)rows);
+}
+__device__ inline long long group_index() { return (long long)blockIdx.y * gridDim.x + blockIdx.x; }
+
 __host__ __device__ constexpr size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
 
 // Pointers read from a descriptor in memory (the Xform fields) are generic to

@@ -79,8 +79,9 @@ __global__ __launch_bounds__(256) void k_bin_count(const XT *__restrict__ xin, c
                                                    int *__restrict__ counts, int *__restrict__ rank,
                                                    int *__restrict__ err, int *__restrict__ keys_out)
 {
-    const int w = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (w >= nwaves) return;
+    const long long gw = group_index() * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (gw >= nwaves) return;
+    const int w = (int)gw;
     const Xform &X = xfs[xform_of(xfs, B, &Xform::wave0, w0 + w)];
     const long long M = X.M, j = (long long)(w0 + w - X.wave0) * 64 + (threadIdx.x & 63);
     if (j >= M) return;
@@ -335,8 +336,9 @@ __global__ __launch_bounds__(256) void k_bin_scatter(const double *__restrict__ 
 {
     constexpr int NW = 3 * M2;
     static_assert((NW * sizeof(R)) % 8 == 0, "window block is a whole number of 8-byte units");
-    const int wv = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (wv >= nwaves) return;
+    const long long gw = group_index() * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (gw >= nwaves) return;
+    const int wv = (int)gw;
     const Xform &X = xfs[xform_of(xfs, B, &Xform::wave0, wv)];
     const long long j = (long long)(wv - X.wave0) * 64 + (threadIdx.x & 63);
     if (j >= X.M) return;
@@ -361,7 +363,7 @@ __global__ __launch_bounds__(256) void k_bin_scatter(const double *__restrict__ 
 constexpr int kTablePoints = 16;
 template <int M2>
 __global__ __launch_bounds__(256) void k_bin_tables(const double *__restrict__ xs, const Xform *__restrict__ xfs, int B,
-                                                    int T, const int *__restrict__ cell_start, int *__restrict__ perm,
+                                                    int nwaves, int T, const int *__restrict__ cell_start, int *__restrict__ perm,
                                                     int *__restrict__ ipos, unsigned char *__restrict__ rec,
                                                     size_t rec_bytes, WindowParams wp, const double *__restrict__ poly,
                                                     int fixed)
@@ -371,8 +373,10 @@ __global__ __launch_bounds__(256) void k_bin_tables(const double *__restrict__ x
     __shared__ double coef[M2 * NC], su[4][kTablePoints][3];
     __shared__ int spos[4][kTablePoints], srot[4][kTablePoints];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const Xform &X = xfs[xform_of(xfs, B, &Xform::wave0, (int)blockIdx.x)];
-    const long long j0 = (long long)((int)blockIdx.x - X.wave0) * 64 + wave * kTablePoints;
+    const long long unit = group_index();
+    if (unit >= nwaves) return;
+    const Xform &X = xfs[xform_of(xfs, B, &Xform::wave0, (int)unit)];
+    const long long j0 = (unit - X.wave0) * 64 + wave * kTablePoints;
     const bool box = X.nbox[0] > 0;
     if (poly)
         for (int i = threadIdx.x; i < M2 * NC; i += 256) coef[i] = poly[i];
@@ -423,7 +427,7 @@ __global__ __launch_bounds__(256) void k_bin_tables(const double *__restrict__ x
 // left zero (the sweeps that stage records fill it per call).
 template <typename R, int M2>
 __global__ __launch_bounds__(64) void k_bin_scatter_lds(const double *__restrict__ xs, const Xform *__restrict__ xfs,
-                                                        int B, int T, const int *__restrict__ cell_start,
+                                                        int B, int nwaves, int T, const int *__restrict__ cell_start,
                                                         int *__restrict__ perm, int *__restrict__ ipos,
                                                         unsigned char *__restrict__ rec, size_t rec_bytes,
                                                         WindowParams wp, const double *__restrict__ poly, int fixed)
@@ -435,8 +439,10 @@ __global__ __launch_bounds__(64) void k_bin_scatter_lds(const double *__restrict
     extern __shared__ uint4 sm[];  // 64 records, then 64 positions
     int *spos = reinterpret_cast<int *>(sm + 64 * U);
     const int lane = threadIdx.x;
-    const Xform &X = xfs[xform_of(xfs, B, &Xform::wave0, (int)blockIdx.x)];
-    const long long M = X.M, j0 = (long long)((int)blockIdx.x - X.wave0) * 64;
+    const long long unit = group_index();
+    if (unit >= nwaves) return;
+    const Xform &X = xfs[xform_of(xfs, B, &Xform::wave0, (int)unit)];
+    const long long M = X.M, j0 = (unit - X.wave0) * 64;
     const long long j = j0 + lane;
     if (j < M) {
         R w[NW];
@@ -617,12 +623,12 @@ hipError_t launch_bin_count(const double *x, const float *x32, const Xform *dxf,
                             double *xs, int *counts, int *rank, int *err, int *keys_out, hipStream_t s)
 {
     if (nwaves <= 0) return hipSuccess;
-    const unsigned nb = (unsigned)((nwaves + 3) / 4);
+    const dim3 grid = launch_grid(((long long)nwaves + 3) / 4, 256);
     if (x32)
-        hipLaunchKernelGGL(k_bin_count<float>, dim3(nb), dim3(256), 0, s, x32, dxf, B, w0, nwaves, T, BW, xs, counts, rank,
+        hipLaunchKernelGGL(k_bin_count<float>, grid, dim3(256), 0, s, x32, dxf, B, w0, nwaves, T, BW, xs, counts, rank,
                            err, keys_out);
     else
-        hipLaunchKernelGGL(k_bin_count<double>, dim3(nb), dim3(256), 0, s, x, dxf, B, w0, nwaves, T, BW, xs, counts, rank,
+        hipLaunchKernelGGL(k_bin_count<double>, grid, dim3(256), 0, s, x, dxf, B, w0, nwaves, T, BW, xs, counts, rank,
                            err, keys_out);
     return hipGetLastError();
 }
@@ -635,17 +641,17 @@ static void scatter_m(const double *xs, const Xform *dxf, int B, int nwaves, int
     if (!grad) {
         constexpr size_t lds = 64 * rec_prefix(M2, sizeof(R)) + 64 * 4;
         auto kl = k_bin_scatter_lds<R, M2>;
-        hipLaunchKernelGGL(kl, dim3((unsigned)nwaves), dim3(64), lds, s, xs, dxf, B, T, cell_start, perm, ipos, rec,
-                           rec_bytes, wp, poly, fixed ? 1 : 0);
+        hipLaunchKernelGGL(kl, launch_grid(nwaves, 64), dim3(64), lds, s, xs, dxf, B, nwaves, T, cell_start, perm, ipos,
+                           rec, rec_bytes, wp, poly, fixed ? 1 : 0);
         return;
     }
     if constexpr (sizeof(R) == 8) {
-        hipLaunchKernelGGL(k_bin_tables<M2>, dim3((unsigned)nwaves), dim3(256), 0, s, xs, dxf, B, T, cell_start, perm, ipos,
-                           rec, rec_bytes, wp, poly, fixed ? 1 : 0);
+        hipLaunchKernelGGL(k_bin_tables<M2>, launch_grid(nwaves, 256), dim3(256), 0, s, xs, dxf, B, nwaves, T, cell_start,
+                           perm, ipos, rec, rec_bytes, wp, poly, fixed ? 1 : 0);
         return;
     } else {
-        hipLaunchKernelGGL((k_bin_scatter<R, M2, true>), dim3((unsigned)((nwaves + 3) / 4)), dim3(256), 0, s, xs, dxf, B, nwaves, T,
-                           cell_start, perm, ipos, rec, rec_bytes, wp, poly, fixed ? 1 : 0);
+        hipLaunchKernelGGL((k_bin_scatter<R, M2, true>), launch_grid(((long long)nwaves + 3) / 4, 256), dim3(256), 0, s, xs,
+                           dxf, B, nwaves, T, cell_start, perm, ipos, rec, rec_bytes, wp, poly, fixed ? 1 : 0);
     }
 }
 

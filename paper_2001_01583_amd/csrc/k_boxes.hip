@@ -73,7 +73,8 @@ __global__ __launch_bounds__(kBoxThreads) void k_spread_box(const Xform *__restr
     __shared__ unsigned short queue[kBoxThreads / 64][kBoxThreads];
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     // neighbouring boxes on one XCD (workgroups go round robin over them)
-    const int k8 = blockIdx.x / kXcds, box_i = (int)(blockIdx.x % kXcds) * per_xcd + k8;
+    const int group = (int)group_index();
+    const int k8 = group / kXcds, box_i = group % kXcds * per_xcd + k8;
     if (k8 >= per_xcd || box_i >= nboxes) return;
     int bl = 0, bh = B;
     while (bh - bl > 1) {
@@ -258,8 +259,8 @@ hipError_t launch_spread_box(int m, const Xform *dxf, int B, int nboxes, const u
 {
     if (nboxes <= 0) return hipSuccess;
     const int per_xcd = (nboxes + kXcds - 1) / kXcds;
-    hipLaunchKernelGGL(k_spread_box<R>, dim3((unsigned)per_xcd * kXcds), dim3(kBoxThreads), 0, s, dxf, B, nboxes, per_xcd,
-                       m, rec, (int)rec_bytes, fs, cell_start);
+    hipLaunchKernelGGL(k_spread_box<R>, launch_grid((long long)per_xcd * kXcds, kBoxThreads), dim3(kBoxThreads), 0, s, dxf,
+                       B, nboxes, per_xcd, m, rec, (int)rec_bytes, fs, cell_start);
     return hipGetLastError();
 }
 

@@ -74,10 +74,11 @@ __global__ __launch_bounds__(256) void k_cells_scatter(const double *__restrict_
 // square of its ion count (about 150 at the sweep's densities).
 __global__ __launch_bounds__(256) void k_cells_reorder(const double4 *__restrict__ sorted_tmp,
                                                        const int *__restrict__ orig_tmp,
-                                                       const int *__restrict__ start,
+                                                       const int *__restrict__ start, long long ncell,
                                                        double4 *__restrict__ sorted, int *__restrict__ orig)
 {
-    const int c = blockIdx.x;
+    const long long c = group_index();
+    if (c >= ncell) return;
     const int s0 = start[c], s1 = start[c + 1];
     for (int i = s0 + threadIdx.x; i < s1; i += blockDim.x) {
         const int oi = orig_tmp[i];
@@ -114,7 +115,9 @@ __global__ __launch_bounds__(kPairThreads) void k_cells_pairs(const double4 *__r
     __shared__ double red[kPairThreads / 64];
     __shared__ int off[28], t0s[27];
     __shared__ double sh[27][3];
-    const int c = blockIdx.x / parts, pt = blockIdx.x - c * parts;
+    const long long group = group_index();
+    const int c = (int)(group / parts), pt = (int)(group - (long long)c * parts);
+    if (c >= nc * nc * nc) return;
     const int cz = c % nc, cy = (c / nc) % nc, cx = c / (nc * nc);
     const int s0 = start[c], s1 = start[c + 1];
     const int tid = threadIdx.x, wave = tid >> 6, nw = kPairThreads / 64;
@@ -163,7 +166,7 @@ __global__ __launch_bounds__(kPairThreads) void k_cells_pairs(const double4 *__r
         }
     }
     const double e = block_sum_fixed(e_acc, red);
-    if (tid == 0) part[blockIdx.x] = e;
+    if (tid == 0) part[group] = e;
 }
 
 // Workspace of the cell-list sum: [starts: nc^3 + 1 ints][scan scratch]
@@ -222,14 +225,14 @@ hipError_t launch_ewald_cells(const double *r, const double *q, long long M, dou
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_cells_scatter, dim3(nb), dim3(256), 0, s, r, q, M, L, start, cell, rank, sorted_tmp,
                        orig_tmp);
-    hipLaunchKernelGGL(k_cells_reorder, dim3((unsigned)ncell), dim3(256), 0, s, sorted_tmp, orig_tmp, start, sorted,
-                       orig);
+    hipLaunchKernelGGL(k_cells_reorder, launch_grid(ncell, 256), dim3(256), 0, s, sorted_tmp, orig_tmp, start, ncell,
+                       sorted, orig);
     const int parts = cell_parts(M, nc);
     e = hipFuncSetAttribute((const void *)k_cells_pairs, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)sizeof(PairTile));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cells_pairs, dim3((unsigned)(ncell * parts)), dim3(kPairThreads), sizeof(PairTile), s, sorted,
-                       orig, start, nc, parts, L, alpha, rcut * rcut, part, forces);
+    hipLaunchKernelGGL(k_cells_pairs, launch_grid(ncell * parts, kPairThreads), dim3(kPairThreads), sizeof(PairTile), s,
+                       sorted, orig, start, nc, parts, L, alpha, rcut * rcut, part, forces);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_sum_partials(part, (int)(ncell * parts), energy, s);

@@ -60,9 +60,10 @@ __global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *_
     using C = typename Complex<R>::T;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // this workgroup's points: share blockIdx mod 8, in order
-    const long long k = (long long)(blockIdx.x / kXcds) * (kGatherThreads / 64) + wave;
-    const long long g = (long long)(blockIdx.x % kXcds) * per_xcd + k;
+    // this workgroup's points: share (index mod 8), in order
+    const long long group = group_index();
+    const long long k = group / kXcds * (kGatherThreads / 64) + wave;
+    const long long g = group % kXcds * per_xcd + k;
     if (k >= per_xcd || g >= total) return;
     // the transform of point g: the last whose first point is not past it
     auto first = [&](const Xform *X) __attribute__((always_inline)) {
@@ -269,9 +270,9 @@ static hipError_t gather_m(bool grad, const Xform *dxf, int B, int which, int Zs
 {
     constexpr int W = kGatherThreads / 64;
     const long long per_xcd = (total + kXcds - 1) / kXcds;
-    const unsigned blocks = (unsigned)((per_xcd + W - 1) / W) * kXcds;
+    const dim3 grid = launch_grid((per_xcd + W - 1) / W * kXcds, kGatherThreads);
     auto kern = grad ? k_interp_gather<R, M2, true> : k_interp_gather<R, M2, false>;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kGatherThreads), 0, s, dxf, B, which, Zs, total, per_xcd, rec,
+    hipLaunchKernelGGL(kern, grid, dim3(kGatherThreads), 0, s, dxf, B, which, Zs, total, per_xcd, rec,
                        (int)rec_bytes, outs);
     return hipGetLastError();
 }

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kCostThreads) void k_tile_cost(const int *__restric
 {
     __shared__ int wsum[kCostThreads / 64];
     // (a wavefront's entries belong to one transform: coff is a multiple of 64)
-    const long long e = (long long)blockIdx.x * blockDim.x + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
+    const long long e = group_index() * blockDim.x + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
     const int nl = T * T / BW;
     int c = 0;
     if (e < entries) {
@@ -83,8 +83,9 @@ __global__ __launch_bounds__(kItemWaves * 64) void k_make_items(const int *__res
 {
     __shared__ int wcount[kItemWaves], wbase[kItemWaves];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool valid = (int)blockIdx.x * kItemWaves + w < pairs;
-    const int gp = valid ? blockIdx.x * kItemWaves + w : 0;
+    const long long gw = group_index() * kItemWaves + w;
+    const bool valid = gw < pairs;
+    const int gp = valid ? (int)gw : 0;
     const int xf = xform_of(xfs, B, &Xform::ioff, gp);
     const int nslab = xfs[xf].nslab, g = gp - xfs[xf].ioff;
     const int tile = g / nslab, slab = g % nslab;
@@ -170,7 +171,7 @@ hipError_t launch_tile_cost(const int *cell_start, const Xform *dxf, int B, long
                             int *lcost, unsigned long long *total, hipStream_t s)
 {
     if (entries <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tile_cost, dim3((unsigned)((entries + kCostThreads - 1) / kCostThreads)), dim3(kCostThreads), 0, s,
+    hipLaunchKernelGGL(k_tile_cost, launch_grid((entries + kCostThreads - 1) / kCostThreads, kCostThreads), dim3(kCostThreads), 0, s,
                        cell_start, dxf, B, entries, T, Zs, m, block_w(2 * m), lcost, total);
     return hipGetLastError();
 }
@@ -180,8 +181,8 @@ hipError_t launch_make_items(const int *lcost, const Xform *dxf, int B, long lon
                              int *nitems, int *overflow, hipStream_t s)
 {
     if (pairs <= 0) return hipSuccess;  // one wavefront per pair
-    hipLaunchKernelGGL(k_make_items, dim3((unsigned)((pairs + kItemWaves - 1) / kItemWaves)), dim3(kItemWaves * 64), 0, s,
-                       lcost, dxf, B, (int)pairs, T, block_w(2 * m), total, cap_div, min_cap, max_items, items, nitems,
+    hipLaunchKernelGGL(k_make_items, launch_grid((pairs + kItemWaves - 1) / kItemWaves, kItemWaves * 64),
+                       dim3(kItemWaves * 64), 0, s, lcost, dxf, B, (int)pairs, T, block_w(2 * m), total, cap_div, min_cap, max_items, items, nitems,
                        overflow);
     return hipGetLastError();
 }
