@@ -20,6 +20,16 @@ namespace hpnfft {
 constexpr int kPairThreads = 1024;
 constexpr int kPairGroups = 1024;  // workgroups worth having
 
+// Boxes of many cells with few ions each take small workgroups, four of which
+// run on a compute unit: a large one's wavefronts would have no ion each, while
+// its tile keeps others out.  Measured, at 1, 2, 8, 16, 32 and 64 ions per cell,
+// 20^3 cells: small 60, 70, 112, 202, 483 and 1637 us, large 121, 138, 177, 264, 557
+// and 1600 (one thread per ion, as before either: 96, 148, 471, 971, 2042 and
+// 4888).  128 threads: 46 us at 1 ion, but 9.7 ms against 7.4 where cells hold 143
+// all the same (ions in a part of the box).
+constexpr int kSparseThreads = 256, kSparseCap = 1024;
+static bool sparse_cells(long long M, long long ncell) { return ncell >= kPairGroups && M < 32 * ncell; }
+
 // Parts a cell's ions are split into.
 static int cell_parts(long long M, int nc)
 {
@@ -93,7 +103,7 @@ __global__ __launch_bounds__(256) void k_cells_reorder(const double4 *__restrict
 // F_i = sum_j q_i q_j [erfc(alpha r)/r + 2 alpha/sqrt(pi) exp(-alpha^2 r^2)] d_ij / r^2.
 //
 // Workgroup <-> (cell, part): the ions of the 27 cells around it go to LDS
-// (in tiles of kPairCap, shifted to their image on the way in), then each
+// (in tiles of CAP, shifted to their image on the way in), then each
 // wavefront takes every (wavefronts x parts)-th ion of the cell.  Small boxes
 // have few cells (27 at L = 3 rcut), so a cell is split into parts until about
 // kPairGroups workgroups run.  An ion's partial sums over later tiles are
@@ -102,7 +112,8 @@ __global__ __launch_bounds__(256) void k_cells_reorder(const double4 *__restrict
 // Bound by the float64 vector unit (pair terms, then distance tests):
 // 393,216 ions, 593 partners each within the cut-off, 143 ions per cell: 8.46
 // -> 2.57 ms; 6,144 ions in 27 cells: 4.90 -> 0.10 ms.
-__global__ __launch_bounds__(kPairThreads) void k_cells_pairs(const double4 *__restrict__ sorted,
+template <int THREADS, int CAP>
+__global__ __launch_bounds__(THREADS) void k_cells_pairs(const double4 *__restrict__ sorted,
                                                               const int *__restrict__ orig,
                                                               const int *__restrict__ start, int nc, int parts,
                                                               double L, double alpha, double rcut2,
@@ -110,9 +121,9 @@ __global__ __launch_bounds__(kPairThreads) void k_cells_pairs(const double4 *__r
                                                               double *__restrict__ forces)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    PairTile &tile = *reinterpret_cast<PairTile *>(smem);
-    __shared__ unsigned short queues[kPairThreads / 64][kPairQueue];
-    __shared__ double red[kPairThreads / 64];
+    PairTileOf<CAP> &tile = *reinterpret_cast<PairTileOf<CAP> *>(smem);
+    __shared__ unsigned short queues[THREADS / 64][kPairQueue];
+    __shared__ double red[THREADS / 64];
     __shared__ int off[28], t0s[27];
     __shared__ double sh[27][3];
     const long long group = group_index();
@@ -120,33 +131,42 @@ __global__ __launch_bounds__(kPairThreads) void k_cells_pairs(const double4 *__r
     if (c >= nc * nc * nc) return;
     const int cz = c % nc, cy = (c / nc) % nc, cx = c / (nc * nc);
     const int s0 = start[c], s1 = start[c + 1];
-    const int tid = threadIdx.x, wave = tid >> 6, nw = kPairThreads / 64;
-    if (tid < 27) {
-        int ax = cx + tid / 9 - 1, ay = cy + (tid / 3) % 3 - 1, az = cz + tid % 3 - 1;
-        double sx = 0.0, sy = 0.0, sz = 0.0;
-        if (ax < 0) { ax += nc; sx = -L; } else if (ax >= nc) { ax -= nc; sx = L; }
-        if (ay < 0) { ay += nc; sy = -L; } else if (ay >= nc) { ay -= nc; sy = L; }
-        if (az < 0) { az += nc; sz = -L; } else if (az >= nc) { az -= nc; sz = L; }
-        const int a = (ax * nc + ay) * nc + az;
-        t0s[tid] = start[a];
-        off[tid + 1] = start[a + 1] - start[a];
-        sh[tid][0] = sx;
-        sh[tid][1] = sy;
-        sh[tid][2] = sz;
+    const int tid = threadIdx.x, wave = tid >> 6, nw = THREADS / 64;
+    if (s0 + nw * pt >= s1) {  // no ion of the cell falls to this workgroup
+        if (tid == 0) part[group] = 0.0;
+        return;
     }
-    __syncthreads();
-    if (tid == 0) {
-        off[0] = 0;
-        for (int k = 1; k < 28; ++k) off[k] += off[k - 1];
+    if (tid < 64) {
+        int n = 0;
+        if (tid < 27) {
+            int ax = cx + tid / 9 - 1, ay = cy + (tid / 3) % 3 - 1, az = cz + tid % 3 - 1;
+            double sx = 0.0, sy = 0.0, sz = 0.0;
+            if (ax < 0) { ax += nc; sx = -L; } else if (ax >= nc) { ax -= nc; sx = L; }
+            if (ay < 0) { ay += nc; sy = -L; } else if (ay >= nc) { ay -= nc; sy = L; }
+            if (az < 0) { az += nc; sz = -L; } else if (az >= nc) { az -= nc; sz = L; }
+            const int a = (ax * nc + ay) * nc + az;
+            t0s[tid] = start[a];
+            n = start[a + 1] - start[a];
+            sh[tid][0] = sx;
+            sh[tid][1] = sy;
+            sh[tid][2] = sz;
+        }
+        if (tid == 0) off[0] = 0;
+#pragma unroll
+        for (int o = 1; o < 32; o <<= 1) {
+            const int y = __shfl_up(n, o, 64);
+            if (tid >= o) n += y;
+        }
+        if (tid < 27) off[tid + 1] = n;
     }
     __syncthreads();
     const int total = off[27], own = off[13] - s0;  // candidate of own-cell ion i: own + i
     const double c2 = 2.0 * alpha / sqrt(M_PI);
     double e_acc = 0.0;
-    for (int t0 = 0; t0 < total; t0 += kPairCap) {
-        const int cnt = min(kPairCap, total - t0);
+    for (int t0 = 0; t0 < total; t0 += CAP) {
+        const int cnt = min(CAP, total - t0);
         if (t0 > 0) __syncthreads();
-        for (int k = tid; k < cnt; k += kPairThreads) {
+        for (int k = tid; k < cnt; k += THREADS) {
             int nb = 0;
 #pragma unroll
             for (int b = 16; b > 0; b >>= 1)
@@ -228,12 +248,15 @@ hipError_t launch_ewald_cells(const double *r, const double *q, long long M, dou
     hipLaunchKernelGGL(k_cells_reorder, launch_grid(ncell, 256), dim3(256), 0, s, sorted_tmp, orig_tmp, start, ncell,
                        sorted, orig);
     const int parts = cell_parts(M, nc);
-    e = hipFuncSetAttribute((const void *)k_cells_pairs, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)sizeof(PairTile));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cells_pairs, launch_grid(ncell * parts, kPairThreads), dim3(kPairThreads), sizeof(PairTile), s,
-                       sorted, orig, start, nc, parts, L, alpha, rcut * rcut, part, forces);
-    e = hipGetLastError();
+    auto pairs = [&](auto kern, int threads, size_t lds) {
+        e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return;
+        hipLaunchKernelGGL(kern, launch_grid(ncell * parts, threads), dim3(threads), lds, s, sorted, orig, start, nc, parts, L,
+                           alpha, rcut * rcut, part, forces);
+        e = hipGetLastError();
+    };
+    if (sparse_cells(M, ncell)) pairs(k_cells_pairs<kSparseThreads, kSparseCap>, kSparseThreads, sizeof(PairTileOf<kSparseCap>));
+    else pairs(k_cells_pairs<kPairThreads, kPairCap>, kPairThreads, sizeof(PairTile));
     if (e != hipSuccess) return e;
     return launch_sum_partials(part, (int)(ncell * parts), energy, s);
 }

@@ -71,16 +71,17 @@ __device__ inline void add_pair(double dx, double dy, double dz, double d2, doub
 // Candidates in LDS (structure of arrays) and a wavefront's queue of accepted
 // ones (a ring of 128 slots: at most 63 wait when 64 more are tested).
 constexpr int kPairCap = 4096;
-struct PairTile {
-    double x[kPairCap], y[kPairCap], z[kPairCap], q[kPairCap];
+template <int CAP> struct PairTileOf {
+    double x[CAP], y[CAP], z[CAP], q[CAP];
 };
+using PairTile = PairTileOf<kPairCap>;
 constexpr int kPairQueue = 128;
 
 // All pairs of the ion p (x, y, z, charge) with candidates 0 .. cnt - 1
 // closer than rcut, except candidate `self`.  IMAGE: take each candidate's
 // nearest periodic image (else the tile already holds it).
-template <bool IMAGE>
-__device__ inline void sweep_pairs(const double4 p, int self, int cnt, const PairTile &t, unsigned short *queue,
+template <bool IMAGE, typename Tile>
+__device__ inline void sweep_pairs(const double4 p, int self, int cnt, const Tile &t, unsigned short *queue,
                                    double rcut2, double alpha, double c2, double L, double invL, PairSum &s)
 {
     const int lane = threadIdx.x & 63;
