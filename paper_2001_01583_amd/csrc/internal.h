@@ -104,8 +104,9 @@ struct Tiling {
 };
 
 // A launch of `groups` workgroups whose number grows with the problem.  HIP
-// refuses 2^32 threads and more per grid dimension, so long launches get several
-// rows: workgroup i is group_index(), and there may be more than `groups`.  Rows
+// counts the threads of a grid dimension in 32 bits, and a launch of 2^32 or more
+// was measured to run a part of them without an error, so long launches get
+// several rows: workgroup i is group_index(), and there may be more than `groups`.  Rows
 // are a multiple of kXcds long, so that the group's XCD stays i mod kXcds.
 inline dim3 launch_grid(long long groups, int threads)
 {

@@ -1,4 +1,5 @@
-"""Launches of 2^32 threads and more: HIP refuses them in one grid dimension.
+"""Launches of 2^32 threads and more: one grid dimension does not hold them, and
+runs a part of them without an error.
 The gathering interpolation runs 64 threads per point (over 2^26 points), the
 cell-list pair sum up to 1024 per cell (over 161 cells per edge).  Points and
 ions of the large call are compared with the same ones in a small call, which
