@@ -198,35 +198,38 @@ __global__ __launch_bounds__(1024) void k_spread_slab(const Xform *__restrict__ 
                 }
             };
             const int n = r.n;
-            for (int i = 0; i < n; i += 4) {
-                const int last = min(n - 1 - i, 3);
-                const int fr = d.c0 + d.u - (m - 1) - z;  // first tap plane
-                const int fmin = uni(fr), fmax = __builtin_amdgcn_readlane(fr, 16 * last);
-                const R w1 = on && p4 <= last ? d.w1 : R(0);
-                const R b = on ? d.w2 : R(0);
-                const R ar = d.f[0] * w1, ai = d.f[1] * w1;
-                R wr[Q], wi[Q];
+            int i = 0;
+            do {
+                const int end = sizeof(R) == 4 ? min(n, i + kSlabRun) : n;
+                for (; i < end; i += 4) {
+                    const int last = min(n - 1 - i, 3);
+                    const int fr = d.c0 + d.u - (m - 1) - z;  // first tap plane
+                    const int fmin = uni(fr), fmax = __builtin_amdgcn_readlane(fr, 16 * last);
+                    const R w1 = on && p4 <= last ? d.w1 : R(0);
+                    const R b = on ? d.w2 : R(0);
+                    const R ar = d.f[0] * w1, ai = d.f[1] * w1;
+                    R wr[Q], wi[Q];
 #pragma unroll
-                for (int q = 0; q < Q; ++q) {
-                    const R w0 = (unsigned)(q - fr) < (unsigned)M2 ? d.w0[q] : R(0);
-                    wr[q] = ar * w0;
-                    wi[q] = ai * w0;
-                }
-                if (i + 4 < n) {
-                    fetch(r, i + 4, z, d);
-                } else {
-                    advance(false);
-                    if (line < nl) fetch(r, 0, z0 + Q * quad, d);
-                }
+                    for (int q = 0; q < Q; ++q) {
+                        const R w0 = (unsigned)(q - fr) < (unsigned)M2 ? d.w0[q] : R(0);
+                        wr[q] = ar * w0;
+                        wi[q] = ai * w0;
+                    }
+                    if (i + 4 < n) {
+                        fetch(r, i + 4, z, d);
+                    } else {
+                        advance(false);
+                        if (line < nl) fetch(r, 0, z0 + Q * quad, d);
+                    }
 #pragma unroll
-                for (int q = 0; q < Q; ++q) {
-                    if (q < fmin || q >= fmax + M2) continue;  // no point of the batch reaches the plane
-                    re[q] = Mat<R>::mul(wr[q], b, re[q]);
-                    ie[q] = Mat<R>::mul(wi[q], b, ie[q]);
+                    for (int q = 0; q < Q; ++q) {
+                        if (q < fmin || q >= fmax + M2) continue;  // no point of the batch reaches the plane
+                        re[q] = Mat<R>::mul(wr[q], b, re[q]);
+                        ie[q] = Mat<R>::mul(wi[q], b, ie[q]);
+                    }
                 }
-                if (sizeof(R) == 4 && i % kSlabRun == kSlabRun - 4 && i + 4 < n) flush();
-            }
-            flush();
+                flush();
+            } while (i < n);
         }
         __syncthreads();
         // the tile to the grid; consecutive lanes add to consecutive reals
