@@ -33,6 +33,7 @@ struct Xform {
     int boff;          // output boxes (box method spread) of the transforms before this one
     int wave0;         // wavefronts of 64 points of the transforms before this one
     int ioff;          // (tile, slab) pairs of the line-method transforms before this one
+    int lgoff;         // line groups (lines.h) of the line-method transforms before this one
     long long coff;    // first entry of this transform's run costs (a multiple of 64)
     long long key_off; // first entry of this transform's cell_start table
     void *grid;        // n0 n1 n2 complex
@@ -274,12 +275,13 @@ template <typename R>
 hipError_t launch_interp(int m, const Xform *dxf, const SItem *items, int nitems, int *queue,
                          Tiling t, const unsigned char *rec, size_t rec_bytes, const int *cell_start,
                          R *outs, hipStream_t s);
-// Interpolation by batches of points on a line (lines.h), one transform per
-// launch: windows of 2m = 10 .. 16 cells.  xf: the transform's device
-// descriptor; n: its grid edges; T: the tile edge of the counting sort.  outs
-// need not be cleared.
+// Interpolation by batches of points on a line (lines.h) of the line-method
+// transforms: windows of 2m = 10 .. 16 cells.  ngroups: their line groups
+// (Xform::lgoff); n0: the largest dim-0 edge among them; T: the tile edge of the
+// counting sort.  outs need not be cleared.
+int line_groups(const Xform &X);
 template <typename R>
-hipError_t launch_interp_lines(int m, bool grad, const Xform *xf, const int n[3], int *queue, int T,
+hipError_t launch_interp_lines(int m, bool grad, const Xform *dxf, int B, int ngroups, int n0, int *queue, int T,
                                const unsigned char *rec, size_t rec_bytes, const int *cs, R *outs, hipStream_t s);
 // odd: some grid edge has a factor 5 or 7
 template <typename R>

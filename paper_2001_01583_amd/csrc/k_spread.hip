@@ -62,15 +62,17 @@ hipError_t launch_interp(int m, const Xform *dxf, const SItem *items, int nitems
 #undef HPNFFT_INTERP_CASE
 }
 
+int line_groups(const Xform &X) { return ((X.n[1] + kLineT - 1) / kLineT) * ((X.n[2] + kLineT - 1) / kLineT); }
+
 template <typename R>
-hipError_t launch_interp_lines(int m, bool grad, const Xform *xf, const int n[3], int *queue, int T,
+hipError_t launch_interp_lines(int m, bool grad, const Xform *dxf, int B, int ngroups, int n0, int *queue, int T,
                                const unsigned char *rec, size_t rec_bytes, const int *cs, R *outs, hipStream_t s)
 {
     switch (m) {
 #define HPNFFT_LINES_CASE(MM)                                                                       \
     case MM:                                                                                        \
-        return grad ? interp_lines_m<R, 2 * MM, true>(xf, n, queue, T, rec, rec_bytes, cs, outs, s)  \
-                    : interp_lines_m<R, 2 * MM, false>(xf, n, queue, T, rec, rec_bytes, cs, outs, s);
+        return grad ? interp_lines_m<R, 2 * MM, true>(dxf, B, ngroups, n0, queue, T, rec, rec_bytes, cs, outs, s)   \
+                    : interp_lines_m<R, 2 * MM, false>(dxf, B, ngroups, n0, queue, T, rec, rec_bytes, cs, outs, s);
         HPNFFT_LINES_CASE(5)
         HPNFFT_LINES_CASE(6)
         HPNFFT_LINES_CASE(7)
@@ -80,9 +82,9 @@ hipError_t launch_interp_lines(int m, bool grad, const Xform *xf, const int n[3]
     }
 }
 
-template hipError_t launch_interp_lines<double>(int, bool, const Xform *, const int *, int *, int,
+template hipError_t launch_interp_lines<double>(int, bool, const Xform *, int, int, int, int *, int,
                                                 const unsigned char *, size_t, const int *, double *, hipStream_t);
-template hipError_t launch_interp_lines<float>(int, bool, const Xform *, const int *, int *, int,
+template hipError_t launch_interp_lines<float>(int, bool, const Xform *, int, int, int, int *, int,
                                                const unsigned char *, size_t, const int *, float *, hipStream_t);
 template hipError_t launch_spread<double>(int, const Xform *, const SItem *, int, int *, Tiling,
                                           const unsigned char *, size_t, const double *, const int *, hipStream_t);

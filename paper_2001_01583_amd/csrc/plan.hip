@@ -84,6 +84,7 @@ struct hpnfft_plan_s {
     std::vector<long long> keys;
     long long Mtot = 0, Ftot = 0, Mbox = 0;  // points, frequencies, points of box transforms
     long long pairs = 0, costs = 0;          // (tile, slab) pairs and run costs of the line transforms
+    int ngroups = 0, linen0 = 0;             // their line groups (lines.h) and largest dim-0 edge
     Tiling til{16, 16, 1024};
     hipStream_t stream = nullptr;
     char *ws = nullptr;
@@ -401,11 +402,16 @@ void choose_methods(hpnfft_plan_s *p)
         p->tbox[b] = box;
     }
     p->Mbox = 0;
-    p->nboxes = 0;
+    p->nboxes = p->ngroups = p->linen0 = 0;
     for (int b = 0; b < p->B; ++b) {
         p->hx[b].goff = p->Mbox;
         p->hx[b].boff = p->nboxes;
-        if (!p->tbox[b]) continue;
+        p->hx[b].lgoff = p->ngroups;
+        if (!p->tbox[b]) {
+            p->ngroups += line_groups(p->hx[b]);
+            p->linen0 = std::max(p->linen0, p->hx[b].n[0]);
+            continue;
+        }
         p->Mbox += p->hx[b].M;
         p->nboxes += spread_boxes(p->hx[b]);
     }
@@ -1051,11 +1057,9 @@ template <typename R> int run_forward(hpnfft_plan_s *p, const void *fhat, void *
                                        lines ? p->Mbox : p->Mtot,
                                        p->at<unsigned char>(L.rec), L.rec_bytes, p->at<R>(L.outs), s));
         if (lines && use_lines(p)) {
-            for (size_t b = 0; b < p->hx.size(); ++b)
-                if (!p->tbox[b])
-                    HCHECK(launch_interp_lines<R>(p->m, false, dxf + b, p->hx[b].n, p->at<int>(L.counters) + 1, p->til.T,
-                                                  p->at<unsigned char>(L.rec), L.rec_bytes,
-                                                  p->at<int>(L.cell_start), p->at<R>(L.outs), s));
+            HCHECK(launch_interp_lines<R>(p->m, false, dxf, p->B, p->ngroups, p->linen0, p->at<int>(L.counters) + 1,
+                                          p->til.T, p->at<unsigned char>(L.rec), L.rec_bytes,
+                                          p->at<int>(L.cell_start), p->at<R>(L.outs), s));
         } else if (lines) {
             Tiling t = p->til;
             t.ring = use_ring(p, t);
@@ -1085,13 +1089,10 @@ int run_backward(hpnfft_plan_s *p, const void *f, const void *gfhat, void *grad_
         HCHECK(launch_interp_gather<R>(p->m, true, dxf, p->B, lines ? GATHER_BOXES : GATHER_ALL, p->det() ? 0 : p->til.Zs,
                                        lines ? p->Mbox : p->Mtot, p->at<unsigned char>(L.rec), L.rec_bytes,
                                        p->at<R>(L.outs), s));
-        if (lines) {
-            for (size_t b = 0; b < p->hx.size(); ++b)
-                if (!p->tbox[b])
-                    HCHECK(launch_interp_lines<R>(p->m, true, dxf + b, p->hx[b].n, p->at<int>(L.counters) + 1,
-                                                  p->til.T, p->at<unsigned char>(L.rec), L.rec_bytes,
-                                                  p->at<int>(L.cell_start), p->at<R>(L.outs), s));
-        }
+        if (lines)
+            HCHECK(launch_interp_lines<R>(p->m, true, dxf, p->B, p->ngroups, p->linen0, p->at<int>(L.counters) + 1,
+                                          p->til.T, p->at<unsigned char>(L.rec), L.rec_bytes,
+                                          p->at<int>(L.cell_start), p->at<R>(L.outs), s));
     }
     {
         PhaseTimer t(p, HPNFFT_PH_GRAD_FIN);
