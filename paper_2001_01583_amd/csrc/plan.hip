@@ -456,6 +456,23 @@ bool use_ring(const hpnfft_plan_s *p, const Tiling &t)
     return true;
 }
 
+// Whether the forward gathers the points of line-method transforms too: float64
+// plans that would interpolate by ring sweeps, below a density of points per
+// cell.  A ring sweep's batch of 16 points takes the time of its matrix products
+// however few points its eight lines hold.  Measured (2m = 8, N = 64^3, forward,
+// us, ring against gather; register windows before either): 119 / 45 (106) at
+// 0.01 points per cell, 147 / 74 (122) at 0.05, 154 / 113 (140) at 0.1, 162 / 151 (158)
+// at 0.15, 179 / 189 (173) at 0.2.
+constexpr double kGatherDensity = 0.15;
+bool gather_lines(const hpnfft_plan_s *p)
+{
+    if (p->prec != HPNFFT_F64 || !use_ring(p, p->til)) return false;
+    double cells = 0;
+    for (int b = 0; b < p->B; ++b)
+        if (!p->tbox[b]) cells += (double)p->hx[b].n[0] * p->hx[b].n[1] * p->hx[b].n[2];
+    return (double)(p->Mtot - p->Mbox) < kGatherDensity * cells;
+}
+
 // Whether the line-method transforms are interpolated by batches of points on
 // a line (lines.h): windows of 2m = 10 .. 16 cells (HPNFFT_LINES=0 selects
 // the staged sweep, and the gather for gradients).
@@ -1042,7 +1059,7 @@ template <typename R> int run_forward(hpnfft_plan_s *p, const void *fhat, void *
     const Layout &L = p->L;
     hipStream_t s = p->stream;
     const Xform *dxf = p->at<Xform>(L.xf);
-    const bool lines = p->any_lines && !p->det();
+    const bool lines = p->any_lines && !p->det() && !gather_lines(p);
     // every sweep stores each point's value once, but the staged one, which
     // adds partial sums into a cleared output
     if (lines && !use_lines(p) && !use_ring(p, p->til)) {
