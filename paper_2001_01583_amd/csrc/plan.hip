@@ -207,10 +207,13 @@ void hlog(const char *fmt, ...)
 //     ...
 //    }}
 // The key names everything the best tiling depends on: the device
-// architecture and compute-unit count, precision, cut-off, window, sigma,
-// the gradient flag, and per transform the grid edges and the point count
-// rounded down to a power of two (batches: a hash of that list).
+// architecture and compute-unit count, the generation of the kernels (a tiling
+// timed with kernels that have been replaced is timed again), precision,
+// cut-off, window, sigma, the gradient flag, and per transform the grid edges
+// and the point count rounded down to a power of two (batches: a hash of that
+// list).  The version is that of the file's format.
 constexpr int kTuneCacheVersion = 3;
+constexpr int kTuneKernels = 2;  // 2: matrix-core spreads, line batches, gathers
 
 const char *tune_cache_path()
 {
@@ -221,8 +224,8 @@ const char *tune_cache_path()
 std::string tune_key(const hpnfft_plan_s *p)
 {
     char head[256];
-    std::snprintf(head, sizeof(head), "v%d|%s|cu%d|%s|m%d|w%d|s%.6g|g%d|B%d|%s", kTuneCacheVersion, p->arch,
-                  p->cus, p->prec == HPNFFT_F32 ? "f32" : "f64", p->m, p->window, p->sigma, p->grad() ? 1 : 0,
+    std::snprintf(head, sizeof(head), "v%d|k%d|%s|cu%d|%s|m%d|w%d|s%.6g|g%d|B%d|%s", kTuneCacheVersion, kTuneKernels,
+                  p->arch, p->cus, p->prec == HPNFFT_F32 ? "f32" : "f64", p->m, p->window, p->sigma, p->grad() ? 1 : 0,
                   p->B, p->boxes ? "boxes" : (p->any_box ? "mixed" : "lines"));
     std::string list;
     for (const Xform &X : p->hx) {
