@@ -97,15 +97,15 @@ struct hpnfft_plan_s {
     std::map<int, std::vector<unsigned char>> h_tw;
     std::vector<FItem> h_fit[3];
     int nitems = 0;
-    // sweep method: requested (HPNFFT_METHOD_*) and in use; the box method's
-    // static work list (one item per output box) and largest box (cells)
+    // sweep method: requested (HPNFFT_METHOD_*) and in use; the deterministic
+    // spread's static work list (one item per output box) and largest box (cells)
     int method = HPNFFT_METHOD_AUTO;
     bool boxes = false;            // every transform uses boxes (tiling = box edges)
     bool any_box = false;          // some transform uses boxes
     bool any_lines = true;         // some transform uses the line sweeps
     std::vector<char> tbox;        // per transform: box method
     int max_cells = 0;
-    int nbitems = 0;               // box work items (one per block of bins)
+    int nbitems = 0;               // its items (one per block of bins)
     int nboxes = 0;                // output boxes of the box method's spread
     std::vector<SItem> h_box_items;
     int cus = 256;
@@ -606,7 +606,8 @@ void build_layout(hpnfft_plan_s *p)
         p->keys[b] = (long long)X.ntx * X.nty * T * T * X.n[0] + 1;
         for (int d = 0; d < 3; ++d) X.nbox[d] = X.gbox[d] = 0;
         if (p->tbox[b]) {
-            // box method: sort keys are point bins; one work item per output box
+            // box method: sort keys are point bins; the deterministic spread has
+            // one work item per output box
             const Tiling bt = box_tiling(p, p->til);
             long long nbins = 1, nboxes = 1, cells = 1;
             for (int d = 0; d < 3; ++d) {
@@ -618,7 +619,7 @@ void build_layout(hpnfft_plan_s *p)
                 cells *= bd.maxw;
             }
             p->keys[b] = nbins + 1;
-            for (long long q = 0; q < nboxes; ++q) p->h_box_items.push_back(SItem{b, (int)q, 0, 0, 0, 0, 0, 0});
+            for (long long q = 0; p->det() && q < nboxes; ++q) p->h_box_items.push_back(SItem{b, (int)q, 0, 0, 0, 0, 0, 0});
             p->max_cells = std::max(p->max_cells, (int)cells);
         }
         maxM = std::max(maxM, X.M);
@@ -684,7 +685,7 @@ void build_layout(hpnfft_plan_s *p)
     L.tcost = take((size_t)p->costs * 4);
     L.max_items = (int)std::min<long long>(pairs + (long long)p->cus * 4 + 64, 0x7fffffffLL / 64);
     L.items = take((size_t)L.max_items * sizeof(SItem));
-    L.bitems = take(std::max<size_t>(1, p->h_box_items.size()) * sizeof(SItem));
+    L.bitems = take(p->h_box_items.size() * sizeof(SItem));
     for (int d = 0; d < 3; ++d) {
         long long cnt = 0;
         for (int b = 0; b < p->B; ++b) {
@@ -879,8 +880,8 @@ int upload_tables(hpnfft_plan_s *p)
     }
     HCHECK(hipMemcpyAsync(p->ws + L.xf, p->hx.data(), p->hx.size() * sizeof(Xform), hipMemcpyHostToDevice,
                           p->stream));
-    if (p->any_box) {
-        // the box method's work list does not depend on the points
+    if (p->det()) {
+        // the deterministic spread's work list does not depend on the points
         HCHECK(hipMemcpyAsync(p->ws + L.bitems, p->h_box_items.data(), p->h_box_items.size() * sizeof(SItem),
                               hipMemcpyHostToDevice, p->stream));
     }
