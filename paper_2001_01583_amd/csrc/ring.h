@@ -374,7 +374,7 @@ __global__ __launch_bounds__(kRingThreads, ring_spread_waves<R>()) void k_spread
 template <typename R> constexpr int ring_pitch() { return sizeof(R) == 4 ? 20 : 18; }
 template <typename R> constexpr int ring_plane() { return kRingP * 2 * ring_pitch<R>(); }
 // points a wavefront stages at a time
-template <typename R> constexpr int ring_interp_chunk() { return 16; }
+template <typename R> constexpr int ring_interp_chunk() { return 16; }  // (one matrix of points)
 template <typename R> constexpr size_t ring_interp_lds()
 {
     return (size_t)2 * kRingZp * ring_plane<R>() * sizeof(R) +
@@ -501,9 +501,8 @@ __global__ __launch_bounds__(kRingThreads, sizeof(R) == 4 ? 6 : 4) void k_interp
                     sg.store(st, lane);
                     if (u & 7) ring_image<R>(st, cnt, u, lane);
                     load_next(r, ch + wpr);
-                  for (int c = 0; c < cnt; c += 16) {
-                    const int lastp = min(cnt - 1 - c, 15);
-                    const unsigned char *rp = st + (c + min(p16, lastp)) * Stage::RB;
+                    const int lastp = cnt - 1;  // (a chunk is one batch)
+                    const unsigned char *rp = st + min(p16, lastp) * Stage::RB;
                     const R *ps = reinterpret_cast<const R *>(rp);
                     const V4 w0a = reinterpret_cast<const V4 *>(rp)[0], w0b = reinterpret_cast<const V4 *>(rp)[1];
                     const V4 w1 = reinterpret_cast<const V4 *>(rp)[2 + (k4 & 1)];
@@ -546,8 +545,7 @@ __global__ __launch_bounds__(kRingThreads, sizeof(R) == 4 ? 6 : 4) void k_interp
                     v = fma(S[2], w1[2], v);
                     v = fma(S[3], w1[3], v);
                     v += __shfl_xor(v, 16, 64);  // the other four tap rows
-                    if (p16 <= lastp && !(k4 & 1)) outs[2 * (poff + first + c + p16) + (k4 >> 1)] = v;
-                  }
+                    if (p16 <= lastp && !(k4 & 1)) outs[2 * (poff + first + p16) + (k4 >> 1)] = v;
                 }
             }
             if (g + 1 < ng) __syncthreads();
