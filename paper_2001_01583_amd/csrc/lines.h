@@ -33,6 +33,10 @@
 namespace hpnfft {
 
 constexpr int kLineT = 4;  // lines per group along dims 1 and 2
+// Planes per item at least, where whole phases would leave workgroups out: 32^3
+// cells, 2m = 16, 200,000 points, float32 236 -> 134 us, float64 229 -> 160 us (three
+// ranges of 13 planes before; register windows, 145 and 233 us).
+constexpr int kLineZ = 4;
 
 template <typename R, int M2, bool GRAD> struct LineBatch {
     static constexpr int P = kLineT + M2 - 1, PLANE = P * P;  // footprint cells of a plane
@@ -56,7 +60,7 @@ template <typename R, int M2, bool GRAD> struct LineBatch {
 
 template <typename R, int M2, bool GRAD>
 __global__ __launch_bounds__((LineBatch<R, M2, GRAD>::threads), (LineBatch<R, M2, GRAD>::waves)) void k_interp_lines(
-    const Xform *__restrict__ xfs, int B, int ngroups, int ranges, int *__restrict__ queue, int T,
+    const Xform *__restrict__ xfs, int B, int ngroups, int ranges, int fine, int *__restrict__ queue, int T,
     const unsigned char *__restrict__ rec, int rbytes, const int *__restrict__ cell_start, R *__restrict__ outs)
 {
     using LB = LineBatch<R, M2, GRAD>;
@@ -83,8 +87,8 @@ __global__ __launch_bounds__((LineBatch<R, M2, GRAD>::threads), (LineBatch<R, M2
         const int range_i = it / ngroups, gi = it - range_i * ngroups;
         const Xform *xf = xfs + xform_of(xfs, B, &Xform::lgoff, uni(gi));
         const int n0 = xf->n[0], n1 = xf->n[1], n2 = xf->n[2], ntx = xf->ntx;
-        const int phases = (n0 + DZ - 1) / DZ, nr = min(phases, ranges);
-        const int Zi = (phases + nr - 1) / nr * DZ;
+        const int phases = (n0 + DZ - 1) / DZ, nr = min(fine ? (n0 + kLineZ - 1) / kLineZ : phases, ranges);
+        const int Zi = fine ? (n0 + nr - 1) / nr : (phases + nr - 1) / nr * DZ;
         const int za = range_i * Zi, ze = min(za + Zi, n0);  // cells of the item's points
         if (za >= n0) continue;  // (a transform of fewer ranges)
         const int ngx = (n2 + kLineT - 1) / kLineT, gl = gi - xf->lgoff;
@@ -94,6 +98,11 @@ __global__ __launch_bounds__((LineBatch<R, M2, GRAD>::threads), (LineBatch<R, M2
         const gptr<const V2> grid = as_global(reinterpret_cast<const V2 *>(xf->grid));
         const size_t pstride = (size_t)n1 * n2;
         const int qb = za - m + 1;                              // its first window plane
+        // a leading dim without a coordinate holds every point at plane 0, with
+        // the unit impulse there: that plane only (ring numbering).  128
+        // frequencies, 200,000 points, 2m = 16, float32 722 -> 251 us, float64 509 ->
+        // 338 us (register windows: 314 and 392 us)
+        const bool flat = xf->flat > 0;
         // sorted points of line `lane` (lanes 0 .. 15) in a phase's planes
         const int ly = (lane & 15) / kLineT, lx = lane & (kLineT - 1);
         const bool has = lane < NL && Y0 + ly < n1 && X0 + lx < n2;
@@ -184,7 +193,8 @@ __global__ __launch_bounds__((LineBatch<R, M2, GRAD>::threads), (LineBatch<R, M2
                     const int c0 = as_const(reinterpret_cast<const int *>(q + OFF_PZ))[0];
                     j1[p] = p < np ? c0 - za : 1 << 28;
                 }
-                const int jlast = as_const(reinterpret_cast<const int *>(rp + (size_t)(np - 1) * rbytes + OFF_PZ))[0] - za;
+                const int clast = as_const(reinterpret_cast<const int *>(rp + (size_t)(np - 1) * rbytes + OFF_PZ))[0];
+                const int jend = flat ? 1 - qb : clast - za + M2;
                 const int base = (ln / kLineT) * P + (ln & (kLineT - 1));
                 // the lane's cells of a plane: cell + k RPG P (rows past the
                 // footprint's last are read from its last row)
@@ -198,7 +208,7 @@ __global__ __launch_bounds__((LineBatch<R, M2, GRAD>::threads), (LineBatch<R, M2
                         sr[p][k] = si[p][k] = R(0);
                         if constexpr (GRAD) dr[p][k] = di[p][k] = R(0);
                     }
-                int j = j1[0];
+                int j = flat ? -qb : j1[0];
                 int ring_p = j % NP;             // plane j's place in the ring
                 int slot = (j + qb + M2) % M2;   // its weights' slot (qb > -m)
                 auto read = [&](V2 (&c)[NR]) __attribute__((always_inline)) {
@@ -234,27 +244,41 @@ __global__ __launch_bounds__((LineBatch<R, M2, GRAD>::threads), (LineBatch<R, M2
                 // meets windows that have ended)
                 V2 ca[NR], cb[NR];
                 read(ca);
-                while (j < jlast + M2) {
+                while (j < jend) {
                     read(cb);
                     step(ca);
                     read(ca);
                     step(cb);
                 }
                 const int j8 = lane >> 3, vq = ((j8 & 1) << 2) | (j8 & 2) | (j8 >> 2);  // value of the lane's group
+                // (all of the weights' loads before their first use: one at a time
+                // they took a fifth of the kernel)
+                R rw1[G][NR], rw2[G], rd1[GRAD ? G : 1][GRAD ? NR : 1], rd2[GRAD ? G : 1];
+#pragma unroll
+                for (int p = 0; p < G; ++p) {
+                    const R *ps = reinterpret_cast<const R *>(rp + (size_t)min(p, np - 1) * rbytes);
+                    rw2[p] = ps[2 * M2 + t2];
+                    if constexpr (GRAD) rd2[p] = ps[OFF_D + 2 * M2 + t2];
+#pragma unroll
+                    for (int k = 0; k < NR; ++k) {
+                        const int r = min(t1 + RPG * k, M2 - 1);
+                        rw1[p][k] = ps[M2 + r];
+                        if constexpr (GRAD) rd1[p][k] = ps[OFF_D + M2 + r];
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
                 if constexpr (GRAD) {
 #pragma unroll
                     for (int p = 0; p < G; ++p) {
                         if (p >= np) break;
-                        const R *ps = reinterpret_cast<const R *>(rp + (size_t)p * rbytes);
                         R v[8];
 #pragma unroll
                         for (int q = 0; q < 8; ++q) v[q] = R(0);
-                        const R w2 = ps[2 * M2 + t2], dw2 = ps[OFF_D + 2 * M2 + t2];
+                        const R w2 = rw2[p], dw2 = rd2[p];
 #pragma unroll
                         for (int k = 0; k < NR; ++k) {
-                            const int r = min(t1 + RPG * k, M2 - 1);
-                            const R w1 = row_on(k) ? ps[M2 + r] : R(0);
-                            const R d1 = (row_on(k) ? ps[OFF_D + M2 + r] : R(0)) * w2, d2 = w1 * dw2;
+                            const R w1 = row_on(k) ? rw1[p][k] : R(0);
+                            const R d1 = (row_on(k) ? rd1[p][k] : R(0)) * w2, d2 = w1 * dw2;
                             const R w12 = w1 * w2;
                             v[0] = fma(sr[p][k], w12, v[0]);
                             v[1] = fma(si[p][k], w12, v[1]);
@@ -274,12 +298,10 @@ __global__ __launch_bounds__((LineBatch<R, M2, GRAD>::threads), (LineBatch<R, M2
                     R v[2 * G];
 #pragma unroll
                     for (int p = 0; p < G; ++p) {
-                        const R *ps = reinterpret_cast<const R *>(rp + (size_t)min(p, np - 1) * rbytes);
                         v[2 * p] = v[2 * p + 1] = R(0);
-                        const R w2 = ps[2 * M2 + t2];
 #pragma unroll
                         for (int k = 0; k < NR; ++k) {
-                            const R w12 = (row_on(k) ? ps[M2 + min(t1 + RPG * k, M2 - 1)] : R(0)) * w2;
+                            const R w12 = (row_on(k) ? rw1[p][k] : R(0)) * rw2[p];
                             v[2 * p] = fma(sr[p][k], w12, v[2 * p]);
                             v[2 * p + 1] = fma(si[p][k], w12, v[2 * p + 1]);
                         }
@@ -309,13 +331,16 @@ static hipError_t interp_lines_m(const Xform *dxf, int B, int ngroups, int n0, i
     if (e != hipSuccess) return e;
     if (ngroups < 1) return hipSuccess;
     // plane ranges of whole phases, enough of them for a few items per
-    // workgroup (each range reads 2m - 1 planes more than it has)
-    const int per_cu = LB::two ? 2 : 1;
+    // workgroup (each range reads 2m - 1 planes more than it has); of fewer
+    // planes where these would leave workgroups out
+    const int slots = cu_count() * (LB::two ? 2 : 1);
     const int phases = (n0 + LB::DZ - 1) / LB::DZ;
-    const int ranges = std::max(1, std::min(phases, 4 * per_cu * cu_count() / ngroups));
-    const int grid = (int)std::min<long long>(cu_count() * per_cu, (long long)ngroups * ranges);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(LB::threads), LB::lds, s, dxf, B, ngroups, ranges, queue, T, rec,
-                       (int)rec_bytes, cs, outs);
+    int ranges = std::max(1, std::min(phases, 4 * slots / ngroups));
+    const bool fine = (long long)ngroups * ranges < slots;
+    if (fine) ranges = std::max(ranges, std::min((n0 + kLineZ - 1) / kLineZ, (slots + ngroups - 1) / ngroups));
+    const int grid = (int)std::min<long long>(slots, (long long)ngroups * ranges);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(LB::threads), LB::lds, s, dxf, B, ngroups, ranges, fine ? 1 : 0, queue, T,
+                       rec, (int)rec_bytes, cs, outs);
     return hipGetLastError();
 }
 

@@ -459,23 +459,6 @@ bool use_ring(const hpnfft_plan_s *p, const Tiling &t)
     return true;
 }
 
-// Whether the forward gathers the points of line-method transforms too: float64
-// plans that would interpolate by ring sweeps, below a density of points per
-// cell.  A ring sweep's batch of 16 points takes the time of its matrix products
-// however few points its eight lines hold.  Measured (2m = 8, N = 64^3, forward,
-// us, ring against gather; register windows before either): 119 / 45 (106) at
-// 0.01 points per cell, 147 / 74 (122) at 0.05, 154 / 113 (140) at 0.1, 162 / 151 (158)
-// at 0.15, 179 / 189 (173) at 0.2.
-constexpr double kGatherDensity = 0.15;
-bool gather_lines(const hpnfft_plan_s *p)
-{
-    if (p->prec != HPNFFT_F64 || !use_ring(p, p->til)) return false;
-    double cells = 0;
-    for (int b = 0; b < p->B; ++b)
-        if (!p->tbox[b]) cells += (double)p->hx[b].n[0] * p->hx[b].n[1] * p->hx[b].n[2];
-    return (double)(p->Mtot - p->Mbox) < kGatherDensity * cells;
-}
-
 // Whether the line-method transforms are interpolated by batches of points on
 // a line (lines.h): windows of 2m = 10 .. 16 cells (HPNFFT_LINES=0 selects
 // the staged sweep, and the gather for gradients).
@@ -487,6 +470,29 @@ bool use_lines(const hpnfft_plan_s *p)
         on = (e && e[0] == '0') ? 0 : 1;
     }
     return on && !p->det() && p->M2() >= 10 && p->M2() <= 16;
+}
+
+// Whether the points of line-method transforms are gathered too, where lines.h or
+// the ring sweep would interpolate them.
+//   * Float64 ring sweeps (forward), below a density of points per cell: a batch of
+// 16 points takes the time of its matrix products however few points its eight
+// lines hold.  Measured (2m = 8, N = 64^3, forward, us, ring against gather;
+// register windows before either): 119 / 45 (106) at 0.01 points per cell, 147 / 74
+// (122) at 0.05, 154 / 113 (140) at 0.1, 162 / 151 (158) at 0.15, 179 / 189 (173) at
+// 0.2.
+//   * Line batches of three-dimensional grids with too few line groups for the
+// chip: 16^3 cells (16 groups), float64, 2m = 16, forward, us, batches against gather:
+// 63 / 45 at 12,000 points, 259 / 186 at 80,000; 24^3 cells (36 groups) 42 / 46 and
+// 105 / 212.
+constexpr double kGatherDensity = 0.15;
+bool gather_lines(const hpnfft_plan_s *p)
+{
+    if (use_lines(p)) return p->hx[0].flat == 0 && p->ngroups < p->cus / 8;
+    if (p->prec != HPNFFT_F64 || !use_ring(p, p->til)) return false;
+    double cells = 0;
+    for (int b = 0; b < p->B; ++b)
+        if (!p->tbox[b]) cells += (double)p->hx[b].n[0] * p->hx[b].n[1] * p->hx[b].n[2];
+    return (double)(p->Mtot - p->Mbox) < kGatherDensity * cells;
 }
 
 bool tiling_fits(const hpnfft_plan_s *p, Tiling t)
@@ -1106,7 +1112,7 @@ int run_backward(hpnfft_plan_s *p, const void *f, const void *gfhat, void *grad_
     if (rc) return rc;
     {
         PhaseTimer t(p, HPNFFT_PH_GRAD);
-        const bool lines = p->any_lines && use_lines(p);
+        const bool lines = p->any_lines && use_lines(p) && !gather_lines(p);
         HCHECK(launch_interp_gather<R>(p->m, true, dxf, p->B, lines ? GATHER_BOXES : GATHER_ALL, p->det() ? 0 : p->til.Zs,
                                        lines ? p->Mbox : p->Mtot, p->at<unsigned char>(L.rec), L.rec_bytes,
                                        p->at<R>(L.outs), s));
