@@ -608,7 +608,9 @@ void build_layout(hpnfft_plan_s *p)
         Xform &X = p->hx[b];
         X.ntx = (X.n[2] + T - 1) / T;
         X.nty = (X.n[1] + T - 1) / T;
-        X.nslab = (X.n[0] + Zs - 1) / Zs;
+        // (a leading dim without a coordinate holds every point at plane 0, with the
+        // unit impulse there: no slab past the first receives anything)
+        X.nslab = X.flat > 0 ? 1 : (X.n[0] + Zs - 1) / Zs;
         p->keys[b] = (long long)X.ntx * X.nty * T * T * X.n[0] + 1;
         for (int d = 0; d < 3; ++d) X.nbox[d] = X.gbox[d] = 0;
         if (p->tbox[b]) {

@@ -79,7 +79,8 @@ __global__ __launch_bounds__(1024) void k_spread_slab(const Xform *__restrict__ 
         // tasks: line W.lb + t / nq, planes from z0 + Q (t % nq) on.  A
         // wavefront's line and quad advance by constant steps; lines / T by
         // multiplication (exact: fewer than 1024 lines, T <= 32).
-        const int nq = (zs + Q - 1) / Q, nl = W.le - W.lb;
+        const bool flat = X->flat > 0;  // (plane 0 only receives anything)
+        const int nq = flat ? 1 : (zs + Q - 1) / Q, nl = W.le - W.lb;
         const int dl = nw / nq, dq = nw - dl * nq;
         const int inv_t = 65536 / T + 1;
         // the dim-0 weights of four planes are one aligned vector when the
@@ -223,7 +224,8 @@ __global__ __launch_bounds__(1024) void k_spread_slab(const Xform *__restrict__ 
                     }
 #pragma unroll
                     for (int q = 0; q < Q; ++q) {
-                        if (q < fmin || q >= fmax + M2) continue;  // no point of the batch reaches the plane
+                        // no point of the batch reaches the plane
+                        if (q < fmin || q >= fmax + M2 || (q > 0 && flat)) continue;
                         re[q] = Mat<R>::mul(wr[q], b, re[q]);
                         ie[q] = Mat<R>::mul(wi[q], b, ie[q]);
                     }
