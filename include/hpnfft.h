@@ -165,10 +165,12 @@ int hpnfft_get_method(hpnfft_plan plan, int *method);
  * run as ring sweeps (one wavefront per block of 8 lines through the whole
  * slab; environment variable HPNFFT_RING=0 selects the staged sweeps
  * instead); threads is then 512 whatever is passed.  With 2m = 10 .. 16 (the
- * default: 8, 8, or 4, 8 for small grids) the spread keeps the tiling, and
- * the interpolation runs by batches of points on a line whatever the tiling
+ * default: 8, 8, or 4, 8 for small float64 grids) the spread keeps the tiling,
+ * and the interpolation runs by batches of points on a line whatever the tiling
  * (environment variable HPNFFT_LINES=0 selects the staged sweep, and the
- * gather for gradients). */
+ * gather for gradients).  It gathers each point's window instead where there
+ * is little to share: plans of few lines in all, and float64 plans of 2m = 8
+ * with few points per cell (forward).  The results agree to rounding. */
 int hpnfft_set_tiles(hpnfft_plan plan, int tile, int slab, int threads);
 int hpnfft_get_tiles(hpnfft_plan plan, int *tile, int *slab, int *threads);
 

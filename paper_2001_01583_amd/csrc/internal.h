@@ -171,7 +171,8 @@ constexpr int kPolyF64 = 17;
 constexpr int kPolyMax = 17;
 
 // LDS layout of the spread / interpolation kernels (bytes from the start of
-// the dynamic LDS block).  kind: 0 spread, 1 interpolation, 2 gradient.
+// the dynamic LDS block).  kind: 0 spread, 1 interpolation, 2 an interpolation
+// with gradients, of which only the size is used (tilings of gradient plans).
 //   [tile][stage: cap records][slot maps: 2 x cap ints][run_p0: 3T^2][run_soff: 3T^2+1]
 //   [scan scratch: 32 ints][a 16-byte cell that is never changed]
 //   [interpolation outputs: cap x 2 NO reals]

@@ -42,15 +42,16 @@ template <> struct Complex<double> { typedef double T __attribute__((ext_vector_
 // SPLIT (float32 gradients, 2m = 8): a line record's window is summed in the
 // parts that the slabs of Zs planes cut it into, each part over the lanes
 // first, and column slots stay on their lanes: the order in which the staged
-// line sweeps add, so that the sums (which the differentiable transform and
-// the Ewald forces return widened to float64) do not depend on the sweep.
+// line sweeps add, so that the sums of a given grid (which the differentiable
+// transform and the Ewald forces return widened to float64) are theirs bit for bit.
 // Bound by the compute unit's scalar unit; its own branch with 32-bit element
 // indices, all weights loaded at once and no conditions where no slab cuts the
 // window: N = 64^3, 2^20 points 0.62 -> 0.39 ms, 2^21 points 1.24 -> 0.78 ms (the
 // staged line sweep: 0.47 and 0.85 ms).
 // A box record's window likewise (Zs > 0), in the parts that the boxes of gbox
 // bins cut it into, the rows of a part on consecutive lanes (165,888 ions on
-// 256^3: 0.18 ms, 0.09 ms as one sum per window).
+// 256^3: 0.18 ms, 0.09 ms as one sum per window, which moves the Ewald forces by
+// 2.8e-7).
 template <typename R, int M2, bool GRAD>
 __global__ __launch_bounds__(kGatherThreads) void k_interp_gather(const Xform *__restrict__ xfs, int B, int which, int Zs,
                                                                   int zinv, long long total, long long per_xcd,

@@ -378,9 +378,12 @@ long long box_max_cells(const hpnfft_plan_s *p, Tiling t)
 //   at 0.02 is the fastest: 48 transforms 3364 us, 3628 at 0.05, 3804 at 0.08
 // A grid with fewer output boxes than compute units leaves some idle: at 32^3
 // (64 boxes) the lines win from 0.035 on with 2m = 16 (234 / 218 at 0.04) and
-// from 0.05 with 2m = 12 (209 / 197 at 0.055).  The switch stays at one density
-// per precision all the same: a tiling that a program sets is one of boxes or
-// of lines, and is accepted for the method that its density has selected.
+// from 0.05 with 2m = 12 (209 / 197 at 0.055).  One density per precision is
+// therefore the wrong side of some crossings: single float32 plans between 0.02
+// and about 0.07 would run faster on boxes, float64 plans of 2m = 16 between 0.07
+// (0.035 on small grids) and 0.1 on lines.  A rule by 2m and the number of
+// transforms has to come with a tiling check that takes a program's tiling for
+// either method, since the method decides which tilings set_tiles accepts.
 constexpr double kBoxDensityF64 = 0.1;
 constexpr double kBoxDensityF32 = 0.02;
 // The method of every transform (a batch may mix them: sparse transforms
@@ -442,8 +445,8 @@ bool whole_groups(const hpnfft_plan_s *p)
 // multiple of 8: set_points, adjoint and forward at N = 30 x 20 x 112, 124,905
 // points, float32 252 -> 194 us; adjoint and forward at 90 x 98 x 100, 10^6
 // clustered points, float32 1380 -> 734 us.  Gradient plans with such grids
-// keep the staged spread: their tiling sets the order of the float32
-// gradients' sums.
+// keep the staged sweeps: in float32 their tiling sets the order of the
+// gradients' sums; in float64 the ring sweeps were not measured there.
 bool use_ring(const hpnfft_plan_s *p, const Tiling &t)
 {
     static int on = -1;
@@ -503,8 +506,8 @@ bool tiling_fits(const hpnfft_plan_s *p, Tiling t)
         // box edges (dims 1, 2: T; dim 0: Zs) of at least m cells
         const Tiling bt = box_tiling(p, t);
         if (bt.T < p->m || bt.Zs < p->m) return false;
-        // 16 bytes per cell of a box (the deterministic spread's tile) beside
-        // run lists, in LDS
+        // 16 bytes per cell of a box beside run lists, in LDS: the deterministic
+        // spread's tile (other plans accept the same tilings)
         if (box_max_cells(p, bt) * 16 + 12 * 1024 > (long long)kLdsLimit) return false;
         if (p->boxes) return true;
     }
@@ -512,6 +515,8 @@ bool tiling_fits(const hpnfft_plan_s *p, Tiling t)
     bool comp = p->prec == HPNFFT_F32;
     if (!(use_ring(p, t) && whole_groups(p)) && !lds_fit(t.T, t.Zs, p->M2(), p->rbytes(), 0, comp).cap) return false;
     if (!lds_fit(t.T, t.Zs, p->M2(), p->rbytes(), 1, false).cap) return false;
+    // (a layout with four outputs per point: no kernel has it, but gradient plans
+    // accept the tilings that it fits, and their defaults follow from it)
     if (p->grad() && !lds_fit(t.T, t.Zs, p->M2(), p->rbytes(), 2, false).cap) return false;
     return true;
 }

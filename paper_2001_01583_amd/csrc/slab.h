@@ -30,6 +30,11 @@
 // 0.82 ms, 2m = 12 1.36 -> 0.62 ms; 200,000 points on 96^3, 2m = 16 0.64 ->
 // 0.24 ms; 150,001 points on 96 x 72 x 120, 2m = 12 0.45 -> 0.18 ms; 4096 points
 // on 32^3 85 -> 28 us.
+//
+// Grids of one and two dimensions (flat): the window along the missing
+// dimension is the cell 0 alone, so the plan has one slab and the sweep holds its
+// first plane (d = 2, 256^2, 400,000 points, 2m = 16, float32 adjoint: 0.61 ms with
+// all planes, 0.21 ms).
 #pragma once
 
 #include "mat.h"
